@@ -46,28 +46,91 @@ struct BlockArgs {
     uint32_t *err_clear;
 };
 
+// LDS of a block sort of THREADS x ITEMS elements.
+template <typename K, bool HAS_V, int THREADS, int ITEMS>
+struct BlockLds {
+    static constexpr int W = THREADS / kWave;
+    static constexpr size_t kStageBytes = (size_t)THREADS * ITEMS * sizeof(K) * (HAS_V ? 2 : 1);
+    static_assert((size_t)W * kRadix * 8 <= kStageBytes, "mask table lives in the staging buffer");
+    uint32_t wcnt[W * kRadix];
+    uint32_t tmp[8];
+    __attribute__((aligned(16))) unsigned char stage[kStageBytes];
+};
+
+// The counting sorts of the 8-bit digit positions in `digits` (bit p:
+// position p), lowest first, of a workgroup's elements in registers: item j
+// of lane l is element j*64 + l of its wave's run, before and after.
 template <typename K, typename V, bool HAS_V, int THREADS, int ITEMS>
-__global__ __launch_bounds__(THREADS) void k_block_sort(BlockArgs a)
+__device__ __forceinline__ void block_sort_digits(BlockLds<K, HAS_V, THREADS, ITEMS> &L,
+                                                  K (&key)[ITEMS], V (&val)[HAS_V ? ITEMS : 1],
+                                                  uint32_t digits)
 {
     constexpr int CAP = THREADS * ITEMS;
     constexpr int W = THREADS / kWave;
-    constexpr int D = num_passes<K, kRadixBits>();
-    constexpr size_t kStageBytes = (size_t)CAP * (sizeof(K) + (HAS_V ? sizeof(V) : 0));
-    static_assert((size_t)W * kRadix * 8 <= kStageBytes, "mask table lives in the staging buffer");
-
-    __shared__ uint32_t s_wcnt[W * kRadix];
-    __shared__ uint32_t s_tmp[8];
-    __shared__ uint32_t s_item;
-    __shared__ __attribute__((aligned(16))) unsigned char s_stage[kStageBytes];
-    K *s_k = (K *)s_stage;
-    V *s_v = (V *)(s_stage + (size_t)CAP * sizeof(K));
-    uint64_t *s_mask = (uint64_t *)s_stage;
-
+    K *s_k = (K *)L.stage;
+    V *s_v = (V *)(L.stage + (size_t)CAP * sizeof(K));
+    uint64_t *s_mask = (uint64_t *)L.stage;
     const uint32_t t = threadIdx.x;
     const uint32_t w = t / kWave;
     const uint32_t lane = t % kWave;
     const uint32_t off0 = w * (kWave * ITEMS) + lane;
-    uint32_t *wc = s_wcnt + w * kRadix;
+    uint32_t *wc = L.wcnt + w * kRadix;
+    for (; digits; digits &= digits - 1) {
+        const int shift = __builtin_ctz(digits) * kRadixBits;
+        for (int i = t; i < W * kRadix; i += THREADS) {
+            L.wcnt[i] = 0;
+            s_mask[i] = 0;
+        }
+        __syncthreads();
+        uint32_t rank[ITEMS];
+        wave_rank<kRadixBits, K, ITEMS>(key, shift, wc, s_mask + w * kRadix, lane, rank);
+        __syncthreads();
+        // exclusive offsets over (digit, wave): digit-major, so that
+        // earlier waves (earlier elements) come first within a digit
+        uint32_t cnt = 0;
+        if (t < kRadix) {
+#pragma unroll
+            for (int ww = 0; ww < W; ++ww) {
+                const uint32_t c = L.wcnt[ww * kRadix + t];
+                L.wcnt[ww * kRadix + t] = cnt;
+                cnt += c;
+            }
+        }
+        const uint32_t excl = bins_exclusive_scan<kRadix>(cnt, L.tmp);
+        if (t < kRadix) {
+#pragma unroll
+            for (int ww = 0; ww < W; ++ww)
+                L.wcnt[ww * kRadix + t] += excl;
+        }
+        __syncthreads();
+#pragma unroll
+        for (int j = 0; j < ITEMS; ++j) {
+            const uint32_t pos = rank[j] + wc[digit_of<kRadixBits>(key[j], shift)];
+            s_k[pos] = key[j];
+            if constexpr (HAS_V)
+                s_v[pos] = val[j];
+        }
+        __syncthreads();
+#pragma unroll
+        for (int j = 0; j < ITEMS; ++j) {
+            key[j] = s_k[off0 + j * kWave];
+            if constexpr (HAS_V)
+                val[j] = s_v[off0 + j * kWave];
+        }
+        __syncthreads();
+    }
+}
+
+template <typename K, typename V, bool HAS_V, int THREADS, int ITEMS>
+__global__ __launch_bounds__(THREADS) void k_block_sort(BlockArgs a)
+{
+    constexpr int D = num_passes<K, kRadixBits>();
+    __shared__ BlockLds<K, HAS_V, THREADS, ITEMS> L;
+    __shared__ uint32_t s_item;
+    const uint32_t t = threadIdx.x;
+    const uint32_t w = t / kWave;
+    const uint32_t lane = t % kWave;
+    const uint32_t off0 = w * (kWave * ITEMS) + lane;
     const K *kin = (const K *)a.kin;
     const V *vin = (const V *)a.vin;
     K *kout = (K *)a.kout;
@@ -115,50 +178,7 @@ __global__ __launch_bounds__(THREADS) void k_block_sort(BlockArgs a)
             }
         }
 
-        for (int p = 0; p < D; ++p) {
-            const int shift = p * kRadixBits;
-            for (int i = t; i < W * kRadix; i += THREADS) {
-                s_wcnt[i] = 0;
-                s_mask[i] = 0;
-            }
-            __syncthreads();
-            uint32_t rank[ITEMS];
-            wave_rank<kRadixBits, K, ITEMS>(key, shift, wc, s_mask + w * kRadix, lane, rank);
-            __syncthreads();
-            // exclusive offsets over (digit, wave): digit-major, so that
-            // earlier waves (earlier elements) come first within a digit
-            uint32_t cnt = 0;
-            if (t < kRadix) {
-#pragma unroll
-                for (int ww = 0; ww < W; ++ww) {
-                    const uint32_t c = s_wcnt[ww * kRadix + t];
-                    s_wcnt[ww * kRadix + t] = cnt;
-                    cnt += c;
-                }
-            }
-            const uint32_t excl = bins_exclusive_scan<kRadix>(cnt, s_tmp);
-            if (t < kRadix) {
-#pragma unroll
-                for (int ww = 0; ww < W; ++ww)
-                    s_wcnt[ww * kRadix + t] += excl;
-            }
-            __syncthreads();
-#pragma unroll
-            for (int j = 0; j < ITEMS; ++j) {
-                const uint32_t pos = rank[j] + wc[digit_of<kRadixBits>(key[j], shift)];
-                s_k[pos] = key[j];
-                if constexpr (HAS_V)
-                    s_v[pos] = val[j];
-            }
-            __syncthreads();
-#pragma unroll
-            for (int j = 0; j < ITEMS; ++j) {
-                key[j] = s_k[off0 + j * kWave];
-                if constexpr (HAS_V)
-                    val[j] = s_v[off0 + j * kWave];
-            }
-            __syncthreads();
-        }
+        block_sort_digits<K, V, HAS_V, THREADS, ITEMS>(L, key, val, (1u << D) - 1u);
 
 #pragma unroll
         for (int j = 0; j < ITEMS; ++j) {

@@ -42,10 +42,31 @@ constexpr uint32_t kFlagMask = 3u << 30;
 constexpr uint32_t kCountMask = (1u << 30) - 1;
 
 // Control block (u32 words at the start of the workspace).
-constexpr int kCtrlTileCounter = 0;  // [0, 16): dynamic tile id per pass
-constexpr int kCtrlPlan = 16;        // [16, 32): plan word per pass
+constexpr int kCtrlTileCounter = 0;  // [0, 16): dynamic tile id per pass slot
+constexpr int kCtrlPlan = 16;        // [16, 32): plan word per pass slot
+constexpr int kCtrlStageDone = 32;   // [32, 48): tiles done per stage of k_last
 constexpr int kCtrlFinal = 48;       // final copy: 0 none, 1 tmp -> out
+constexpr int kCtrlFinish = 49;      // run finish word (kFinish*), 0: none
+constexpr int kCtrlUnsorted = 50;    // a long run is out of order: k_last has work
+constexpr int kCtrlLongLen = 51;     // long runs listed by k_finish
+constexpr int kCtrlGiant = 52;       // an unsorted run is too long for one workgroup
+constexpr int kCtrlDigits = 53;      // bit p: digit position p moves data
+constexpr int kCtrlSkew = 54;        // bit p: digit position p is skewed
+constexpr int kCtrlSlots = 55;       // pass slots in use
+constexpr int kCtrlRestClaim = 57;   // work claims of k_last: (stage, tile) items,
+constexpr int kCtrlLongClaim = 58;   // long runs,
+constexpr int kCtrlLongDone = 59;    // and long runs finished;
+constexpr int kCtrlLongerLen = 60;   // those too long for a wave: listed,
+constexpr int kCtrlLongerClaim = 61; // claimed
+constexpr int kCtrlLongerDone = 62;  // and finished
 constexpr int kCtrlWords = 64;
+
+// Run finish word: the array is sorted by its bits from kFinishShift up; the
+// runs of equal high bits are then put in order by k_finish.
+constexpr uint32_t kFinishRun = 1u;
+constexpr int kFinishSrcShift = 2;   // buffer id, 2 bits
+constexpr int kFinishDstShift = 4;   // buffer id, 2 bits
+constexpr int kFinishShift = 8;      // bit position of the lowest digit sorted, 6 bits
 
 // Error word: the same index in the control block of the plain and of the
 // segmented sort, read back by the host after the stream completes.
@@ -67,7 +88,7 @@ constexpr uint32_t kDefaultSpinLimit = 1u << 22;
 constexpr uint32_t kStallLookback = 1u;
 constexpr uint32_t kStallClaim = 2u;
 
-// Plan word of one pass.
+// Plan word of one pass slot.
 constexpr uint32_t kPlanRun = 1u;          // the pass moves data
 constexpr uint32_t kPlanCopyIn = 2u;       // no pass runs: copy the keys in -> out here
 constexpr int kPlanSrcShift = 2;           // buffer id, 2 bits
@@ -77,6 +98,7 @@ constexpr uint32_t kPlanBallot = 64u;      // skewed digit: rank with ballots, n
 constexpr uint32_t kPlanFirst = 128u;      // the first moving pass (reads the input)
 constexpr uint32_t kPlanLast = 256u;       // the last moving pass, writing the output
 constexpr uint32_t kPlanCopyInV = 512u;    // no pass runs: copy the values in -> out here
+constexpr int kPlanDigitShift = 12;        // digit position of the slot, 4 bits
 
 template <typename K>
 struct KeyTraits;
@@ -216,6 +238,31 @@ __device__ __forceinline__ uint32_t wave_inclusive_scan(uint32_t v)
     v += row_shr<8>(v);
     v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x142, 0xa, 0xf, false);
     v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x143, 0xc, 0xf, false);
+    return v;
+}
+
+// The largest of the wave's values, in its last lane (the same steps).
+__device__ __forceinline__ uint32_t wave_max(uint32_t v)
+{
+    v = max(v, row_shr<1>(v));
+    v = max(v, row_shr<2>(v));
+    v = max(v, row_shr<4>(v));
+    v = max(v, row_shr<8>(v));
+    v = max(v, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x142, 0xa, 0xf, false));
+    v = max(v, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x143, 0xc, 0xf, false));
+    return v;
+}
+
+// The sum of the wave's values, in its last lane (the same steps).
+__device__ __forceinline__ float wave_sum(float v)
+{
+    auto step = [&](auto moved) { v += __int_as_float(moved); };
+    step(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x111, 0xf, 0xf, false));
+    step(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x112, 0xf, 0xf, false));
+    step(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x114, 0xf, 0xf, false));
+    step(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x118, 0xf, 0xf, false));
+    step(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x142, 0xa, 0xf, false));
+    step(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x143, 0xc, 0xf, false));
     return v;
 }
 

@@ -105,6 +105,9 @@ struct HistArgs {
     uint32_t kmap;        // key order (kMap*), applied to every key read
     uint32_t fine;        // small sorts: up to 16 keys per thread, key by key,
                           // instead of batches (n <= 16 * grid * kHistThreads)
+    void *sample;         // when not null: a sample of the mapped keys for k_plan
+    uint32_t sample_every;  // a batch in this many gives to the sample,
+    uint32_t sample_step;   // one key of a thread in this many
 };
 
 // Counters of k_hist: per digit position and per bin, kHistCols columns of
@@ -209,6 +212,8 @@ __global__ __launch_bounds__(kHistThreads) void k_hist(HistArgs a)
                     hist_add<R, COLS>(tab, p, digit_of<R>(k, p * R), col);
             }
         }
+        if (a.sample && gtid % a.sample_step == 0)
+            ((K *)a.sample)[gtid / a.sample_step] = map_in(key[0], a.kmap);
         __syncthreads();
         if (a.part)
             hist_store<D, R, COLS>(tab, a.part + (uint64_t)blockIdx.x * ((uint32_t)D << R), t);
@@ -242,6 +247,9 @@ __global__ __launch_bounds__(kHistThreads) void k_hist(HistArgs a)
             for (int i = 0; i < NK; ++i)
                 key[i] = map_in(key[i], a.kmap);
         }
+        if (a.sample && b % a.sample_every == 0 && t % a.sample_step == 0)
+            ((K *)a.sample)[b / a.sample_every * (kHistThreads / a.sample_step) +
+                            t / a.sample_step] = key[0];
 #pragma unroll
         for (int p = 0; p < D; ++p) {
 #pragma unroll
@@ -270,9 +278,11 @@ __global__ __launch_bounds__(kHistThreads) void k_hist(HistArgs a)
 // ---------------------------------------------------------------------------
 // k_plan (one workgroup, 256 threads per row group): digit_base = exclusive scan of each
 // histogram row (the counting sort's starting offsets), and the plan of
-// every pass.  A pass whose digit is the same for all n keys is the identity
-// permutation and is skipped; the remaining passes alternate between the
-// output and the scratch copy so that the last one lands in the output.
+// every pass slot.  A digit that is the same for all n keys gives the identity
+// permutation and gets no slot; the remaining digits take the slots in order,
+// the lowest first, and alternate between the output and the scratch copy so
+// that the last one lands in the output.  With a.finish the slots may hold
+// the high digits only, and k_finish sorts by the rest.
 
 struct PlanArgs {
     uint32_t *hist;         // [d][2^R]: read; or written, as the sum of part
@@ -284,7 +294,74 @@ struct PlanArgs {
     int keys_in_place;  // keys_out == keys_in
     int vals_in_place;  // pairs with vals_out == vals_in (0 for keys only)
     int limit;          // digit positions [0, limit) are sorted (the whole key: d)
+    int slots;          // pass slots launched (at least 1)
+    int finish;         // k_finish is launched too: the plan may leave low digits to it
+    const void *sample;     // k_hist's sample of the mapped keys when finish is set
+    uint32_t sample_count;  // at most kSampleMax per thread
+    uint32_t allow;         // repeats accepted in the sample (see kFinishMean)
 };
+
+// When the plan may stop at a high digit position.  The passes then sort by
+// the bits from that position up, and k_finish orders the runs of keys that
+// share them.  Both tests below estimate a run's length:
+//   * kFinishMean  n times the product of the sorted digits' largest shares:
+//     the mean run at the densest place if the digits were independent.
+//   * a sample of the keys: how many share the sorted bits with a key before
+//     them in the sample, but not all bits, against the number that runs of
+//     kFinishRepeatMean elements would give.  It sees what the first test
+//     cannot, digits that depend on each other (a few thousand identifiers
+//     in the high half, say).
+// Where the sample holds repeats of whole keys (kSampleSame), keys come in
+// groups, and a run that two groups share is long: then no two different
+// keys of the sample may share the sorted bits and, unless most of the
+// sample are repeats (it has then seen most groups), kFinishMeanSame takes the
+// place of kFinishMean, so that hardly any run holds two groups.
+// A wrong guess costs time only: k_finish lists the runs it could not order
+// and k_last sorts them.
+constexpr float kFinishMean = 32.f;
+constexpr float kFinishMeanSame = 1.f / 32.f;
+constexpr uint32_t kSampleSame = 4;
+constexpr uint32_t kFinishRepeatMean = 48;
+// k_finish costs about a pass, so it has to save two (this also leaves the
+// last slot free for k_last).
+constexpr int kFinishSaves = 2;
+constexpr uint32_t kSampleMax = 4;        // keys sampled per thread, at most
+constexpr uint32_t kSampleThreads = 1024; // threads of k_plan with 8-bit digits
+constexpr uint32_t kSampleTab = 2 * kSampleMax * kSampleThreads;  // hash table slots
+
+// Sampled keys whose bits from `shift` up equal those of another one counted
+// before, from an LDS hash table (open addressing on a 32-bit hash; 32-bit
+// keys hash one to one).  The table is clear, *out zero; one barrier after
+// the call *out holds the count.  Called by every thread.
+template <typename K>
+__device__ __forceinline__ void sample_repeats(const K (&key)[kSampleMax], uint32_t count,
+                                               int shift, uint32_t *tag, uint32_t *out)
+{
+    const uint32_t t = threadIdx.x;
+    uint32_t repeats = 0;
+#pragma unroll
+    for (uint32_t j = 0; j < kSampleMax; ++j) {
+        bool again = false;
+        if (j * kSampleThreads + t < count) {
+            const K x = key[j] >> shift;
+            uint32_t h;
+            if constexpr (sizeof(K) == 8)
+                h = (uint32_t)((x * 0x9E3779B97F4A7C15ull) >> 32);
+            else
+                h = x * 0x9E3779B1u;
+            h = h ? h : 1u;
+            uint32_t s = (h >> 19) & (kSampleTab - 1);
+            // the table holds twice the sample: a free slot or a match is found
+            uint32_t old;
+            while ((old = atomicCAS(&tag[s], 0u, h)) != 0 && old != h)
+                s = (s + 1) & (kSampleTab - 1);
+            again = old == h;
+        }
+        repeats += (uint32_t)__popcll(__ballot(again));
+    }
+    if (t % kWave == 0 && repeats)
+        atomicAdd(out, repeats);
+}
 
 // Rows are scanned side by side: row group g (threads [256 g, 256 g + 256))
 // takes rows g, g + G, g + 2 G, ... (G = plan_groups row groups); a group's
@@ -306,16 +383,37 @@ __global__ __launch_bounds__(kRadix * 4) void k_plan(PlanArgs a)
     constexpr int BPT = NB > kRadix ? NB / kRadix : 1;
     constexpr int WPG = kRadix / kWave;  // waves per group
     __shared__ uint32_t s_tot[G][WPG];
-    __shared__ unsigned long long s_sq[G][WPG];
+    __shared__ float s_sq[G][WPG];
     __shared__ int s_trivial[D];
     __shared__ int s_skewed[D];
+    __shared__ uint32_t s_max[D];  // the largest bin of each row
     const uint32_t t = threadIdx.x;
     const uint32_t g = t / kRadix;
     const uint32_t lt = t % kRadix;
     const uint32_t w = lt / kWave;
     const bool active = lt * BPT < (uint32_t)NB;
-    if (t < (uint32_t)D)
+    if (t < (uint32_t)D) {
         s_trivial[t] = 0;
+        s_max[t] = 0;
+    }
+    // the sampled keys and a clear table for them (8-bit digits only)
+    __shared__ uint32_t s_tag[R == 8 ? kSampleTab : 1], s_tag_same[R == 8 ? kSampleTab : 1];
+    __shared__ uint32_t s_repeats, s_same;
+    K sample[kSampleMax] = {};
+    if (R == 8 && a.finish) {
+#pragma unroll
+        for (uint32_t j = 0; j < kSampleMax; ++j)
+            if (j * kSampleThreads + t < a.sample_count)
+                sample[j] = ((const K *)a.sample)[j * kSampleThreads + t];
+        for (uint32_t i = t; i < kSampleTab; i += kSampleThreads) {
+            s_tag[i] = 0;
+            s_tag_same[i] = 0;
+        }
+        if (t == 0) {
+            s_repeats = 0;
+            s_same = 0;
+        }
+    }
     // the control block starts cleared (claim counters, error word); the
     // plan words are written at the end, after barriers
     for (uint32_t i = t; i < (uint32_t)kCtrlWords; i += blockDim.x)
@@ -374,25 +472,28 @@ __global__ __launch_bounds__(kRadix * 4) void k_plan(PlanArgs a)
         const int p = r * G + (int)g;
         uint32_t sum = 0;
         bool full = false;
-        unsigned long long sq = 0;
+        float sq = 0.f;
 #pragma unroll
         for (int i = 0; i < BPT; ++i) {
             sum += cnt[r][i];
             full = full || cnt[r][i] == a.n;
-            sq += (unsigned long long)cnt[r][i] * cnt[r][i];
+            sq += (float)cnt[r][i] * (float)cnt[r][i];
         }
         // exclusive scan of the row over the group's threads
         const uint32_t inc = wave_inclusive_scan(sum);
         // chance that two keys share this digit: sum_b (c_b / n)^2
-#pragma unroll
-        for (int off = 32; off > 0; off >>= 1)
-            sq += __shfl_xor(sq, off);
-        if ((lt & (kWave - 1)) == kWave - 1)
+        sq = wave_sum(sq);
+        if ((lt & (kWave - 1)) == kWave - 1) {
             s_tot[g][w] = inc;
-        if ((lt & (kWave - 1)) == 0)
             s_sq[g][w] = sq;
+        }
         if (full && p < D)
             s_trivial[p] = 1;  // every writer stores the same value
+        if (a.finish && p < D) {
+            const uint32_t mx = wave_max(cnt[r][0]);
+            if ((lt & (kWave - 1)) == kWave - 1)
+                atomicMax(&s_max[p], mx);
+        }
         __syncthreads();
         uint32_t ex = inc - sum;
         for (uint32_t i = 0; i < w; ++i)
@@ -405,50 +506,122 @@ __global__ __launch_bounds__(kRadix * 4) void k_plan(PlanArgs a)
             }
         }
         if (lt == 0 && p < D) {
-            unsigned long long tot = 0;
+            float tot = 0.f;
             for (int i = 0; i < WPG; ++i)
                 tot += s_sq[g][i];
             // above 1/100 many lanes of a wave share a slot of the LDS lane-mask
             // table, whose same-address atomics serialise; ballots do not
-            // (n < 2^30, so n^2 fits 64 bits; tot <= n^2)
-            s_skewed[p] = tot > (unsigned long long)a.n * a.n / 100ull;
+            // (both rank alike, so the test need not be exact)
+            s_skewed[p] = tot > 0.01f * (float)a.n * (float)a.n;
         }
         __syncthreads();
     }
     __syncthreads();
+    const int limit = a.limit < D ? a.limit : D;
+    // the lowest digit position the passes sort: 0, or higher when k_finish
+    // can order what is left
+    int low = 0;
+    if constexpr (R == 8) {
+        if (a.finish) {
+            const float inv_n = 1.f / (float)a.n;
+            // the highest position whose runs, by the product of shares, are
+            // within `bound`; 0 if the digits below it are fewer than saved
+            auto stop_at = [&](float bound) {
+                float mean = (float)a.n;
+                int at = 0, left = 0;
+                for (int p = D - 1; p >= 0; --p) {
+                    if (s_trivial[p])
+                        continue;
+                    if (mean <= bound) {
+                        ++left;
+                    } else {
+                        mean *= (float)s_max[p] * inv_n;
+                        at = p;
+                    }
+                }
+                return left >= kFinishSaves ? at : 0;
+            };
+            low = stop_at(kFinishMean);
+            if (low) {
+                sample_repeats<K>(sample, a.sample_count, 0, s_tag_same, &s_same);
+                sample_repeats<K>(sample, a.sample_count, low * R, s_tag, &s_repeats);
+                __syncthreads();
+                const bool groups = s_same >= kSampleSame;
+                const uint32_t allow = groups ? 0u : a.allow;
+                if (groups && 2 * s_same < a.sample_count)
+                    low = min(low, stop_at(kFinishMeanSame));
+                // the sample's repeats were counted at the first choice; a
+                // lower one has no more
+                while (low && s_repeats - min(s_repeats, s_same) > allow) {
+                    int left = 0;
+                    do
+                        --low;
+                    while (low && s_trivial[low]);
+                    for (int p = 0; p < low; ++p)
+                        left += !s_trivial[p];
+                    if (left < kFinishSaves) {
+                        low = 0;
+                        break;
+                    }
+                    __syncthreads();  // every thread has read s_repeats
+                    for (uint32_t i = t; i < kSampleTab; i += kSampleThreads)
+                        s_tag[i] = 0;
+                    if (t == 0)
+                        s_repeats = 0;
+                    __syncthreads();
+                    sample_repeats<K>(sample, a.sample_count, low * R, s_tag, &s_repeats);
+                    __syncthreads();
+                }
+            }
+        }
+    }
     if (t == 0) {
-        const int limit = a.limit < D ? a.limit : D;
         int q_total = 0;
-        for (int p = 0; p < limit; ++p)
-            q_total += !s_trivial[p];
+        uint32_t digits = 0, skew = 0;
+        for (int p = 0; p < limit; ++p) {
+            if (s_trivial[p])
+                continue;
+            digits |= 1u << p;
+            skew |= s_skewed[p] ? 1u << p : 0u;
+            q_total += p >= low;
+        }
+        const bool finish = low > 0;
+        // moves of the whole array: the passes, and k_finish if it runs
+        const int moves = q_total + (finish ? 1 : 0);
         // in place if either array is: the first moving pass must not write
         // its own input
         const bool in_place = a.keys_in_place || a.vals_in_place;
-        const bool odd_in_place = in_place && (q_total & 1);
+        const bool odd_in_place = in_place && (moves & 1);
         int q = 0;
         uint32_t prev = kBufIn;
-        for (int p = 0; p < D; ++p) {
-            uint32_t plan = 0;
-            if (p < limit && !s_trivial[p]) {
-                uint32_t dst;
-                if (odd_in_place)
-                    dst = (q & 1) ? kBufOut : kBufTmp;
-                else
-                    dst = ((q_total - 1 - q) & 1) ? kBufTmp : kBufOut;
-                plan = kPlanRun | (prev << kPlanSrcShift) | (dst << kPlanDstShift) |
-                       (s_skewed[p] ? kPlanBallot : 0u) | (q == 0 ? kPlanFirst : 0u) |
-                       (q == q_total - 1 && dst == kBufOut ? kPlanLast : 0u);
-                prev = dst;
-                ++q;
-            }
-            a.ctrl[kCtrlPlan + p] = plan;
+        auto next_dst = [&] {
+            return odd_in_place ? ((q & 1) ? kBufOut : kBufTmp)
+                                : (((moves - 1 - q) & 1) ? kBufTmp : kBufOut);
+        };
+        for (int p = low; p < limit; ++p) {
+            if (s_trivial[p])
+                continue;
+            const uint32_t dst = next_dst();
+            a.ctrl[kCtrlPlan + q] = kPlanRun | (prev << kPlanSrcShift) | (dst << kPlanDstShift) |
+                                    (s_skewed[p] ? kPlanBallot : 0u) | (q == 0 ? kPlanFirst : 0u) |
+                                    (q == moves - 1 && dst == kBufOut ? kPlanLast : 0u) |
+                                    ((uint32_t)p << kPlanDigitShift);
+            prev = dst;
+            ++q;
         }
+        if (finish)
+            a.ctrl[kCtrlFinish] = kFinishRun | (prev << kFinishSrcShift) |
+                                  (next_dst() << kFinishDstShift) |
+                                  ((uint32_t)(low * R) << kFinishShift);
         // no pass moves data: the output is the input, so each array that is
         // not sorted in place is copied by the last pass launched
         if (q_total == 0)
-            a.ctrl[kCtrlPlan + (limit > 0 ? limit - 1 : 0)] =
+            a.ctrl[kCtrlPlan + a.slots - 1] =
                 (a.keys_in_place ? 0u : kPlanCopyIn) | (a.vals_in_place ? 0u : kPlanCopyInV);
         a.ctrl[kCtrlFinal] = odd_in_place ? 1u : 0u;
+        a.ctrl[kCtrlDigits] = digits;
+        a.ctrl[kCtrlSkew] = skew;
+        a.ctrl[kCtrlSlots] = (uint32_t)q_total;
     }
 }
 
@@ -458,10 +631,9 @@ __global__ __launch_bounds__(kRadix * 4) void k_plan(PlanArgs a)
 struct PassArgs {
     Bufs b;
     uint32_t n;
-    int pass;
-    int shift;
+    int pass;  // pass slot: its plan word names the digit position
     uint32_t *ctrl;
-    const uint32_t *digit_base;  // row of this pass
+    const uint32_t *digit_base;  // [d][2^R]
     uint32_t *status;            // [tiles][2^R] of this pass
     uint32_t *gagg;              // [tiles / kGroup][2^R] group aggregates (see lookback_digit)
     uint32_t *claims;            // per-XCD claim counters and group lists
@@ -976,16 +1148,15 @@ __device__ __forceinline__ void pass_tile(PassLds<K, C, HAS_V> &L, const K *tk, 
 
 namespace rs {
 
-template <typename K, typename V, bool HAS_V, typename C>
-__global__ __launch_bounds__(C::kThreads) void k_pass(PassArgs a)
+// The pass slot a.pass, by a workgroup of k_pass (or of k_last).
+template <typename K, typename V, bool HAS_V, typename C, typename Lds>
+__device__ __forceinline__ void pass_slot(const PassArgs a, Lds &L)
 {
     constexpr int THREADS = C::kThreads;
     constexpr int T = C::kTile;
-    using Lds = std::conditional_t<C::kWide, WideLds<K, C, HAS_V>, PassLds<K, C, HAS_V>>;
-    __shared__ Lds L;
 
     const uint32_t t = threadIdx.x;
-    const uint32_t plan = a.ctrl[kCtrlPlan + a.pass];
+    const uint32_t plan = __builtin_amdgcn_readfirstlane(a.ctrl[kCtrlPlan + a.pass]);
     if (!(plan & kPlanRun)) {
         if (plan & (kPlanCopyIn | kPlanCopyInV)) {
             // no pass moves data: copy in -> out (each array not sorted in place)
@@ -1010,16 +1181,19 @@ __global__ __launch_bounds__(C::kThreads) void k_pass(PassArgs a)
     const V *sv = HAS_V ? pick<const V>(a.b, src, true) : nullptr;
     K *dk = pick<K>(a.b, dstb, false);
     V *dv = HAS_V ? pick<V>(a.b, dstb, true) : nullptr;
+    const uint32_t digit = (plan >> kPlanDigitShift) & 15u;
+    const int shift = (int)digit * C::kRadixBits;
+    const uint32_t *row = a.digit_base + digit * C::kBins;
     // the starting offsets of this thread's digits, fetched early (used
     // after the look-back): digit t, or digits 2t and 2t+1 of a wide pass
     uint32_t dbase = 0;
     uint32_t db[2] = {0, 0};
     if constexpr (C::kWide) {
-        const uint2 d2 = ((const uint2 *)a.digit_base)[t];
+        const uint2 d2 = ((const uint2 *)row)[t];
         db[0] = d2.x;
         db[1] = d2.y;
     } else {
-        dbase = t < (uint32_t)C::kBins ? a.digit_base[t] : 0u;
+        dbase = t < (uint32_t)C::kBins ? row[t] : 0u;
     }
     const uint32_t xcc = t == 0 ? xcc_id() : 0u;
     // the next tile is claimed once the current tile's look-back is done:
@@ -1042,17 +1216,24 @@ __global__ __launch_bounds__(C::kThreads) void k_pass(PassArgs a)
         };
         if constexpr (C::kWide)
             pass_tile_wide<K, V, HAS_V, C>(L, sk + tb, HAS_V ? sv + tb : nullptr, dk, dv, valid,
-                                           a.n, tile, 0, a.status, db, a.shift,
+                                           a.n, tile, 0, a.status, db, shift,
                                            (plan & kPlanBallot) != 0,
                                            (plan & kPlanFirst) ? a.kmap : 0u,
                                            (plan & kPlanLast) ? a.kmap : 0u, a, claim_next);
         else
             pass_tile<K, V, HAS_V, C>(L, sk + tb, HAS_V ? sv + tb : nullptr, dk, dv, valid, a.n,
-                                      tile, 0, a.status, a.gagg, dbase, a.shift,
+                                      tile, 0, a.status, a.gagg, dbase, shift,
                                       (plan & kPlanBallot) != 0,
                                       (plan & kPlanFirst) ? a.kmap : 0u,
                                       (plan & kPlanLast) ? a.kmap : 0u, a, claim_next);
     }
+}
+
+template <typename K, typename V, bool HAS_V, typename C>
+__global__ __launch_bounds__(C::kThreads) void k_pass(PassArgs a)
+{
+    __shared__ std::conditional_t<C::kWide, WideLds<K, C, HAS_V>, PassLds<K, C, HAS_V>> L;
+    pass_slot<K, V, HAS_V, C>(a, L);
 }
 
 // ---------------------------------------------------------------------------

@@ -5,6 +5,7 @@
 // that compile in parallel.
 #pragma once
 
+#include "rs_finish.h"
 #include "rs_kernels.h"
 
 namespace rs {
@@ -19,6 +20,11 @@ struct SortOps {
     void (*plan)(const PlanArgs &, hipStream_t);
     void (*pass)(const PassArgs &, uint32_t grid, hipStream_t);
     const void *pass_kernel;  // for occupancy queries
+    // 8-bit digits only (null otherwise): the end of a sort whose passes stop
+    // at a high digit position (rs_finish.h)
+    void (*finish)(const FinishArgs &, int items, uint32_t grid, hipStream_t);
+    void (*last)(const LastArgs &, uint32_t grid, hipStream_t);
+    const void *finish_kernel;  // the larger tile
 };
 
 struct SegOps {
@@ -50,10 +56,29 @@ struct SortLaunch {
     {
         hipLaunchKernelGGL((k_pass<K, K, HAS_V, C>), dim3(grid), dim3(THREADS), 0, s, a);
     }
+    static void finish(const FinishArgs &a, int items, uint32_t grid, hipStream_t s)
+    {
+        if (items == kFinishItems)
+            hipLaunchKernelGGL((k_finish<K, K, HAS_V, kFinishThreads, kFinishItems>), dim3(grid),
+                               dim3(kFinishThreads), 0, s, a);
+        else
+            hipLaunchKernelGGL((k_finish<K, K, HAS_V, kFinishThreads, kFinishItemsSmall>),
+                               dim3(grid), dim3(kFinishThreads), 0, s, a);
+    }
+    static void last(const LastArgs &a, uint32_t grid, hipStream_t s)
+    {
+        hipLaunchKernelGGL((k_last<K, K, HAS_V, C>), dim3(grid), dim3(THREADS), 0, s, a);
+    }
     static SortOps ops()
     {
-        return SortOps{R, THREADS, ITEMS, C::kTile, num_passes<K, R>(), &hist, &plan, &pass,
-                       (const void *)k_pass<K, K, HAS_V, C>};
+        SortOps o{R, THREADS, ITEMS, C::kTile, num_passes<K, R>(), &hist, &plan, &pass,
+                  (const void *)k_pass<K, K, HAS_V, C>, nullptr, nullptr, nullptr};
+        if constexpr (R == kRadixBits) {
+            o.finish = &finish;
+            o.last = &last;
+            o.finish_kernel = (const void *)k_finish<K, K, HAS_V, kFinishThreads, kFinishItems>;
+        }
+        return o;
     }
 };
 

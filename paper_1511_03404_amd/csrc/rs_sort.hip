@@ -21,6 +21,7 @@
 #include <string.h>
 
 #include <algorithm>
+#include <cmath>
 #include <mutex>
 #include <string>
 #include <vector>
@@ -563,6 +564,19 @@ static rs_status run_sort(rs_context *ctx, const K *kin, const K *vin, K *kout, 
             hipLaunchKernelGGL(k_init, dim3(1), dim3(256), 0, s, ctrl, hist, (int)(L.d * L.bins));
         });
 
+    // With 8-bit digits the plan may leave the low digits to k_finish, and
+    // then few of the slots run; an idle launch costs 1.8 us.
+    // 32-bit keys have to stop at two of four digits to gain, so n is at
+    // most kFinishMean for each of their 2^16 values (an eighth less: the
+    // mean is taken at the densest place).
+    const bool finish = op.finish != nullptr && !debug &&
+                        (sizeof(K) == 8 || n <= ((uint64_t)kFinishMean << 16) / 8 * 7);
+    const int slots = std::max(run_passes, 1);
+    // k_hist's sample of the keys, in the scratch copy (which the first pass
+    // overwrites after k_plan has read it): 1024 keys up to 2^20, else 4096,
+    // from batches spread over the array and threads spread over a batch
+    void *sample = nullptr;
+    uint32_t sample_count = 0, allow = 0;
     HistArgs ha{};
     ha.keys = kin;
     ha.n = (uint32_t)n;
@@ -576,11 +590,34 @@ static rs_status run_sort(rs_context *ctx, const K *kin, const K *vin, K *kout, 
     uint32_t *part = (uint32_t *)(wb + L.off_part);
     ha.part = L.parts ? part : nullptr;
     ha.fine = L.hist_fine ? 1u : 0u;
+    if (finish) {
+        const uint32_t want = n <= (1u << 20) ? kSampleThreads : kSampleMax * kSampleThreads;
+        const uint32_t batches = ha.nvec * (16 / sizeof(K)) / 16384;
+        sample = wb + L.off_tmp_k;
+        ha.sample = sample;
+        ha.sample_every = 1;
+        if (ha.fine) {
+            ha.sample_step = L.hist_blocks;  // of all threads
+            sample_count = kHistThreads;
+        } else {
+            while (batches / ha.sample_every > want)
+                ha.sample_every *= 2;
+            const uint32_t from = (batches + ha.sample_every - 1) / ha.sample_every;
+            ha.sample_step = 1;
+            while (from * (kHistThreads / ha.sample_step) > want && ha.sample_step < kHistThreads)
+                ha.sample_step *= 2;
+            sample_count = std::min(from * (kHistThreads / ha.sample_step),
+                                    kSampleMax * kSampleThreads);
+        }
+        // repeats of `sample_count` draws from runs of kFinishRepeatMean
+        const double m = sample_count, runs = (double)n / kFinishRepeatMean;
+        allow = (uint32_t)std::max(3.0, m - runs * (1.0 - std::exp(-m / runs)));
+    }
     launch(ctx, s, sizeof(K) == 4 ? "k_hist_u32" : "k_hist_u64",
            [&] { op.hist(ha, L.hist_blocks, s); });
 
     PlanArgs pl{hist, part, L.parts, base, ctrl, (uint32_t)n, keys_in_place, vals_in_place,
-                run_passes};
+                run_passes, slots, finish, sample, sample_count, allow};
     launch(ctx, s, "k_plan", [&] { op.plan(pl, s); });
     // after k_plan: with row blocks, k_plan writes their sum into hist
     if (hist_out &&
@@ -602,28 +639,41 @@ static rs_status run_sort(rs_context *ctx, const K *kin, const K *vin, K *kout, 
     const uint32_t pass_grid = (uint32_t)std::min<uint64_t>(
         flat ? L.tiles : L.tiles * kXcdSlots,
         (uint64_t)resident_blocks(op.pass_kernel, op.threads) * ctx_cus(ctx));
-    // the passes of digit positions [0, run_passes); at least one is launched,
-    // which copies the input when no pass moves data
-    for (int p = 0; p < std::max(run_passes, 1); ++p) {
-        PassArgs pa{};
-        pa.b = b;
-        pa.n = (uint32_t)n;
+    PassArgs pa{};
+    pa.b = b;
+    pa.n = (uint32_t)n;
+    pa.ctrl = ctrl;
+    pa.digit_base = base;
+    pa.num_tiles = (uint32_t)L.tiles;
+    pa.num_groups = (uint32_t)((L.tiles + kClaimGroup - 1) / kClaimGroup);
+    pa.flat = flat ? 1u : 0u;
+    pa.kmap = kmap;
+    pa.err = ctrl + kCtrlError;
+    pa.spin_limit = ctx->spin_limit;
+    pa.stall = ctx->stall;
+    // the pass slots; the last one copies the input when no pass moves data,
+    // or follows up on k_finish
+    for (int p = 0; p < slots; ++p) {
         pa.pass = p;
-        pa.shift = p * op.r;
-        pa.ctrl = ctrl;
-        pa.digit_base = base + p * L.bins;
         pa.status = status + (uint64_t)p * L.tiles * L.bins;
         pa.claims = status + (uint64_t)L.d * L.tiles * L.bins + (uint64_t)p * L.claim_words;
         pa.gagg = status + (uint64_t)L.d * (L.tiles * L.bins + L.claim_words) +
                   (uint64_t)p * L.groups * L.bins;
-        pa.num_tiles = (uint32_t)L.tiles;
-        pa.num_groups = (uint32_t)((L.tiles + kClaimGroup - 1) / kClaimGroup);
-        pa.flat = flat ? 1u : 0u;
-        pa.kmap = kmap;
-        pa.err = ctrl + kCtrlError;
-        pa.spin_limit = ctx->spin_limit;
-        pa.stall = ctx->stall;
-        launch(ctx, s, pass_name<K, HAS_V>(), [&] { op.pass(pa, pass_grid, s); });
+        if (!finish || p < slots - 1) {
+            launch(ctx, s, pass_name<K, HAS_V>(), [&] { op.pass(pa, pass_grid, s); });
+            continue;
+        }
+        // the list of long runs takes the place of the passes' look-back words
+        const uint32_t list_cap =
+            (uint32_t)std::min<uint64_t>(n, (uint64_t)L.d * L.tiles * L.bins);
+        FinishArgs fa{b, (uint32_t)n, ctrl, status, list_cap, kmap};
+        const int items = n <= kFinishSmall ? kFinishItemsSmall : kFinishItems;
+        const uint32_t fgrid = (uint32_t)std::min<uint64_t>(
+            (n + kFinishThreads * items - 1) / (kFinishThreads * items),
+            (uint64_t)resident_blocks(op.finish_kernel, kFinishThreads) * ctx_cus(ctx));
+        launch(ctx, s, "k_finish", [&] { op.finish(fa, items, fgrid, s); });
+        LastArgs la{pa, status, (uint32_t)L.d, status, list_cap};
+        launch(ctx, s, "k_last", [&] { op.last(la, pass_grid, s); });
     }
     if (in_place) {
         const uint32_t blocks = (uint32_t)std::min<uint64_t>(4096, (n + 255) / 256);
