@@ -5,13 +5,21 @@
 // (one launch) and for the small and medium segments of a segmented sort.
 #pragma once
 
+#include <cstddef>
+
 #include "rs_device.h"
+#include "rs_runs.h"
 
 namespace rs {
 
-// Block-sort shapes: kSmall for up to 4096 elements (several workgroups per
-// CU), kMedium for up to 16384 (8192 for 64-bit pairs, whose staging would
-// not fit otherwise).
+// Block-sort shapes of the segmented sort: kSmall for up to 4096 elements
+// (several workgroups per CU), kMedium for up to 16384 (8192 for 64-bit pairs,
+// whose staging would not fit otherwise).  A whole sort has one workgroup, so
+// its time is a chain of latencies, above all the items that a wave ranks
+// one after another: as many threads and as few items as hold it.  Whole
+// sorts of uniform keys, one shape for all sizes and a pass for every digit
+// -> now, device time: 1000 32-bit keys 22 -> 9.5 us, 12000 32-bit pairs 50 ->
+// 29 us, 16384 64-bit keys 75 -> 37 us.
 template <typename K, bool HAS_V>
 struct BlockShape {
     static constexpr int kSmallThreads = 256;
@@ -51,86 +59,262 @@ template <typename K, bool HAS_V, int THREADS, int ITEMS>
 struct BlockLds {
     static constexpr int W = THREADS / kWave;
     static constexpr size_t kStageBytes = (size_t)THREADS * ITEMS * sizeof(K) * (HAS_V ? 2 : 1);
-    static_assert((size_t)W * kRadix * 8 <= kStageBytes, "mask table lives in the staging buffer");
+    // the lane-mask tables live in the staging buffer, which a tile of few
+    // elements makes larger than its elements need
+    static constexpr size_t kMaskBytes = (size_t)W * kRadix * 8;
     uint32_t wcnt[W * kRadix];
     uint32_t tmp[8];
-    __attribute__((aligned(16))) unsigned char stage[kStageBytes];
+    uint64_t head[2 * W];  // head words of each wave's first and last chunk
+    uint64_t diff;         // bits in which the keys differ
+    __attribute__((aligned(16))) K before[kRunMax];  // run_move's neighbours of the first keys
+    __attribute__((aligned(16))) unsigned char
+        stage[(kStageBytes > kMaskBytes ? kStageBytes : kMaskBytes) + kRunMax * sizeof(K)];
 };
 
-// The counting sorts of the 8-bit digit positions in `digits` (bit p:
-// position p), lowest first, of a workgroup's elements in registers: item j
-// of lane l is element j*64 + l of its wave's run, before and after.
+// How a workgroup holds m elements in registers: item j of lane l of wave w is
+// element (w * used + j) * 64 + l, j < used = ceil(m / THREADS) rounded up to
+// whole groups of kGroup, so that all waves have about the same number of
+// items.  Groups past `used` are skipped (a scalar branch); within a group
+// the lanes past m take part without effect, so that its items overlap.
+template <int THREADS, int ITEMS>
+struct BlockItems {
+    static constexpr int kGroup = ITEMS < 4 ? ITEMS : 4;
+    uint32_t m;
+    uint32_t used;
+    uint32_t base;  // this lane's element of item 0
+    __device__ __forceinline__ explicit BlockItems(uint32_t m_)
+        : m(__builtin_amdgcn_readfirstlane(m_)),
+          used((m + THREADS * kGroup - 1) / (THREADS * kGroup) * kGroup),
+          base(__builtin_amdgcn_readfirstlane(threadIdx.x / kWave) * used * kWave +
+               threadIdx.x % kWave)
+    {
+    }
+    // element of item j; has: there is one (for j < used)
+    __device__ __forceinline__ uint32_t at(int j) const { return base + j * kWave; }
+    __device__ __forceinline__ bool has(int j) const { return at(j) < m; }
+    template <typename F>
+    __device__ __forceinline__ void each(F &&f) const
+    {
+#pragma unroll
+        for (int g = 0; g < ITEMS; g += kGroup) {
+            if ((uint32_t)g < used) {
+#pragma unroll
+                for (int i = 0; i < kGroup; ++i)
+                    f(g + i);
+            }
+        }
+    }
+};
+
+// One stable counting sort of the workgroup's elements by the 8-bit digit at
+// bit `shift`.  The sorted keys are also left in L.stage.
 template <typename K, typename V, bool HAS_V, int THREADS, int ITEMS>
-__device__ __forceinline__ void block_sort_digits(BlockLds<K, HAS_V, THREADS, ITEMS> &L,
-                                                  K (&key)[ITEMS], V (&val)[HAS_V ? ITEMS : 1],
-                                                  uint32_t digits)
+__device__ __forceinline__ void block_sort_digit(BlockLds<K, HAS_V, THREADS, ITEMS> &L,
+                                                 const BlockItems<THREADS, ITEMS> &it,
+                                                 K (&key)[ITEMS], V (&val)[HAS_V ? ITEMS : 1],
+                                                 int shift)
 {
     constexpr int CAP = THREADS * ITEMS;
     constexpr int W = THREADS / kWave;
     K *s_k = (K *)L.stage;
+    // behind the keys, or in the place of run_move's guard there: the values
+    // are dead when the guard is written
     V *s_v = (V *)(L.stage + (size_t)CAP * sizeof(K));
     uint64_t *s_mask = (uint64_t *)L.stage;
     const uint32_t t = threadIdx.x;
     const uint32_t w = t / kWave;
     const uint32_t lane = t % kWave;
-    const uint32_t off0 = w * (kWave * ITEMS) + lane;
     uint32_t *wc = L.wcnt + w * kRadix;
-    for (; digits; digits &= digits - 1) {
-        const int shift = __builtin_ctz(digits) * kRadixBits;
-        for (int i = t; i < W * kRadix; i += THREADS) {
-            L.wcnt[i] = 0;
-            s_mask[i] = 0;
+    uint64_t *wm = s_mask + w * kRadix;
+    // a wave's counters and lane-mask table are its own: it clears them itself
+    for (uint32_t i = lane; i < (uint32_t)kRadix; i += kWave) {
+        wc[i] = 0;
+        wm[i] = 0;
+    }
+    // stable ranks within the wave, as in wave_rank; a lane past m sets no
+    // bit and takes a slot of its own, so that those lanes do not meet
+    uint32_t rank[ITEMS];
+    uint32_t *wm32 = (uint32_t *)wm + (lane >> 5);
+    it.each([&](int j) {
+        const bool has = it.has(j);
+        const uint32_t d = has ? digit_at<kRadixBits>(key[j], shift) : lane;
+        atomicOr(&wm32[2 * d], has ? 1u << (lane & 31) : 0u);
+        const uint64_t peers = wm[d];
+        const uint32_t c = wc[d];
+        const uint32_t below = lanes_below(peers);
+        rank[j] = c + below;
+        if (has && below == 0) {
+            wc[d] = c + (uint32_t)__popcll(peers);
+            wm[d] = 0;
         }
-        __syncthreads();
-        uint32_t rank[ITEMS];
-        wave_rank<kRadixBits, K, ITEMS>(key, shift, wc, s_mask + w * kRadix, lane, rank);
-        __syncthreads();
-        // exclusive offsets over (digit, wave): digit-major, so that
-        // earlier waves (earlier elements) come first within a digit
-        uint32_t cnt = 0;
-        if (t < kRadix) {
+    });
+    __syncthreads();
+    // exclusive offsets over (digit, wave): digit-major, so that earlier
+    // waves (earlier elements) come first within a digit
+    uint32_t cnt = 0;
+    if (t < kRadix) {
 #pragma unroll
-            for (int ww = 0; ww < W; ++ww) {
-                const uint32_t c = L.wcnt[ww * kRadix + t];
-                L.wcnt[ww * kRadix + t] = cnt;
-                cnt += c;
-            }
+        for (int ww = 0; ww < W; ++ww) {
+            const uint32_t c = L.wcnt[ww * kRadix + t];
+            L.wcnt[ww * kRadix + t] = cnt;
+            cnt += c;
         }
-        const uint32_t excl = bins_exclusive_scan<kRadix>(cnt, L.tmp);
-        if (t < kRadix) {
+    }
+    const uint32_t excl = bins_exclusive_scan<kRadix>(cnt, L.tmp);
+    if (t < kRadix) {
 #pragma unroll
-            for (int ww = 0; ww < W; ++ww)
-                L.wcnt[ww * kRadix + t] += excl;
-        }
-        __syncthreads();
-#pragma unroll
-        for (int j = 0; j < ITEMS; ++j) {
-            const uint32_t pos = rank[j] + wc[digit_of<kRadixBits>(key[j], shift)];
+        for (int ww = 0; ww < W; ++ww)
+            L.wcnt[ww * kRadix + t] += excl;
+    }
+    __syncthreads();
+    it.each([&](int j) {
+        if (it.has(j)) {
+            const uint32_t pos = rank[j] + wc[digit_at<kRadixBits>(key[j], shift)];
             s_k[pos] = key[j];
             if constexpr (HAS_V)
                 s_v[pos] = val[j];
         }
-        __syncthreads();
+    });
+    __syncthreads();
+    // lanes past m read their stale slots: in range, and never used
+    it.each([&](int j) {
+        const uint32_t at = min(it.at(j), (uint32_t)CAP - 1);
+        key[j] = s_k[at];
+        if constexpr (HAS_V)
+            val[j] = s_v[at];
+    });
+    __syncthreads();
+}
+
+// The counting sorts of the 8-bit digit positions in `digits` (bit p:
+// position p), lowest first.
+template <typename K, typename V, bool HAS_V, int THREADS, int ITEMS>
+__device__ __forceinline__ void block_sort_digits(BlockLds<K, HAS_V, THREADS, ITEMS> &L,
+                                                  const BlockItems<THREADS, ITEMS> &it,
+                                                  K (&key)[ITEMS], V (&val)[HAS_V ? ITEMS : 1],
+                                                  uint32_t digits)
+{
+    for (; digits; digits &= digits - 1)
+        block_sort_digit<K, V, HAS_V, THREADS, ITEMS>(L, it, key, val,
+                                                      __builtin_ctz(digits) * kRadixBits);
+}
+
+// Sorts the workgroup's elements; to[j] is where item j then belongs.
+//
+// The keys' highest differing bit is found first, and only the 16 bits from
+// there down are sorted by counting sorts, two passes for any key width: up
+// to 16384 elements then share those bits with few others, and each such
+// run is put in order by counting (run_move), which needs no staging of the
+// values.  Runs that are too long and out of order send the whole tile
+// through every digit that differs.
+template <typename K, typename V, bool HAS_V, int THREADS, int ITEMS>
+__device__ __forceinline__ void block_sort(BlockLds<K, HAS_V, THREADS, ITEMS> &L,
+                                           const BlockItems<THREADS, ITEMS> &it, K (&key)[ITEMS],
+                                           V (&val)[HAS_V ? ITEMS : 1], uint32_t (&to)[ITEMS])
+{
+    constexpr int W = THREADS / kWave;
+    K *s_k = (K *)L.stage;
+    const uint32_t t = threadIdx.x;
+    const uint32_t w = __builtin_amdgcn_readfirstlane(t / kWave);
+    const uint32_t lane = t % kWave;
 #pragma unroll
-        for (int j = 0; j < ITEMS; ++j) {
-            key[j] = s_k[off0 + j * kWave];
-            if constexpr (HAS_V)
-                val[j] = s_v[off0 + j * kWave];
-        }
-        __syncthreads();
+    for (int j = 0; j < ITEMS; ++j)
+        to[j] = it.at(j);
+    // the bits in which any key differs from the first one
+    if (t == 0) {
+        L.diff = 0;
+        s_k[0] = key[0];
     }
+    __syncthreads();
+    const K first = s_k[0];
+    {
+        K d = 0;
+        it.each([&](int j) { d |= it.has(j) ? key[j] ^ first : (K)0; });
+        const uint32_t lo = wave_or((uint32_t)d);
+        const uint32_t hi = sizeof(K) == 8 ? wave_or((uint32_t)((uint64_t)d >> 32)) : 0u;
+        if (lane == kWave - 1 && (lo | hi))
+            atomicOr((unsigned long long *)&L.diff, ((uint64_t)hi << 32) | lo);
+    }
+    __syncthreads();
+    const uint64_t diff = uniform_word(L.diff);
+    if (diff == 0)
+        return;  // one key only: in place
+    const int top = (kWave - 1) - __builtin_clzll(diff);
+    const int shift = max(0, top - (2 * kRadixBits - 1));
+    block_sort_digit<K, V, HAS_V, THREADS, ITEMS>(L, it, key, val, shift);
+    if (top >= kRadixBits)
+        block_sort_digit<K, V, HAS_V, THREADS, ITEMS>(L, it, key, val, shift + kRadixBits);
+    if (shift == 0 || (diff & (((uint64_t)1 << shift) - 1)) == 0)
+        return;  // nothing below the sorted bits
+    // the runs: head words and neighbours out of order, as in k_finish
+    const K low_ones = ((K)1 << shift) - 1;
+    uint64_t head[ITEMS];
+    bool inv = false;
+    K *s_run = L.before + kRunMax;  // the keys, with kRunMax before them
+    using Lds = BlockLds<K, HAS_V, THREADS, ITEMS>;
+    static_assert(offsetof(Lds, stage) == offsetof(Lds, before) + kRunMax * sizeof(K),
+                  "those neighbours lie right before the keys");
+    uint64_t last = ~0ull;
+#pragma unroll
+    for (int j = 0; j < ITEMS; ++j)
+        head[j] = ~0ull;
+    it.each([&](int j) {
+        const uint32_t at = it.at(j);
+        const bool has = it.has(j);
+        const K prev = s_run[(int32_t)(has ? at : 0u) - 1];
+        head[j] = __ballot(at == 0 || !has || (key[j] ^ prev) > low_ones);
+        inv = inv || (has && at > 0 && key[j] < prev);
+        last = head[j];
+    });
+    if (lane == 0) {
+        L.head[2 * w] = head[0];
+        L.head[2 * w + 1] = last;
+    }
+    if (!__syncthreads_or(inv))
+        return;  // every run is in order already
+    const uint64_t before = w == 0 ? ~0ull : uniform_word(L.head[2 * w - 1]);
+    const uint64_t behind = w == W - 1 ? ~0ull : uniform_word(L.head[2 * w + 2]);
+    // nothing before the first key is larger, nothing after the last smaller
+    if (t < kRunMax) {
+        L.before[t] = 0;
+        s_k[it.m + t] = KeyTraits<K>::kPad;
+    }
+    __syncthreads();
+    bool lost = false;
+    it.each([&](int j) {
+        // the wave as a whole: run_move takes part with every lane
+        if (it.at(j) - lane < it.m) {
+            const uint32_t at = min(it.at(j), it.m - 1);
+            const uint64_t next = j + 1 < ITEMS && (uint32_t)j + 1 < it.used
+                                      ? head[j + 1 < ITEMS ? j + 1 : j]
+                                      : behind;
+            bool whole;
+            const int32_t move = run_move(s_run, at, key[j], lane, head[j],
+                                          j ? head[j ? j - 1 : 0] : before, next, &whole);
+            if (it.has(j)) {
+                to[j] += (uint32_t)move;
+                lost = lost || (!whole && key[j] > s_k[at + 1] &&
+                                ((key[j] ^ s_k[at + 1]) <= low_ones));
+            }
+        }
+    });
+    if (!__syncthreads_or(lost))
+        return;
+    uint32_t digits = 0;
+    for (int p = 0; p < num_passes<K, kRadixBits>(); ++p)
+        digits |= ((diff >> (p * kRadixBits)) & (kRadix - 1)) ? 1u << p : 0u;
+    block_sort_digits<K, V, HAS_V, THREADS, ITEMS>(L, it, key, val, digits);
+#pragma unroll
+    for (int j = 0; j < ITEMS; ++j)
+        to[j] = it.at(j);
 }
 
 template <typename K, typename V, bool HAS_V, int THREADS, int ITEMS>
 __global__ __launch_bounds__(THREADS) void k_block_sort(BlockArgs a)
 {
-    constexpr int D = num_passes<K, kRadixBits>();
     __shared__ BlockLds<K, HAS_V, THREADS, ITEMS> L;
     __shared__ uint32_t s_item;
     const uint32_t t = threadIdx.x;
-    const uint32_t w = t / kWave;
-    const uint32_t lane = t % kWave;
-    const uint32_t off0 = w * (kWave * ITEMS) + lane;
     const K *kin = (const K *)a.kin;
     const V *vin = (const V *)a.vin;
     K *kout = (K *)a.kout;
@@ -157,38 +341,28 @@ __global__ __launch_bounds__(THREADS) void k_block_sort(BlockArgs a)
             m = (uint32_t)a.n;
         }
 
-        // load: position j*64 + l of the wave's run; padding keys (all ones)
-        // stay behind every real key in every pass
+        const BlockItems<THREADS, ITEMS> it(m);
         K key[ITEMS];
         V val[HAS_V ? ITEMS : 1];
-#pragma unroll
-        for (int j = 0; j < ITEMS; ++j) {
-            const uint32_t pos = off0 + j * kWave;
-            key[j] = pos < m ? kin[start + pos] : KeyTraits<K>::kPad;
+        it.each([&](int j) {
+            key[j] = it.has(j) ? kin[start + it.at(j)] : (K)0;
             if constexpr (HAS_V)
-                val[j] = pos < m ? vin[start + pos] : (V)0;
-        }
+                val[j] = it.has(j) ? vin[start + it.at(j)] : (V)0;
+        });
         // mapped once every load is issued (a map between loads would wait
-        // for each in turn); padding keys stay unmapped
-        if (a.kmap) {
-#pragma unroll
-            for (int j = 0; j < ITEMS; ++j) {
-                const K mk = map_in(key[j], a.kmap);
-                key[j] = off0 + j * kWave < m ? mk : key[j];
-            }
-        }
-
-        block_sort_digits<K, V, HAS_V, THREADS, ITEMS>(L, key, val, (1u << D) - 1u);
-
-#pragma unroll
-        for (int j = 0; j < ITEMS; ++j) {
-            const uint32_t pos = off0 + j * kWave;
-            if (pos < m) {
-                kout[start + pos] = map_out(key[j], a.kmap);
+        // for each in turn)
+        if (a.kmap)
+            it.each([&](int j) { key[j] = map_in(key[j], a.kmap); });
+        uint32_t to[ITEMS];
+        block_sort<K, V, HAS_V, THREADS, ITEMS>(L, it, key, val, to);
+        it.each([&](int j) {
+            if (it.has(j)) {
+                kout[start + to[j]] = map_out(key[j], a.kmap);
                 if constexpr (HAS_V)
-                    vout[start + pos] = val[j];
+                    vout[start + to[j]] = val[j];
             }
-        }
+        });
+        __syncthreads();  // the next range overwrites the LDS
     }
 }
 

@@ -187,6 +187,20 @@ __device__ __forceinline__ uint32_t digit_of(uint64_t k, int shift)
     }
 }
 
+// The same for a digit that starts at any bit (the one above takes 64-bit
+// digits that lie within one 32-bit half).
+template <int R>
+__device__ __forceinline__ uint32_t digit_at(uint32_t k, int shift)
+{
+    return __builtin_amdgcn_ubfe(k, (uint32_t)shift, (uint32_t)R);
+}
+
+template <int R>
+__device__ __forceinline__ uint32_t digit_at(uint64_t k, int shift)
+{
+    return (uint32_t)(k >> shift) & ((1u << R) - 1u);
+}
+
 __device__ __forceinline__ uint32_t lane_id()
 {
     return __builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, 0u));
@@ -250,6 +264,18 @@ __device__ __forceinline__ uint32_t wave_max(uint32_t v)
     v = max(v, row_shr<8>(v));
     v = max(v, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x142, 0xa, 0xf, false));
     v = max(v, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x143, 0xc, 0xf, false));
+    return v;
+}
+
+// All bits set in the wave's values, in its last lane (the same steps).
+__device__ __forceinline__ uint32_t wave_or(uint32_t v)
+{
+    v |= row_shr<1>(v);
+    v |= row_shr<2>(v);
+    v |= row_shr<4>(v);
+    v |= row_shr<8>(v);
+    v |= (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x142, 0xa, 0xf, false);
+    v |= (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x143, 0xc, 0xf, false);
     return v;
 }
 

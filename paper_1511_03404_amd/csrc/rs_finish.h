@@ -18,6 +18,7 @@
 #pragma once
 
 #include "rs_kernels.h"
+#include "rs_runs.h"
 
 namespace rs {
 
@@ -25,14 +26,10 @@ struct FinishArgs {
     Bufs b;
     uint32_t n;
     uint32_t *ctrl;
-    uint32_t *list;     // starts of the runs longer than kFinishRunMax
+    uint32_t *list;     // starts of the runs longer than kRunMax
     uint32_t list_cap;
     uint32_t kmap;      // key order undone when the sweep writes the output
 };
-
-// Longest run ordered by counting: with one 64-element chunk on either side
-// of its own, every element of such a run sees the whole run.
-constexpr uint32_t kFinishRunMax = kWave;
 
 constexpr int kFinishThreads = 256;
 constexpr int kFinishItems = 4;
@@ -43,32 +40,20 @@ constexpr uint32_t kFinishSmall = 1u << 19;
 
 // Workgroups loop over tiles of THREADS x ITEMS elements; a tile's keys and
 // the chunk before and after it are held in LDS.  A chunk is the 64 elements
-// of one wave's item; its head word (a ballot) has a bit for every element
-// that starts a run, so the longest run that touches the chunk, and with it
-// the distance D over which elements can be out of order, comes from a few
-// scalar operations on three words.
+// of one wave's item; its head word is a ballot, and run_move orders the
+// chunk's elements with it and its neighbours' (rs_runs.h).
 //
-// An element moves left by the number of larger keys among the D before it
-// and right by the number of smaller keys among the D after it.  Neighbours
-// in other runs need no test: the array is sorted by the high bits, so those
-// before are smaller and those after larger.  Equal keys never pass each
-// other, so the sweep is stable.  Per distance that is two LDS reads at
-// consecutive addresses, two compares and two adds with carry, and no
-// address depends on data, so the reads of several distances are in flight
-// together.  Counting over each element's own run, found from the head words
-// by every lane, was slower: its reads depended on the run bounds, and 64-bit
-// shifts per lane cost more than the count (2^25 64-bit keys, runs of 2:
-// 137 us, now 119 us, 4.5 TB/s; 2^20 32-bit keys, runs of 16: 17.8 us, now
-// 12.0 us).  It is bound by the compares (VALU) for runs of 4 and more, by
-// HBM below.
+// Counting over each element's own run, found from the head words by every
+// lane, was slower: its reads depended on the run bounds, and 64-bit shifts
+// per lane cost more than the count (2^25 64-bit keys, runs of 2: 137 us, now
+// 119 us, 4.5 TB/s; 2^20 32-bit keys, runs of 16: 17.8 us, now 12.0 us).  It
+// is bound by the compares (VALU) for runs of 4 and more, by HBM below.
 template <typename K, typename V, bool HAS_V, int THREADS, int ITEMS>
 __global__ __launch_bounds__(THREADS) void k_finish(FinishArgs a)
 {
     constexpr uint32_t T = THREADS * ITEMS;
     constexpr uint32_t H = kWave;  // elements held on either side
     constexpr int W = THREADS / kWave;
-    constexpr int STEP = 4;        // distances per round (the scalar masks below)
-    static_assert(kFinishRunMax % STEP == 0, "the last round stays inside the held elements");
     __shared__ K s_k[T + 2 * H];
     // per wave: the head words of its first and last chunk; then those of the
     // chunks before and after the tile.  Below them the same for the words of
@@ -171,15 +156,10 @@ __global__ __launch_bounds__(THREADS) void k_finish(FinishArgs a)
         {
             const uint32_t p = w == 0 ? 2 * W : 2 * w - 1;
             const uint32_t q = w == W - 1 ? 2 * W + 1 : 2 * w + 2;
-            auto uniform = [](uint64_t x) {
-                const uint32_t hi = __builtin_amdgcn_readfirstlane((uint32_t)(x >> 32));
-                const uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)x);
-                return ((uint64_t)hi << 32) | lo;
-            };
-            head[0] = uniform(s_head[p]);
-            head[ITEMS + 1] = uniform(s_head[q]);
-            inv[0] = uniform(s_inv[p]);
-            inv[ITEMS + 1] = uniform(s_inv[q]);
+            head[0] = uniform_word(s_head[p]);
+            head[ITEMS + 1] = uniform_word(s_head[q]);
+            inv[0] = uniform_word(s_inv[p]);
+            inv[ITEMS + 1] = uniform_word(s_inv[q]);
         }
 #pragma unroll
         for (int j = 0; j < ITEMS; ++j) {
@@ -189,58 +169,15 @@ __global__ __launch_bounds__(THREADS) void k_finish(FinishArgs a)
             const uint64_t here = head[j + 1], prev = head[j], next = head[j + 2];
             // nothing adjacent out of order in the three chunks: in place
             if ((inv[j] | inv[j + 1] | inv[j + 2]) != 0) {
-                // the longest run that touches this chunk: clear bits in a
-                // row, across either of its ends (counted here) or inside it
-                // (`clear` keeps a bit while d of them are in a row below it)
-                const uint32_t into = here ? __builtin_ctzll(here) : kWave;
-                const uint32_t outof = here ? __builtin_clzll(here) : kWave;
-                const uint32_t left = into + (prev ? __builtin_clzll(prev) : kWave);
-                const uint32_t right = outof + (next ? __builtin_ctzll(next) : kWave);
-                uint32_t dist = max(left, right);
-                uint64_t clear = ~here;
-                const uint64_t two = clear & (clear << 1), four = two & (two << 2);
-                bool whole = true;  // this element's run is short enough
-                if (dist >= kFinishRunMax) {
-                    // this element's distance from its run's first and last
-                    // element (kWave or more where no head is in sight)
-                    const uint64_t upto = here << (kWave - 1 - lane);
-                    const uint64_t after = lane < kWave - 1 ? here >> (lane + 1) : 0ull;
-                    const uint32_t back = upto   ? __builtin_clzll(upto)
-                                          : prev ? lane + 1 + __builtin_clzll(prev)
-                                                 : 2 * kWave;
-                    const uint32_t ahead = after  ? __builtin_ctzll(after)
-                                           : next ? kWave - 1 - lane + __builtin_ctzll(next)
-                                                  : 2 * kWave;
-                    whole = back + ahead < kFinishRunMax;
-                    dist = kFinishRunMax - 1;
-                    clear = 0;
-                    if (!whole) {
-                        const bool in_run =
-                            lane < kWave - 1 ? (after & 1ull) == 0 : (next & 1ull) == 0;
-                        if (in_run && key[j] > s_k[at + 1])
-                            __hip_atomic_store(&a.ctrl[kCtrlUnsorted], 1u, __ATOMIC_RELAXED,
-                                               __HIP_MEMORY_SCOPE_AGENT);
-                    }
-                    if (__ballot(whole) == 0)
-                        dist = 0;
+                bool whole;
+                pos += (uint32_t)run_move(s_k, at, key[j], lane, here, prev, next, &whole);
+                if (!whole) {
+                    const bool in_run =
+                        (lane < kWave - 1 ? (here >> (lane + 1)) & 1ull : next & 1ull) == 0;
+                    if (in_run && key[j] > s_k[at + 1])
+                        __hip_atomic_store(&a.ctrl[kCtrlUnsorted], 1u, __ATOMIC_RELAXED,
+                                           __HIP_MEMORY_SCOPE_AGENT);
                 }
-                int32_t move = 0;
-                for (uint32_t d = 1; d <= dist || clear != 0; d += STEP) {
-                    K l[STEP], r[STEP];
-#pragma unroll
-                    for (int i = 0; i < STEP; ++i) {
-                        l[i] = s_k[at - d - i];
-                        r[i] = s_k[at + d + i];
-                    }
-#pragma unroll
-                    for (int i = 0; i < STEP; ++i) {
-                        move -= l[i] > key[j];
-                        move += r[i] < key[j];
-                    }
-                    clear &= four << d;
-                }
-                if (whole)
-                    pos += (uint32_t)move;
             }
             if (pos < n && (full || tb + e < n)) {
                 store_at(dk, pos, map_out(key[j], map));
@@ -249,7 +186,7 @@ __global__ __launch_bounds__(THREADS) void k_finish(FinishArgs a)
             }
             // the starts of the runs that are too long, in order or not
             const uint32_t ends = here ? __builtin_clzll(here) : 0;
-            if (here && ends + (next ? __builtin_ctzll(next) : kWave) >= kFinishRunMax) {
+            if (here && ends + (next ? __builtin_ctzll(next) : kWave) >= kRunMax) {
                 const uint32_t i = tb + e;
                 if (lane == kWave - 1 - ends && i < n) {
                     const uint32_t l = atomicAdd(&a.ctrl[kCtrlLongLen], 1u);
@@ -445,7 +382,6 @@ __global__ __launch_bounds__(C::kThreads) void k_last(LastArgs a)
     if (ctrl[kCtrlUnsorted] == 0)
         return;
     const uint32_t t = threadIdx.x;
-    const uint32_t off0 = (t / kWave) * (kWave * ITEMS) + t % kWave;
     const uint32_t n = a.p.n;
     const uint32_t buf = (finish >> kFinishDstShift) & 3u;  // where k_finish wrote
     const uint32_t digits = __builtin_amdgcn_readfirstlane(ctrl[kCtrlDigits]);
@@ -495,19 +431,10 @@ __global__ __launch_bounds__(C::kThreads) void k_last(LastArgs a)
                     ++mine;
                     const uint32_t start = a.list[a.list_cap - 1 - s_item];
                     const K lead = map_in(bk[start], map) >> shift;
-                    K key[ITEMS];
-                    V val[HAS_V ? ITEMS : 1];
                     uint32_t end = T;
-#pragma unroll
-                    for (int j = 0; j < ITEMS; ++j) {
-                        const uint32_t e = off0 + j * kWave;
-                        const bool in = e < n - start;
-                        key[j] = in ? map_in(bk[start + e], map) : KeyTraits<K>::kPad;
-                        if constexpr (HAS_V)
-                            val[j] = in ? bv[start + e] : (V)0;
-                        if (!in || (key[j] >> shift) != lead)
+                    for (uint32_t e = t; e < T; e += THREADS)
+                        if (e >= n - start || (map_in(bk[start + e], map) >> shift) != lead)
                             end = min(end, e);
-                    }
                     if (end < T)
                         atomicMin(&s_len, end);
                     __syncthreads();
@@ -540,19 +467,23 @@ __global__ __launch_bounds__(C::kThreads) void k_last(LastArgs a)
                             __hip_atomic_store(&ctrl[kCtrlGiant], 1u, __ATOMIC_RELAXED,
                                                __HIP_MEMORY_SCOPE_AGENT);
                     } else {
-#pragma unroll
-                        for (int j = 0; j < ITEMS; ++j)
-                            key[j] = off0 + j * kWave < m ? key[j] : KeyTraits<K>::kPad;
-                        block_sort_digits<K, V, HAS_V, THREADS, ITEMS>(L.block, key, val, low);
-#pragma unroll
-                        for (int j = 0; j < ITEMS; ++j) {
-                            const uint32_t e = off0 + j * kWave;
-                            if (e < m) {
-                                bk[start + e] = map_out(key[j], map);
+                        const BlockItems<THREADS, ITEMS> it(m);
+                        K key[ITEMS];
+                        V val[HAS_V ? ITEMS : 1];
+                        it.each([&](int j) {
+                            key[j] = it.has(j) ? map_in(bk[start + it.at(j)], map) : (K)0;
+                            if constexpr (HAS_V)
+                                val[j] = it.has(j) ? bv[start + it.at(j)] : (V)0;
+                        });
+                        __syncthreads();  // everything is read before it is overwritten
+                        block_sort_digits<K, V, HAS_V, THREADS, ITEMS>(L.block, it, key, val, low);
+                        it.each([&](int j) {
+                            if (it.has(j)) {
+                                bk[start + it.at(j)] = map_out(key[j], map);
                                 if constexpr (HAS_V)
-                                    bv[start + e] = val[j];
+                                    bv[start + it.at(j)] = val[j];
                             }
-                        }
+                        });
                     }
                 }
                 __syncthreads();

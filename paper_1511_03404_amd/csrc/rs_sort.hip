@@ -523,17 +523,20 @@ static rs_status run_sort(rs_context *ctx, const K *kin, const K *vin, K *kout, 
                 err_clear = (uint32_t *)o->ptr + kCtrlError;
         }
         BlockArgs ba{kin, vin, kout, vout, nullptr, nullptr, nullptr, n, kmap, err_clear};
-        if (n <= (uint64_t)B::kSmallCap) {
-            launch(ctx, s, "k_block_sort_small", [&] {
-                hipLaunchKernelGGL((k_block_sort<K, K, HAS_V, B::kSmallThreads, B::kItems>),
-                                   dim3(1), dim3(B::kSmallThreads), 0, s, ba);
-            });
-        } else {
-            launch(ctx, s, "k_block_sort_medium", [&] {
-                hipLaunchKernelGGL((k_block_sort<K, K, HAS_V, B::kMediumThreads, B::kItems>),
-                                   dim3(1), dim3(B::kMediumThreads), 0, s, ba);
-            });
-        }
+        auto go = [&](auto kernel, int threads, const char *name) {
+            launch(ctx, s, name,
+                   [&] { hipLaunchKernelGGL(kernel, dim3(1), dim3(threads), 0, s, ba); });
+        };
+        if (n <= 1024)
+            go(k_block_sort<K, K, HAS_V, 256, 4>, 256, "k_block_sort_small");
+        else if (n <= 2048)
+            go(k_block_sort<K, K, HAS_V, 512, 4>, 512, "k_block_sort_small");
+        else if (n <= 4096)
+            go(k_block_sort<K, K, HAS_V, 1024, 4>, 1024, "k_block_sort_small");
+        else if (n <= 8192)
+            go(k_block_sort<K, K, HAS_V, 1024, 8>, 1024, "k_block_sort_medium");
+        else if constexpr (B::kMediumCap > 8192)
+            go(k_block_sort<K, K, HAS_V, 1024, 16>, 1024, "k_block_sort_medium");
         const hipError_t e = hipGetLastError();
         if (e != hipSuccess)
             return fail(RS_ERR_DEVICE, "kernel launch failed: %s", hipGetErrorString(e));
