@@ -167,11 +167,16 @@ __global__ __launch_bounds__(256) void k_seg_bitonic(TinyArgs a)
 {
     const uint32_t lane = threadIdx.x & (kWave - 1);
     const uint32_t len = *a.list_len;
-    while (true) {
-        uint32_t item = 0;
-        if (lane == 0)
-            item = atomicAdd(a.claim, 1u);
-        item = (uint32_t)__shfl((int)item, 0);
+    const uint32_t waves = gridDim.x * (blockDim.x / kWave);
+    // the first segment is the wave's own number, the others are claimed
+    uint32_t item = blockIdx.x * (blockDim.x / kWave) + threadIdx.x / kWave;
+    for (bool claim = false;; claim = true) {
+        if (claim) {
+            uint32_t c = 0;
+            if (lane == 0)
+                c = atomicAdd(a.claim, 1u);
+            item = waves + __builtin_amdgcn_readfirstlane(c);
+        }
         if (item >= len)
             break;
         const uint64_t start = a.list[item].start;

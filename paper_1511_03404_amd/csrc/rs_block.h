@@ -323,8 +323,10 @@ __global__ __launch_bounds__(THREADS) void k_block_sort(BlockArgs a)
         *a.err_clear = 0;
 
     for (uint32_t iter = 0;; ++iter) {
+        // the first entry is the workgroup's own number: workgroups beyond the
+        // list's end claim nothing
         if (t == 0)
-            s_item = a.list ? atomicAdd(a.claim, 1u) : iter;
+            s_item = iter == 0 ? blockIdx.x : a.list ? gridDim.x + atomicAdd(a.claim, 1u) : 1u;
         __syncthreads();
         const uint32_t item = s_item;
         uint64_t start;

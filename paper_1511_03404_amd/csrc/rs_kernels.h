@@ -35,9 +35,6 @@ constexpr int kClaimGroup = 8;
 // kind, 2^24 keys of 16384-key tiles).
 constexpr uint32_t kFlatClaimTiles = 1024;
 
-// Per-XCD claim counters (XCC_ID has 3 bits; gfx950 has 8 XCDs).
-constexpr uint32_t kXcdSlots = 8;
-
 // One wave in kBallotShare ranks with ballots (see PassCfg::kBallotWaves).
 constexpr int kBallotShare = 4;
 
@@ -1238,7 +1235,7 @@ __global__ __launch_bounds__(C::kThreads) void k_pass(PassArgs a)
 
 // ---------------------------------------------------------------------------
 // Segmented sort: digit histograms of the large segments, chunk by chunk.
-// Persistent workgroups claim chunks of kSegChunk elements, count all digit
+// Persistent workgroups claim chunks (seg_chunk), count all digit
 // positions in the column table of k_hist and add the counts to the
 // segment's histogram (global atomics).
 
@@ -1247,10 +1244,12 @@ struct SegHistArgs {
     const SegLarge *large;
     const uint32_t *chunk_seg;
     uint32_t max_chunks;
+    uint32_t chunk;  // elements per chunk
     uint32_t *ctrl;
     uint32_t *seg_hist;   // [large segment][d][2^R], zeroed
     uint32_t *seg_base;   // [large segment][d][2^R]
-    uint32_t *seg_flags;  // [large segment]: bit p pass p's digit is the same for the
+    uint32_t *seg_flags;  // [large segment]: first its first chunk (k_seg_hist), then
+                          // (k_seg_scan) bit p pass p's digit is the same for the
                           // whole segment; bit 16 + p pass p's digits are skewed
     uint32_t kmap;        // key order applied to every key read
 };
@@ -1275,23 +1274,21 @@ __global__ __launch_bounds__(kSegHistThreads) void k_seg_hist(SegHistArgs a)
     const uint32_t chunks = min(a.ctrl[kSegChunks], a.max_chunks);
     for (uint32_t i = t; i < TAB; i += kSegHistThreads)
         tab[i] = 0;
-    while (true) {
+    // the first chunk is the workgroup's own number, the others are claimed
+    for (bool claim = false;; claim = true) {
         // the barrier also ends the previous chunk's flush in every thread
         if (t == 0)
-            s_item = atomicAdd(&a.ctrl[kSegChunkClaim], 1u);
+            s_item = claim ? gridDim.x + atomicAdd(&a.ctrl[kSegChunkClaim], 1u) : blockIdx.x;
         __syncthreads();
         const uint32_t item = s_item;
         if (item >= chunks)
             break;
         const uint32_t seg = a.chunk_seg[item];
         const SegLarge rec = a.large[seg];
-        // this chunk's index within its segment: chunks of a segment are
-        // consecutive, so count back to the segment's first chunk
-        uint32_t first = item;
-        while (first > 0 && a.chunk_seg[first - 1] == seg)
-            --first;
-        const uint64_t lo = (uint64_t)(item - first) * kSegChunk;
-        const uint32_t len = rec.size > lo ? (uint32_t)min<uint64_t>(kSegChunk, rec.size - lo) : 0u;
+        // k_seg_classify left the segment's first chunk where k_seg_scan will
+        // put the segment's flags
+        const uint64_t lo = (uint64_t)(item - a.seg_flags[seg]) * a.chunk;
+        const uint32_t len = rec.size > lo ? (uint32_t)min<uint64_t>(a.chunk, rec.size - lo) : 0u;
         const K *sk = keys + rec.start + lo;
         for (uint32_t r0 = 0; r0 < len; r0 += ROUND) {
             if (r0 + ROUND <= len) {
@@ -1337,7 +1334,7 @@ __global__ __launch_bounds__(kSegHistThreads) void k_seg_hist(SegHistArgs a)
 }
 
 // seg_base[seg][p] = exclusive scan of seg_hist[seg][p], one workgroup per
-// large segment (persistent).
+// large segment.
 template <typename K, int R>
 __global__ __launch_bounds__(256) void k_seg_scan(SegHistArgs a)
 {
@@ -1345,16 +1342,11 @@ __global__ __launch_bounds__(256) void k_seg_scan(SegHistArgs a)
     constexpr int NB = 1 << R;
     static_assert(D <= kSegSkewShift, "pass flags fit 16 bits each");
     __shared__ uint32_t s_tmp[8];
-    __shared__ uint32_t s_item;
     __shared__ unsigned long long s_sq[256 / kWave];
     const uint32_t t = threadIdx.x;
-    while (true) {
-        if (t == 0)
-            s_item = atomicAdd(&a.ctrl[kSegScanClaim], 1u);
-        __syncthreads();
-        const uint32_t item = s_item;
-        if (item >= a.ctrl[kSegLargeLen])
-            break;
+    // equal work per segment: workgroups take them in turn, without claims
+    // (a grid of workgroups claiming from one counter took 30 us for nothing)
+    for (uint32_t item = blockIdx.x; item < a.ctrl[kSegLargeLen]; item += gridDim.x) {
         const uint32_t size = a.large[item].size;
         uint32_t flags = 0;
         for (int p = 0; p < D; ++p) {

@@ -25,6 +25,9 @@ namespace rs {
 
 using SegLarge = SegRange;
 
+// Per-XCD claim counters (XCC_ID has 3 bits; gfx950 has 8 XCDs).
+constexpr uint32_t kXcdSlots = 8;
+
 // Segmented control block (u32 words).
 constexpr int kSegSmallLen = 0;
 constexpr int kSegMediumLen = 1;
@@ -39,11 +42,21 @@ constexpr int kSegTinyClaim = 9;
 constexpr int kSegPassCounter = 32; // [32, 48): group counter per pass
 constexpr int kSegChunks = 16;      // histogram chunks of the large segments
 constexpr int kSegChunkClaim = 17;
-constexpr int kSegScanClaim = 18;
 constexpr int kSegWords = 64;
 // Large segments are histogrammed in chunks of this many elements, so that
-// one huge segment does not leave a single workgroup reading it alone.
-constexpr uint32_t kSegChunk = 1u << 18;
+// one huge segment does not leave a single workgroup reading it alone: at
+// most 2^18 (a chunk's end adds its counts to memory), fewer when the batch
+// would make less than two chunks per compute unit (7.2M 64-bit elements in
+// 24 segments: 74 us with 2^18, 27 us with 2^14).
+constexpr uint32_t kSegChunkMax = 1u << 18;
+constexpr uint32_t kSegChunkMin = 1u << 14;
+inline uint32_t seg_chunk(uint64_t total)
+{
+    uint32_t c = kSegChunkMax;
+    while (c > kSegChunkMin && total / c < 512)
+        c /= 2;
+    return c;
+}
 
 struct SegClassifyArgs {
     const uint64_t *offsets;
@@ -58,6 +71,7 @@ struct SegClassifyArgs {
     uint32_t *tile_seg;
     uint32_t *chunk_seg;  // large segment of each histogram chunk
     uint32_t max_chunks;
+    uint32_t *first_chunk;  // of each large segment (read by k_seg_hist)
     const void *kin;
     const void *vin;
     void *kout;
@@ -66,20 +80,26 @@ struct SegClassifyArgs {
     uint32_t small_cap;
     uint32_t medium_cap;
     uint32_t tile;
+    uint32_t chunk;  // elements per histogram chunk
 };
 
 template <typename K, bool HAS_V>
 __global__ __launch_bounds__(256) void k_seg_classify(SegClassifyArgs a)
 {
     const uint32_t stride = gridDim.x * blockDim.x;
-    for (uint32_t s = blockIdx.x * blockDim.x + threadIdx.x; s < a.num_segments; s += stride) {
+    const uint32_t lane = threadIdx.x % kWave;
+    // whole waves go round, so that all lanes can fill a large segment's maps
+    const uint32_t first = blockIdx.x * blockDim.x + threadIdx.x;
+    for (uint32_t s = first; s - lane < a.num_segments; s += stride) {
         // clamp to [0, total): a malformed offsets array sorts garbage
         // ranges but never leaves the arrays
-        const uint64_t start = std::min<uint64_t>(a.offsets[s], a.total);
-        const uint64_t end = std::min<uint64_t>(std::max<uint64_t>(a.offsets[s + 1], start), a.total);
-        const uint64_t size = end - start;
+        uint64_t start = 0, size = 0;
+        if (s < a.num_segments) {
+            start = std::min<uint64_t>(a.offsets[s], a.total);
+            size = std::min<uint64_t>(std::max<uint64_t>(a.offsets[s + 1], start), a.total) - start;
+        }
+        uint32_t idx = 0, nt = 0, ts = 0, nc = 0, cs = 0;
         if (size == 0) {
-            continue;
         } else if (size == 1) {
             ((K *)a.kout)[start] = ((const K *)a.kin)[start];
             if constexpr (HAS_V)
@@ -93,21 +113,28 @@ __global__ __launch_bounds__(256) void k_seg_classify(SegClassifyArgs a)
         } else if (size >= RS_MAX_ELEMENTS) {
             atomicOr(&a.ctrl[kSegError], kErrSegTooLarge);
         } else {
-            const uint32_t idx = atomicAdd(&a.ctrl[kSegLargeLen], 1u);
-            const uint32_t nt = (uint32_t)((size + a.tile - 1) / a.tile);
-            const uint32_t ts = atomicAdd(&a.ctrl[kSegTiles], nt);
+            idx = atomicAdd(&a.ctrl[kSegLargeLen], 1u);
+            nt = (uint32_t)((size + a.tile - 1) / a.tile);
+            ts = atomicAdd(&a.ctrl[kSegTiles], nt);
             // overlapping segments can need more tiles than the workspace
             // holds: such a segment keeps its tiles but sorts nothing
             const bool fits = (uint64_t)ts + nt <= a.max_tiles;
             if (!fits)
                 atomicOr(&a.ctrl[kSegError], kErrSegTiles);
             a.large[idx] = SegLarge{start, fits ? (uint32_t)size : 0u, ts};
-            for (uint32_t i = 0; i < nt && ts + i < a.max_tiles; ++i)
-                a.tile_seg[ts + i] = idx;
-            const uint32_t nc = (uint32_t)((size + kSegChunk - 1) / kSegChunk);
-            const uint32_t cs = atomicAdd(&a.ctrl[kSegChunks], nc);
-            for (uint32_t i = 0; i < nc && cs + i < a.max_chunks; ++i)
-                a.chunk_seg[cs + i] = idx;
+            nc = (uint32_t)((size + a.chunk - 1) / a.chunk);
+            cs = atomicAdd(&a.ctrl[kSegChunks], nc);
+            a.first_chunk[idx] = cs;
+        }
+        // the wave fills the maps of its large segments, one after another
+        for (uint64_t left = __ballot(nt != 0); left; left &= left - 1) {
+            const int l = __builtin_ctzll(left);
+            const uint32_t i = __shfl(idx, l), n = __shfl(nt, l), t0 = __shfl(ts, l);
+            const uint32_t m = __shfl(nc, l), c0 = __shfl(cs, l);
+            for (uint32_t j = lane; j < n && t0 + j < a.max_tiles; j += kWave)
+                a.tile_seg[t0 + j] = i;
+            for (uint32_t j = lane; j < m && c0 + j < a.max_chunks; j += kWave)
+                a.chunk_seg[c0 + j] = i;
         }
     }
 }
