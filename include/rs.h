@@ -126,8 +126,9 @@ rs_status rs_sort_pairs_u64(rs_context *ctx, const uint64_t *keys_in, const uint
  * rs_segmented_workspace_bytes().  Offsets are read on the device only (no
  * host round trip); a non-monotone offsets array is not detected and gives
  * unspecified (but in-bounds) results.  Segments are classified on the
- * device: up to the tiny cap (rs_segmented_tiny_cap_set, 1024 by default) a
- * bitonic network per wave (Section 2.1), up to 16384 elements (8192 for
+ * device: up to the tiny cap (rs_segmented_tiny_cap_set, 1024 by default) one
+ * wave each (up to 64 elements a bitonic network, Section 2.1, else an LDS
+ * radix sort), up to 16384 elements (8192 for
  * 64-bit pairs) a one-workgroup LDS radix sort, larger ones batched digit
  * passes (Section 2.6); every class gives the same stable sort.  One
  * segment must hold fewer than 2^30 elements; a larger one is left
@@ -253,10 +254,11 @@ rs_status rs_segmented_sort_order(rs_context *ctx, rs_key_type key_type, uint32_
 
 /*
  * Tiny segments of a segmented sort.  Segments of 2 .. cap elements (cap at
- * most 1024; the default is 1024) are sorted by one wave each with Batcher's
- * bitonic network (Section 2.1) in registers, on (key, position in the
- * segment) pairs so that the result is the same stable sort as the radix
- * path's; cap 0 (or 1) sends them to the one-workgroup radix sort instead.
+ * most 1024; the default is 1024) are sorted by one wave each: up to 64
+ * elements with Batcher's bitonic network (Section 2.1) in registers, on
+ * (key, position in the segment) pairs so that the result is the same stable
+ * sort as the radix path's, longer ones with a radix sort in the wave's LDS;
+ * cap 0 (or 1) sends them to the one-workgroup radix sort instead.
  * The setting belongs to the context and applies to later
  * rs_segmented_sort* calls and to graphs captured after it.
  * cap > 1024 -> RS_ERR_INVALID_ARGUMENT.

@@ -174,8 +174,9 @@ class Context:
         return out.value
 
     def tiny_cap(self, cap: int | None = None) -> int:
-        """Segments of 2 .. cap elements are sorted by a bitonic network per
-        wave (cap <= 1024, 0 sends them to the one-workgroup radix sort).
+        """Segments of 2 .. cap elements are sorted by one wave each, up to
+        64 elements with a bitonic network, longer ones with an LDS radix sort
+        (cap <= 1024, 0 sends them to the one-workgroup radix sort).
         Sets the cap if given; returns the cap in force."""
         if cap is not None:
             _check(lib().rs_segmented_tiny_cap_set(self.handle, int(cap)))

@@ -1,28 +1,32 @@
-// Bitonic sorting network (paper, Section 2.1; Batcher) for the tiny
-// segments of a segmented sort: one wave per segment of up to 1024
-// elements, held in registers as 64 lanes x R slots (element e = j * 64 +
-// lane in slot j), R = 1, 2, ..., 16 by the segment's size.
+// The tiny segments of a segmented sort, one wave per segment of up to 1024
+// elements: up to 64 by a bitonic sorting network in registers (paper,
+// Section 2.1; Batcher), more by the wave's LDS radix sort (rs_wave.h).
 //
-// Stage k = 2, 4, ..., 64 R builds sorted runs of length k; its steps of
-// distance s = k/2, ..., 1 compare element e with e XOR s and order each
-// pair ascending when bit k of e is clear, descending when it is set.  A
-// distance of 64 or more pairs two slots of the same lane; a smaller one
-// pairs the same slot of two lanes (a cross-lane shuffle).
+// Stage k = 2, 4, ..., 64 of the network builds sorted runs of length k; its
+// steps of distance s = k/2, ..., 1 compare element e (in lane e) with e XOR s
+// by a cross-lane shuffle and order each pair ascending when bit k of e is
+// clear, descending when it is set.
 //
 // The network alone is not stable; every element is the pair (key, position
 // in the segment), compared lexicographically, so all elements differ and
 // the sorted order is the stable sort.  Values do not travel through the
-// network: each output gathers its value by the position it carries.  Slots
+// network: each output gathers its value by the position it carries.  Lanes
 // past the segment hold a padding element greater than every real one.
+//
+// The network's steps grow with the square of log2 of the size; from 65
+// elements on, two digit passes and a count over short runs take fewer
+// (50,000 segments of 2 to 1024 32-bit pairs, whole batch: 211 us with the
+// network up to 64, 218 us up to 128).
 #pragma once
 
 #include "rs_block.h"
 #include "rs_device.h"
+#include "rs_wave.h"
 
 namespace rs {
 
-// Largest segment the network sorts (64 lanes x 16 slots).
-constexpr uint32_t kTinyMax = 1024;
+// Largest tiny segment.
+constexpr uint32_t kTinyMax = kWaveSortMax;
 
 // (key, position) as one comparable word: 32-bit keys pack into a 64-bit
 // integer; 64-bit keys keep the position beside the key.
@@ -84,113 +88,110 @@ struct TinyArgs {
     uint32_t kmap;            // key order: applied on load, undone on store
 };
 
-template <typename K, typename V, bool HAS_V, int R>
+template <typename K, typename V, bool HAS_V>
 __device__ __forceinline__ void bitonic_wave(const TinyArgs &a, uint64_t start, uint32_t m,
                                              uint32_t lane)
 {
     using E = BitonicElem<K>;
     using T = typename E::T;
-    constexpr uint32_t N = kWave * R;
-    const K *kin = (const K *)a.kin + start;
-
-    K raw[R];
-#pragma unroll
-    for (int j = 0; j < R; ++j) {
-        const uint32_t e = j * kWave + lane;
-        raw[j] = e < m ? kin[e] : (K)0;
-    }
-    T x[R];
-#pragma unroll
-    for (int j = 0; j < R; ++j) {
-        const uint32_t e = j * kWave + lane;
-        x[j] = E::sel(e < m, E::make(map_in(raw[j], a.kmap), e), E::pad());
-    }
-
-    for (uint32_t k = 2; k <= N; k <<= 1) {
-        // distances of 64 and more: two slots of this lane
-#pragma unroll
-        for (int sr = R / 2; sr >= 1; sr >>= 1) {
-            if ((uint32_t)sr * kWave < k) {
-#pragma unroll
-                for (int j = 0; j < R; ++j) {
-                    if (j & sr)
-                        continue;
-                    const bool up = ((j * kWave + lane) & k) == 0;
-                    const T lo = x[j], hi = x[j | sr];
-                    const bool sw = up ? E::less(hi, lo) : E::less(lo, hi);
-                    x[j] = E::sel(sw, hi, lo);
-                    x[j | sr] = E::sel(sw, lo, hi);
-                }
-            }
-        }
-        // distances below 64: the same slot of lane XOR s
-        for (uint32_t s = min(k >> 1, (uint32_t)kWave / 2); s >= 1; s >>= 1) {
+    const bool in = lane < m;
+    const K raw = in ? ((const K *)a.kin)[start + lane] : (K)0;
+    T x = E::sel(in, E::make(map_in(raw, a.kmap), lane), E::pad());
+    for (uint32_t k = 2; k <= (uint32_t)kWave; k <<= 1) {
+        const bool up = (lane & k) == 0;
+        for (uint32_t s = k >> 1; s >= 1; s >>= 1) {
             const bool lower = (lane & s) == 0;
-#pragma unroll
-            for (int j = 0; j < R; ++j) {
-                const bool up = ((j * kWave + lane) & k) == 0;
-                const T y = E::shfl_xor(x[j], s);
-                // the lower element of an ascending pair keeps the smaller
-                const bool take_y = (lower == up) == E::less(y, x[j]);
-                x[j] = E::sel(take_y, y, x[j]);
-            }
+            const T y = E::shfl_xor(x, s);
+            // the lower element of an ascending pair keeps the smaller
+            const bool take_y = (lower == up) == E::less(y, x);
+            x = E::sel(take_y, y, x);
         }
     }
+    // every value is read before any is written (in place: vin == vout)
+    V val = 0;
+    if constexpr (HAS_V)
+        val = in ? ((const V *)a.vin)[start + E::pos(x)] : (V)0;
+    if (in) {
+        ((K *)a.kout)[start + lane] = map_out((K)E::key(x), a.kmap);
+        if constexpr (HAS_V)
+            ((V *)a.vout)[start + lane] = val;
+    }
+}
 
+// The same segment by the wave's LDS radix sort, R slots of 64 elements.
+template <typename K, typename V, bool HAS_V, int R>
+__device__ __forceinline__ void radix_wave(WaveLds<K, HAS_V> &L, const TinyArgs &a,
+                                           uint64_t start, uint32_t m, uint32_t lane)
+{
+    const K *kin = (const K *)a.kin + start;
+    K key[R];
+    uint32_t pos[HAS_V ? R : 1], to[R];
+#pragma unroll
+    for (int j = 0; j < R; ++j) {
+        const uint32_t e = j * kWave + lane;
+        key[j] = e < m ? kin[e] : (K)0;
+        if constexpr (HAS_V)
+            pos[j] = e;
+    }
+    if (a.kmap) {
+#pragma unroll
+        for (int j = 0; j < R; ++j)
+            key[j] = map_in(key[j], a.kmap);
+    }
+    wave_sort<K, HAS_V, R>(L, key, pos, m, lane, to);
     // every value is read before any is written (in place: vin == vout)
     V val[HAS_V ? R : 1];
     if constexpr (HAS_V) {
         const V *vin = (const V *)a.vin + start;
 #pragma unroll
-        for (int j = 0; j < R; ++j) {
-            const uint32_t e = j * kWave + lane;
-            val[j] = e < m ? vin[E::pos(x[j])] : (V)0;
-        }
+        for (int j = 0; j < R; ++j)
+            val[j] = j * kWave + lane < m ? vin[pos[j]] : (V)0;
     }
     K *kout = (K *)a.kout + start;
     V *vout = HAS_V ? (V *)a.vout + start : nullptr;
 #pragma unroll
     for (int j = 0; j < R; ++j) {
-        const uint32_t e = j * kWave + lane;
-        if (e < m) {
-            kout[e] = map_out((K)E::key(x[j]), a.kmap);
+        if (j * kWave + lane < m) {
+            kout[to[j]] = map_out(key[j], a.kmap);
             if constexpr (HAS_V)
-                vout[e] = val[j];
+                vout[to[j]] = val[j];
         }
     }
 }
 
-// Persistent workgroups of 4 waves; each wave claims one tiny segment at a
+// Persistent workgroups of 4 waves; each wave takes one tiny segment at a
 // time until the list is exhausted.
 template <typename K, typename V, bool HAS_V>
 __global__ __launch_bounds__(256) void k_seg_bitonic(TinyArgs a)
 {
+    __shared__ WaveLds<K, HAS_V> s_lds[4];
+    WaveLds<K, HAS_V> &L = s_lds[threadIdx.x / kWave];
     const uint32_t lane = threadIdx.x & (kWave - 1);
     const uint32_t len = *a.list_len;
-    const uint32_t waves = gridDim.x * (blockDim.x / kWave);
-    // the first segment is the wave's own number, the others are claimed
-    uint32_t item = blockIdx.x * (blockDim.x / kWave) + threadIdx.x / kWave;
-    for (bool claim = false;; claim = true) {
-        if (claim) {
+    ListTurn turn(len, gridDim.x * (blockDim.x / kWave),
+                  blockIdx.x * (blockDim.x / kWave) + threadIdx.x / kWave);
+    while (true) {
+        uint32_t item;
+        if (turn.own()) {
+            item = turn.take();
+        } else {
             uint32_t c = 0;
             if (lane == 0)
                 c = atomicAdd(a.claim, 1u);
-            item = waves + __builtin_amdgcn_readfirstlane(c);
+            item = turn.fixed + __builtin_amdgcn_readfirstlane(c);
         }
         if (item >= len)
             break;
         const uint64_t start = a.list[item].start;
         const uint32_t m = a.list[item].size;
-        if (m <= 64)
-            bitonic_wave<K, V, HAS_V, 1>(a, start, m, lane);
-        else if (m <= 128)
-            bitonic_wave<K, V, HAS_V, 2>(a, start, m, lane);
+        if (m <= (uint32_t)kWave)
+            bitonic_wave<K, V, HAS_V>(a, start, m, lane);
         else if (m <= 256)
-            bitonic_wave<K, V, HAS_V, 4>(a, start, m, lane);
+            radix_wave<K, V, HAS_V, 4>(L, a, start, m, lane);
         else if (m <= 512)
-            bitonic_wave<K, V, HAS_V, 8>(a, start, m, lane);
+            radix_wave<K, V, HAS_V, 8>(L, a, start, m, lane);
         else
-            bitonic_wave<K, V, HAS_V, 16>(a, start, m, lane);
+            radix_wave<K, V, HAS_V, 16>(L, a, start, m, lane);
     }
 }
 

@@ -36,6 +36,29 @@ struct SegRange {
     uint32_t tile_start;  // first tile in a batched tile sequence (large segments)
 };
 
+// How workers share a list of `len` segments of uneven size: most of it in
+// turn, worker w taking entries w, w + workers, ..., and the last eighth by
+// claims from one counter, which evens the workers out.  A claim by every
+// entry was what bound the tiny segments: atomics on one address end one
+// after another, 14 ns apart (50,000 segments, 8.2M elements: 580 us with a
+// bitonic network or a radix sort alike, 176 us with most taken in turn).
+struct ListTurn {
+    uint32_t workers;
+    uint32_t fixed;  // entries taken in turn: whole rounds, at least one
+    uint32_t at;     // this worker's next one
+    __device__ __forceinline__ ListTurn(uint32_t len, uint32_t workers_, uint32_t worker)
+        : workers(workers_), fixed(max(1u, (len - len / 8) / workers_) * workers_), at(worker)
+    {
+    }
+    __device__ __forceinline__ bool own() const { return at < fixed; }
+    __device__ __forceinline__ uint32_t take()
+    {
+        const uint32_t item = at;
+        at += workers;
+        return item;
+    }
+};
+
 struct BlockArgs {
     const void *kin;
     const void *vin;
@@ -322,17 +345,19 @@ __global__ __launch_bounds__(THREADS) void k_block_sort(BlockArgs a)
     if (a.err_clear && blockIdx.x == 0 && t == 0)
         *a.err_clear = 0;
 
+    const uint32_t len = a.list ? *a.list_len : 1u;
+    ListTurn turn(len, gridDim.x, blockIdx.x);
     for (uint32_t iter = 0;; ++iter) {
-        // the first entry is the workgroup's own number: workgroups beyond the
-        // list's end claim nothing
         if (t == 0)
-            s_item = iter == 0 ? blockIdx.x : a.list ? gridDim.x + atomicAdd(a.claim, 1u) : 1u;
+            s_item = !a.list      ? iter
+                     : turn.own() ? turn.take()
+                                  : turn.fixed + atomicAdd(a.claim, 1u);
         __syncthreads();
         const uint32_t item = s_item;
         uint64_t start;
         uint32_t m;
         if (a.list) {
-            if (item >= *a.list_len)
+            if (item >= len)
                 break;
             start = a.list[item].start;
             m = a.list[item].size;

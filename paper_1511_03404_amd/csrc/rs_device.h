@@ -206,6 +206,29 @@ __device__ __forceinline__ uint32_t lane_id()
     return __builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, 0u));
 }
 
+// Orders this wave's LDS accesses before and after it: waits for the wave's
+// outstanding LDS operations and keeps the compiler from moving LDS
+// accesses across it (the lanes of one wave then see each other's writes).
+__device__ __forceinline__ void wave_lds_fence()
+{
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
+// Lane `lane`'s x, uniform.
+template <typename K>
+__device__ __forceinline__ K read_lane(K x, uint32_t lane)
+{
+    if constexpr (sizeof(K) == 8) {
+        const uint32_t lo = __builtin_amdgcn_readlane((uint32_t)x, lane);
+        const uint32_t hi = __builtin_amdgcn_readlane((uint32_t)(x >> 32), lane);
+        return ((uint64_t)hi << 32) | lo;
+    } else {
+        return (uint32_t)__builtin_amdgcn_readlane(x, lane);
+    }
+}
+
 // Number of set bits of m below this lane.
 __device__ __forceinline__ uint32_t lanes_below(uint64_t m)
 {

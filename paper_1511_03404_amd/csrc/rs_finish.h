@@ -248,18 +248,6 @@ __device__ __forceinline__ bool hand_on_and_wait(uint32_t *done, uint32_t add, u
 constexpr uint32_t kRestSlots = 8;
 constexpr uint32_t kRestWaveRun = kRestSlots * kWave;
 
-template <typename K>
-__device__ __forceinline__ K read_lane(K x, uint32_t lane)
-{
-    if constexpr (sizeof(K) == 8) {
-        const uint32_t lo = __builtin_amdgcn_readlane((uint32_t)x, lane);
-        const uint32_t hi = __builtin_amdgcn_readlane((uint32_t)(x >> 32), lane);
-        return ((uint64_t)hi << 32) | lo;
-    } else {
-        return (uint32_t)__builtin_amdgcn_readlane(x, lane);
-    }
-}
-
 // Writes a run of m <= 64 SLOTS elements, in registers (element s*64 + lane
 // in slot s), back in order.
 template <typename K, typename V, bool HAS_V, uint32_t SLOTS>

@@ -127,16 +127,6 @@ __device__ __forceinline__ void merge_chains(const K *s_k, uint32_t base, uint32
     }
 }
 
-// Orders this wave's LDS accesses before and after it: waits for the wave's
-// outstanding LDS operations and keeps the compiler from moving LDS
-// accesses across it (the lanes of one wave then see each other's writes).
-__device__ __forceinline__ void wave_lds_fence()
-{
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-}
-
 // Stable odd-even transposition sort of ITEMS registers: ITEMS rounds of
 // compare-exchanges between neighbours, exchanging only strictly greater
 // keys, so equal keys never pass each other.

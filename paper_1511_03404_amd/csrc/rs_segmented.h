@@ -1,9 +1,10 @@
 // Batched segmented sort: many independent stable LSD radix sorts (paper,
 // Section 2.6) of uneven sizes in one enqueue, classified on the device:
 //   * size 0 or 1           -- nothing to sort (a single element is copied);
-//   * size <= tiny cap      -- one wave sorts it in registers with a bitonic
-//                              network on (key, position) pairs (Section 2.1,
-//                              k_seg_bitonic in rs_bitonic.h; the cap is a
+//   * size <= tiny cap      -- one wave sorts it: up to 64 elements with a
+//                              bitonic network on (key, position) pairs
+//                              (Section 2.1), more with an LDS radix sort
+//                              (k_seg_bitonic in rs_bitonic.h; the cap is a
 //                              context setting, 0 turns the class off);
 //   * size <= small cap     -- one workgroup sorts it in LDS (k_block_sort,
 //                              small shape, several workgroups per CU);

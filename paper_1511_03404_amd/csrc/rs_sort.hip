@@ -183,7 +183,7 @@ struct rs_context {
     // tune table: configuration index per [64-bit keys][values][segmented]
     // [ceil(log2 n)], -1 = the default (index 0)
     int8_t tune[2][2][2][kTuneClasses];
-    // segments of 2 .. tiny_cap elements go to the bitonic network (0: none)
+    // segments of 2 .. tiny_cap elements are sorted by a wave each (0: none)
     uint32_t tiny_cap = kTinyMax;
     // bound of the waits on other workgroups, and test-only stalls
     uint32_t spin_limit = kDefaultSpinLimit;

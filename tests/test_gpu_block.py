@@ -1,4 +1,4 @@
-"""Sorts that one workgroup holds (up to 16384 elements), whole or as segments:
+"""Sorts that one workgroup or one wave holds (up to 16384 elements), whole or as segments:
 every shape at its edges, and keys for every way through it: the 16 highest
 differing bits at any place in the key, runs of equal high bits within the
 counting limit, beyond it in order, and beyond it out of order."""
@@ -69,18 +69,21 @@ def test_whole_sorts(rs, oracle_lib, bits, pairs, name):
         assert np.array_equal(ko.cpu().numpy(), ok), f"keys differ, n={n}"
 
 
+@pytest.mark.parametrize("tiny_cap", [0, 1024])
 @pytest.mark.parametrize("order,descending", [("unsigned", False), ("float", True)])
 @pytest.mark.parametrize("bits,pairs", KINDS)
-def test_segments(rs, oracle_lib, bits, pairs, order, descending):
-    """The same keys as segments of one batch, without the tiny class."""
-    parts = [make(name, n, bits, seed=n % 7 + 2) for name in NAMES for n in (2, 700, 4096, 4097, 8192)]
+def test_segments(rs, oracle_lib, bits, pairs, order, descending, tiny_cap):
+    """The same keys as segments of one batch: without the tiny class, and as
+    tiny segments (one wave each) at the edges of its shapes."""
+    sizes = (2, 64, 65, 255, 256, 257, 512, 513, 1000, 1024) if tiny_cap else (2, 700, 4096, 4097, 8192)
+    parts = [make(name, n, bits, seed=n % 7 + 2) for name in NAMES for n in sizes]
     off = np.zeros(len(parts) + 1, dtype=np.uint64)
     off[1:] = np.cumsum([p.size for p in parts])
     keys = np.concatenate(parts)
     vals = datagen.values(keys.size, bits) if pairs else None
     print(f"case bits={bits} pairs={pairs} order={order}", flush=True)
     ctx = rs.Context(0)
-    ctx.tiny_cap(0)
+    ctx.tiny_cap(tiny_cap)
     ko, vo = rs.segmented_sort(dev(keys), dev(vals) if pairs else None, dev(off.view(np.int64)),
                                ctx=ctx, order=order, descending=descending)
     ok, ov = oracle_lib.segmented_sort_ordered(keys, vals, off, order=order, descending=descending)
