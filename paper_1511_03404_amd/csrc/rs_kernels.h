@@ -326,20 +326,44 @@ constexpr uint32_t kSampleMax = 4;        // keys sampled per thread, at most
 constexpr uint32_t kSampleThreads = 1024; // threads of k_plan with 8-bit digits
 constexpr uint32_t kSampleTab = 2 * kSampleMax * kSampleThreads;  // hash table slots
 
+// The highest of D digit positions whose runs, by the product of the largest
+// bins' shares, are within `bound`; 0 if fewer than kFinishSaves positions
+// that move data lie below it.
+template <int D>
+__device__ __forceinline__ int stop_at(uint32_t n, const int *trivial, const uint32_t *largest,
+                                       float bound)
+{
+    const float inv_n = 1.f / (float)n;
+    float mean = (float)n;
+    int at = 0, left = 0;
+    for (int p = D - 1; p >= 0; --p) {
+        if (trivial[p])
+            continue;
+        if (mean <= bound) {
+            ++left;
+        } else {
+            mean *= (float)largest[p] * inv_n;
+            at = p;
+        }
+    }
+    return left >= kFinishSaves ? at : 0;
+}
+
 // Sampled keys whose bits from `shift` up equal those of another one counted
 // before, from an LDS hash table (open addressing on a 32-bit hash; 32-bit
 // keys hash one to one).  The table is clear, *out zero; one barrier after
 // the call *out holds the count.  Called by every thread.
-template <typename K>
-__device__ __forceinline__ void sample_repeats(const K (&key)[kSampleMax], uint32_t count,
-                                               int shift, uint32_t *tag, uint32_t *out)
+template <typename K, uint32_t PER, uint32_t THREADS>
+__device__ __forceinline__ void sample_repeats(const K (&key)[PER], uint32_t count, int shift,
+                                               uint32_t *tag, uint32_t *out)
 {
+    constexpr uint32_t TAB = 2 * PER * THREADS;
     const uint32_t t = threadIdx.x;
     uint32_t repeats = 0;
 #pragma unroll
-    for (uint32_t j = 0; j < kSampleMax; ++j) {
+    for (uint32_t j = 0; j < PER; ++j) {
         bool again = false;
-        if (j * kSampleThreads + t < count) {
+        if (j * THREADS + t < count) {
             const K x = key[j] >> shift;
             uint32_t h;
             if constexpr (sizeof(K) == 8)
@@ -347,11 +371,11 @@ __device__ __forceinline__ void sample_repeats(const K (&key)[kSampleMax], uint3
             else
                 h = x * 0x9E3779B1u;
             h = h ? h : 1u;
-            uint32_t s = (h >> 19) & (kSampleTab - 1);
+            uint32_t s = h >> (32 - __builtin_ctz(TAB));
             // the table holds twice the sample: a free slot or a match is found
             uint32_t old;
             while ((old = atomicCAS(&tag[s], 0u, h)) != 0 && old != h)
-                s = (s + 1) & (kSampleTab - 1);
+                s = (s + 1) & (TAB - 1);
             again = old == h;
         }
         repeats += (uint32_t)__popcll(__ballot(again));
@@ -520,33 +544,15 @@ __global__ __launch_bounds__(kRadix * 4) void k_plan(PlanArgs a)
     int low = 0;
     if constexpr (R == 8) {
         if (a.finish) {
-            const float inv_n = 1.f / (float)a.n;
-            // the highest position whose runs, by the product of shares, are
-            // within `bound`; 0 if the digits below it are fewer than saved
-            auto stop_at = [&](float bound) {
-                float mean = (float)a.n;
-                int at = 0, left = 0;
-                for (int p = D - 1; p >= 0; --p) {
-                    if (s_trivial[p])
-                        continue;
-                    if (mean <= bound) {
-                        ++left;
-                    } else {
-                        mean *= (float)s_max[p] * inv_n;
-                        at = p;
-                    }
-                }
-                return left >= kFinishSaves ? at : 0;
-            };
-            low = stop_at(kFinishMean);
+            low = stop_at<D>(a.n, s_trivial, s_max, kFinishMean);
             if (low) {
-                sample_repeats<K>(sample, a.sample_count, 0, s_tag_same, &s_same);
-                sample_repeats<K>(sample, a.sample_count, low * R, s_tag, &s_repeats);
+                sample_repeats<K, kSampleMax, kSampleThreads>(sample, a.sample_count, 0, s_tag_same, &s_same);
+                sample_repeats<K, kSampleMax, kSampleThreads>(sample, a.sample_count, low * R, s_tag, &s_repeats);
                 __syncthreads();
                 const bool groups = s_same >= kSampleSame;
                 const uint32_t allow = groups ? 0u : a.allow;
                 if (groups && 2 * s_same < a.sample_count)
-                    low = min(low, stop_at(kFinishMeanSame));
+                    low = min(low, stop_at<D>(a.n, s_trivial, s_max, kFinishMeanSame));
                 // the sample's repeats were counted at the first choice; a
                 // lower one has no more
                 while (low && s_repeats - min(s_repeats, s_same) > allow) {
@@ -566,7 +572,7 @@ __global__ __launch_bounds__(kRadix * 4) void k_plan(PlanArgs a)
                     if (t == 0)
                         s_repeats = 0;
                     __syncthreads();
-                    sample_repeats<K>(sample, a.sample_count, low * R, s_tag, &s_repeats);
+                    sample_repeats<K, kSampleMax, kSampleThreads>(sample, a.sample_count, low * R, s_tag, &s_repeats);
                     __syncthreads();
                 }
             }
@@ -1250,11 +1256,46 @@ struct SegHistArgs {
     uint32_t *seg_base;   // [large segment][d][2^R]
     uint32_t *seg_flags;  // [large segment]: first its first chunk (k_seg_hist), then
                           // (k_seg_scan) bit p pass p's digit is the same for the
-                          // whole segment; bit 16 + p pass p's digits are skewed
+                          // whole segment; bit 16 + p pass p's digits are skewed;
+                          // with 8-bit digits kSegLowShift and kSegGiant too
     uint32_t kmap;        // key order applied to every key read
 };
 
 constexpr int kSegSkewShift = 16;
+// 8-bit digits (at most eight positions) leave bits free:
+constexpr int kSegLowShift = 8;             // 4 bits: the lowest position sorted by passes when
+                                            // k_seg_finish orders the rest, else 0
+constexpr uint32_t kSegGiant = 1u << 31;    // an unsorted run longer than a tile (k_seg_last)
+// kSegPassMask: bit p: a segment moves in pass p; and
+constexpr uint32_t kSegAnyFinish = 1u << 16;
+
+// How a large segment moves: the digit positions that its passes sort by, and
+// the moves of its data (those passes, and k_seg_finish if it follows), which
+// alternate between the output and the scratch copy so that the last one
+// lands in the output (in place, an odd number ends in the scratch copy).
+struct SegMoves {
+    uint32_t low;     // k_seg_finish orders by the bits below this position
+    uint32_t digits;  // bit p: pass p moves the segment
+    uint32_t moves;
+    bool odd_in_place;
+    // buffer that move q writes
+    __device__ __forceinline__ uint32_t dst(uint32_t q) const
+    {
+        return odd_in_place ? ((q & 1) ? kBufOut : kBufTmp)
+                            : (((moves - 1 - q) & 1) ? kBufTmp : kBufOut);
+    }
+};
+
+template <typename K, int R>
+__device__ __forceinline__ SegMoves seg_moves(uint32_t flags, bool in_place)
+{
+    SegMoves m;
+    m.low = R == kRadixBits ? (flags >> kSegLowShift) & 15u : 0u;
+    m.digits = ~flags & ((1u << num_passes<K, R>()) - 1u) & ~((1u << m.low) - 1u);
+    m.moves = (uint32_t)__popc(m.digits) + (m.low ? 1u : 0u);
+    m.odd_in_place = in_place && (m.moves & 1);
+    return m;
+}
 
 constexpr int kSegHistThreads = 1024;
 
@@ -1341,13 +1382,21 @@ __global__ __launch_bounds__(256) void k_seg_scan(SegHistArgs a)
     constexpr int D = num_passes<K, R>();
     constexpr int NB = 1 << R;
     static_assert(D <= kSegSkewShift, "pass flags fit 16 bits each");
+    constexpr uint32_t PER = 2, TAB = 2 * PER * 256;  // sampled keys per thread, hash slots
     __shared__ uint32_t s_tmp[8];
-    __shared__ unsigned long long s_sq[256 / kWave];
+    __shared__ float s_sq[256 / kWave];
+    __shared__ int s_trivial[D];
+    __shared__ uint32_t s_max[D];
+    __shared__ uint32_t s_tag[R == kRadixBits ? TAB : 1], s_tag_same[R == kRadixBits ? TAB : 1];
+    __shared__ uint32_t s_repeats, s_same;
     const uint32_t t = threadIdx.x;
     // equal work per segment: workgroups take them in turn, without claims
     // (a grid of workgroups claiming from one counter took 30 us for nothing)
     for (uint32_t item = blockIdx.x; item < a.ctrl[kSegLargeLen]; item += gridDim.x) {
-        const uint32_t size = a.large[item].size;
+        const SegLarge rec = a.large[item];
+        const uint32_t size = rec.size;
+        if (t < (uint32_t)D)
+            s_max[t] = 0;
         uint32_t flags = 0;
         for (int p = 0; p < D; ++p) {
             const uint64_t i = ((uint64_t)item * D + p) * NB + t;
@@ -1358,23 +1407,90 @@ __global__ __launch_bounds__(256) void k_seg_scan(SegHistArgs a)
             // one digit for the whole segment: this pass is the identity
             const bool trivial = __syncthreads_or(c == size) != 0;
             // skewed: sum of squared counts above size^2 / 100 (as k_plan)
-            unsigned long long sq = (unsigned long long)c * c;
-#pragma unroll
-            for (int off = 32; off > 0; off >>= 1)
-                sq += __shfl_xor(sq, off);
-            if ((t & (kWave - 1)) == 0)
+            const float sq = wave_sum((float)c * (float)c);
+            const uint32_t mx = wave_max(c);
+            if ((t & (kWave - 1)) == kWave - 1) {
                 s_sq[t / kWave] = sq;
+                atomicMax(&s_max[p], mx);
+            }
+            if (t == 0)
+                s_trivial[p] = trivial;
             __syncthreads();
-            unsigned long long tot = 0;
+            float tot = 0.f;
 #pragma unroll
             for (int w = 0; w < 256 / kWave; ++w)
                 tot += s_sq[w];
-            const bool skewed = tot > (unsigned long long)size * size / 100ull;
+            const bool skewed = tot > 0.01f * (float)size * (float)size;
             flags |= (trivial ? 1u << p : 0u) | (skewed ? 1u << (kSegSkewShift + p) : 0u);
             __syncthreads();
         }
-        if (t == 0)
+        int low = 0;
+        if constexpr (R == kRadixBits) {
+            // where the segment's passes may stop, as k_plan, from a sample
+            // of 512 of its keys
+            low = stop_at<D>(size, s_trivial, s_max, kFinishMean);
+            if (low) {
+                K sample[PER];
+                const uint32_t stretch = size / (PER * 256);
+#pragma unroll
+                for (uint32_t j = 0; j < PER; ++j) {
+                    const uint32_t i = j * 256 + t;
+                    const uint32_t off = __umulhi(i * 0x9E3779B1u + 0x7F4A7C15u, stretch);
+                    sample[j] = map_in(((const K *)a.kin)[rec.start + i * stretch + off], a.kmap);
+                }
+                const float m = PER * 256.f, runs = (float)size / kFinishRepeatMean;
+                uint32_t allow = (uint32_t)max(3.f, m - runs * (1.f - __expf(-m / runs)));
+                bool same_known = false;
+                while (low) {
+                    for (uint32_t i = t; i < TAB; i += 256) {
+                        s_tag[i] = 0;
+                        s_tag_same[i] = 0;
+                    }
+                    if (t == 0) {
+                        s_repeats = 0;
+                        s_same = 0;
+                    }
+                    __syncthreads();
+                    sample_repeats<K, PER, 256>(sample, PER * 256, low * R, s_tag, &s_repeats);
+                    sample_repeats<K, PER, 256>(sample, PER * 256, 0, s_tag_same, &s_same);
+                    __syncthreads();
+                    const uint32_t repeats = s_repeats, same = s_same;
+                    __syncthreads();
+                    if (!same_known && same >= kSampleSame) {
+                        allow = 0;
+                        if (2 * same < PER * 256) {
+                            const int strict = stop_at<D>(size, s_trivial, s_max, kFinishMeanSame);
+                            if (strict < low) {
+                                low = strict;
+                                same_known = true;
+                                continue;
+                            }
+                        }
+                    }
+                    same_known = true;
+                    if (repeats - min(repeats, same) <= allow)
+                        break;
+                    int left = 0;
+                    do
+                        --low;
+                    while (low && s_trivial[low]);
+                    for (int p = 0; p < low; ++p)
+                        left += !s_trivial[p];
+                    if (left < kFinishSaves)
+                        low = 0;
+                }
+                flags |= (uint32_t)low << kSegLowShift;
+            }
+        }
+        if (t == 0 && size) {
             a.seg_flags[item] = flags;
+            const SegMoves m = seg_moves<K, R>(flags, false);
+            // a segment that does not move is copied in the last pass
+            atomicOr(&a.ctrl[kSegPassMask],
+                     m.digits | (m.low ? kSegAnyFinish : 0u) | (m.moves ? 0u : 1u << (D - 1)));
+        } else if (t == 0) {
+            a.seg_flags[item] = 0;  // no room for its tiles: nothing moves
+        }
         __syncthreads();
     }
 }
@@ -1384,23 +1500,19 @@ __global__ __launch_bounds__(256) void k_seg_scan(SegHistArgs a)
 // look-back chain starts at its first tile.
 
 struct SegPassArgs {
-    const void *src_k;
-    const void *src_v;
-    void *dst_k;
-    void *dst_v;
+    Bufs b;
+    int keys_in_place;
+    int vals_in_place;
     const SegLarge *large;
     const uint32_t *tile_seg;
     const uint32_t *seg_base;  // [large segment][d][2^R]
-    const uint32_t *seg_flags; // [large segment]: trivial and skewed passes (k_seg_scan)
+    uint32_t *seg_flags;       // [large segment] (k_seg_scan)
     uint32_t *ctrl;            // segmented control block
     uint32_t *status;          // look-back words of this pass
     uint32_t *claims;          // claim counters of this pass
     uint32_t max_tiles;        // tiles the workspace holds
     int pass;
-    int shift;
-    int d;
-    uint32_t map_load;   // key order applied to the keys read (first pass)
-    uint32_t map_store;  // key order undone on the keys written (last pass into the output)
+    uint32_t kmap;
     uint32_t spin_limit;  // polls without progress before a wait gives up
     uint32_t stall;       // test-only kStall* bits; 0 in every working call
 };
@@ -1409,9 +1521,14 @@ template <typename K, typename V, bool HAS_V, typename C>
 __global__ __launch_bounds__(C::kThreads) void k_seg_pass(SegPassArgs a)
 {
     constexpr int T = C::kTile;
+    constexpr int R = C::kRadixBits;
+    constexpr int D = num_passes<K, R>();
     constexpr uint32_t NB = C::kBins;
     __shared__ PassLds<K, C, HAS_V> L;
     const uint32_t t = threadIdx.x;
+    if (!((a.ctrl[kSegPassMask] >> a.pass) & 1u))
+        return;  // no segment moves
+    const bool in_place = a.keys_in_place || a.vals_in_place;
     PassArgs pa{};
     pa.ctrl = a.ctrl + (kSegPassCounter - kCtrlTileCounter);
     pa.pass = a.pass;
@@ -1434,81 +1551,76 @@ __global__ __launch_bounds__(C::kThreads) void k_seg_pass(SegPassArgs a)
         const uint32_t lt = tile - rec.tile_start;
         const uint32_t first = lt * T;
         const uint32_t valid = rec.size > first ? std::min<uint32_t>(T, rec.size - first) : 0u;
-        const uint32_t flags = a.seg_flags[seg];
+        const uint32_t flags = __builtin_amdgcn_readfirstlane(a.seg_flags[seg]);
+        const SegMoves m = seg_moves<K, R>(flags, in_place);
         const uint64_t off = rec.start + (uint64_t)lt * T;
-        if ((flags >> a.pass) & 1u) {
-            // the segment's digit is the same everywhere: the pass is the
-            // identity permutation, so the tile is copied (no rank, no
-            // look-back; the segment's other tiles do the same).  All of a
-            // thread's loads are in flight before its first store.
-            const uint32_t off0 = (t / kWave) * (kWave * C::kItems) + t % kWave;
-            K key[C::kItems];
-            V val[HAS_V ? C::kItems : 1];
-            load_tile<K, V, HAS_V, C::kItems>((const K *)a.src_k + off,
-                                              HAS_V ? (const V *)a.src_v + off : nullptr, valid,
-                                              off0, key, val, valid == (uint32_t)T, a.map_load);
-            K *dk = (K *)a.dst_k + off;
-            V *dv = HAS_V ? (V *)a.dst_v + off : nullptr;
-#pragma unroll
-            for (int j = 0; j < C::kItems; ++j) {
-                const uint32_t i = off0 + j * kWave;
-                if (i < valid) {
-                    dk[i] = map_out(key[j], a.map_store);
-                    if constexpr (HAS_V)
-                        dv[i] = val[j];
+        if (!((m.digits >> a.pass) & 1u)) {
+            // the segment does not move in this pass; one that never moves is
+            // copied here, each array not sorted in place
+            if (m.moves == 0 && a.pass == D - 1 && valid) {
+                if (!a.keys_in_place)
+                    copy_range(pick<const K>(a.b, kBufIn, false), pick<K>(a.b, kBufOut, false),
+                               off, off + valid, t, C::kThreads);
+                if constexpr (HAS_V) {
+                    if (!a.vals_in_place)
+                        copy_range(pick<const V>(a.b, kBufIn, true), pick<V>(a.b, kBufOut, true),
+                                   off, off + valid, t, C::kThreads);
                 }
             }
             __syncthreads();  // every thread has read this tile's id
             continue;
         }
-        const uint32_t dbase = t < NB ? a.seg_base[((uint64_t)seg * a.d + a.pass) * NB + t] : 0u;
-        pass_tile<K, V, HAS_V, C>(L, (const K *)a.src_k + off,
-                                  HAS_V ? (const V *)a.src_v + off : nullptr,
-                                  (K *)a.dst_k + rec.start,
-                                  HAS_V ? (V *)a.dst_v + rec.start : nullptr, valid, rec.size,
-                                  tile, rec.tile_start, a.status, nullptr, dbase, a.shift,
-                                  ((flags >> (kSegSkewShift + a.pass)) & 1u) != 0, a.map_load,
-                                  a.map_store, pa, [](uint32_t) {});
+        const uint32_t q = (uint32_t)__popc(m.digits & ((1u << a.pass) - 1u));
+        const uint32_t src = q == 0 ? kBufIn : m.dst(q - 1);
+        const uint32_t dst = m.dst(q);
+        const uint32_t dbase = t < NB ? a.seg_base[((uint64_t)seg * D + a.pass) * NB + t] : 0u;
+        pass_tile<K, V, HAS_V, C>(L, pick<const K>(a.b, src, false) + off,
+                                  HAS_V ? pick<const V>(a.b, src, true) + off : nullptr,
+                                  pick<K>(a.b, dst, false) + rec.start,
+                                  HAS_V ? pick<V>(a.b, dst, true) + rec.start : nullptr, valid,
+                                  rec.size, tile, rec.tile_start, a.status, nullptr, dbase,
+                                  a.pass * R, ((flags >> (kSegSkewShift + a.pass)) & 1u) != 0,
+                                  q == 0 ? a.kmap : 0u,
+                                  q == m.moves - 1 && dst == kBufOut ? a.kmap : 0u, pa,
+                                  [](uint32_t) {});
     }
 }
 
-// In-place segmented sort with an odd number of passes: the large segments
-// end in the scratch copy; copy them back, tile by tile.
+// In-place segmented sort: the large segments that moved an odd number of
+// times end in the scratch copy; copy them back, tile by tile.
 struct SegCopyArgs {
-    const void *src_k;
-    const void *src_v;
-    void *dst_k;
-    void *dst_v;
+    Bufs b;
     const SegLarge *large;
     const uint32_t *tile_seg;
+    const uint32_t *seg_flags;
     const uint32_t *ctrl;  // segmented control block
     uint32_t max_tiles;
     uint32_t tile;  // elements per tile
     uint32_t kmap;  // key order undone on the keys copied out
 };
 
-template <typename K, bool HAS_V>
+template <typename K, bool HAS_V, int R>
 __global__ __launch_bounds__(256) void k_seg_copy(SegCopyArgs a)
 {
     const uint32_t tiles = std::min(a.ctrl[kSegTiles], a.max_tiles);
     for (uint32_t tl = blockIdx.x; tl < tiles; tl += gridDim.x) {
-        const SegLarge rec = a.large[a.tile_seg[tl]];
+        const uint32_t seg = a.tile_seg[tl];
+        const SegLarge rec = a.large[seg];
         const uint64_t lo = (uint64_t)(tl - rec.tile_start) * a.tile;
-        if (lo >= rec.size)
+        if (lo >= rec.size || !seg_moves<K, R>(a.seg_flags[seg], true).odd_in_place)
             continue;
         const uint64_t hi = std::min<uint64_t>(lo + a.tile, rec.size);
+        const K *sk = pick<const K>(a.b, kBufTmp, false) + rec.start;
+        K *dk = pick<K>(a.b, kBufOut, false) + rec.start;
         if (a.kmap) {
-            const K *sk = (const K *)a.src_k + rec.start;
-            K *dk = (K *)a.dst_k + rec.start;
             for (uint64_t i = lo + threadIdx.x; i < hi; i += 256)
                 dk[i] = map_out(sk[i], a.kmap);
         } else {
-            copy_range((const K *)a.src_k + rec.start, (K *)a.dst_k + rec.start, lo, hi,
-                       threadIdx.x, 256);
+            copy_range(sk, dk, lo, hi, threadIdx.x, 256);
         }
         if constexpr (HAS_V)
-            copy_range((const K *)a.src_v + rec.start, (K *)a.dst_v + rec.start, lo, hi,
-                       threadIdx.x, 256);
+            copy_range(pick<const K>(a.b, kBufTmp, true) + rec.start,
+                       pick<K>(a.b, kBufOut, true) + rec.start, lo, hi, threadIdx.x, 256);
     }
 }
 

@@ -32,7 +32,12 @@ struct SegOps {
     void (*hist)(const SegHistArgs &, uint32_t grid, hipStream_t);
     void (*scan)(const SegHistArgs &, uint32_t grid, hipStream_t);
     void (*pass)(const SegPassArgs &, uint32_t grid, hipStream_t);
+    void (*copy)(const SegCopyArgs &, uint32_t grid, hipStream_t);
     const void *hist_kernel, *scan_kernel, *pass_kernel;
+    // 8-bit digits only (null otherwise), as SortOps
+    void (*finish)(const SegFinishArgs &, uint32_t grid, hipStream_t);
+    void (*last)(const SegLastArgs &, uint32_t grid, hipStream_t);
+    const void *finish_kernel;
 };
 
 // Tables of the plain and segmented sorts for 32- and 64-bit keys.
@@ -97,19 +102,44 @@ struct SegLaunch {
     {
         hipLaunchKernelGGL((k_seg_pass<K, K, HAS_V, C>), dim3(grid), dim3(THREADS), 0, s, a);
     }
+    static void copy(const SegCopyArgs &a, uint32_t grid, hipStream_t s)
+    {
+        hipLaunchKernelGGL((k_seg_copy<K, HAS_V, R>), dim3(grid), dim3(256), 0, s, a);
+    }
+    static void finish(const SegFinishArgs &a, uint32_t grid, hipStream_t s)
+    {
+        hipLaunchKernelGGL((k_seg_finish<K, K, HAS_V, kFinishThreads, kFinishItems>), dim3(grid),
+                           dim3(kFinishThreads), 0, s, a);
+    }
+    static void last(const SegLastArgs &a, uint32_t grid, hipStream_t s)
+    {
+        hipLaunchKernelGGL((k_seg_last<K, K, HAS_V, C>), dim3(grid), dim3(THREADS), 0, s, a);
+    }
     static SegOps ops()
     {
-        return SegOps{R,
-                      THREADS,
-                      ITEMS,
-                      C::kTile,
-                      num_passes<K, R>(),
-                      &hist,
-                      &scan,
-                      &pass,
-                      (const void *)k_seg_hist<K, R>,
-                      (const void *)k_seg_scan<K, R>,
-                      (const void *)k_seg_pass<K, K, HAS_V, C>};
+        SegOps o{R,
+                 THREADS,
+                 ITEMS,
+                 C::kTile,
+                 num_passes<K, R>(),
+                 &hist,
+                 &scan,
+                 &pass,
+                 &copy,
+                 (const void *)k_seg_hist<K, R>,
+                 (const void *)k_seg_scan<K, R>,
+                 (const void *)k_seg_pass<K, K, HAS_V, C>,
+                 nullptr,
+                 nullptr,
+                 nullptr};
+        static_assert(C::kTile % (kFinishThreads * kFinishItems) == 0, "whole sweep tiles");
+        if constexpr (R == kRadixBits) {
+            o.finish = &finish;
+            o.last = &last;
+            o.finish_kernel =
+                (const void *)k_seg_finish<K, K, HAS_V, kFinishThreads, kFinishItems>;
+        }
+        return o;
     }
 };
 

@@ -9,11 +9,13 @@
 //   * size <= small cap     -- one workgroup sorts it in LDS (k_block_sort,
 //                              small shape, several workgroups per CU);
 //   * size <= medium cap    -- the same with the medium shape;
-//   * larger                -- per-segment digit histograms (k_seg_hist), then
-//                              one digit-pass launch per digit over the tiles
-//                              of all large segments (k_seg_pass, in
-//                              rs_kernels.h), each segment with its own
-//                              look-back chain.
+//   * larger                -- per-segment digit histograms (k_seg_hist) and
+//                              plans (k_seg_scan), then one digit-pass launch
+//                              per digit over the tiles of all large segments
+//                              (k_seg_pass, in rs_kernels.h), each segment
+//                              with its own look-back chain and moving only in
+//                              the passes of its plan, then the sweep that
+//                              orders the short runs left (rs_finish.h).
 // Only device counters decide the work, so the sequence is graph-capturable
 // and needs no host round trip.
 #pragma once
@@ -43,7 +45,10 @@ constexpr int kSegTinyClaim = 9;
 constexpr int kSegPassCounter = 32; // [32, 48): group counter per pass
 constexpr int kSegChunks = 16;      // histogram chunks of the large segments
 constexpr int kSegChunkClaim = 17;
-constexpr int kSegWords = 64;
+constexpr int kSegStageDone = 18;   // [18, 27): items done per stage of k_seg_last
+constexpr int kSegPassMask = 49;    // passes in which a segment moves, kSegAnyFinish
+constexpr int kSegWords = 64;       // (k_seg_finish and k_seg_last: the words of the plain
+                                    // sort's control block from kCtrlUnsorted on)
 // Large segments are histogrammed in chunks of this many elements, so that
 // one huge segment does not leave a single workgroup reading it alone: at
 // most 2^18 (a chunk's end adds its counts to memory), fewer when the batch

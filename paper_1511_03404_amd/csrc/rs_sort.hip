@@ -1020,11 +1020,9 @@ static rs_status run_segmented(rs_context *ctx, const void *kin, const void *vin
             hipLaunchKernelGGL(kern, dim3(g), dim3(B::kMediumThreads), 0, s, ba);
         });
     }
-    // large segments: per-segment histograms, then the batched digit passes.
-    // Pass p writes the output when d - 1 - p is even, the scratch copy
-    // otherwise, so the last pass lands in the output; in place (the first
-    // pass may not write its own input) with an odd d, the passes start in
-    // the scratch copy and the large segments are copied back at the end.
+    // large segments: per-segment histograms and plans, then the batched digit
+    // passes (each segment moves in those that its plan names), and for 8-bit
+    // digits the sweep that orders the runs a plan leaves
     {
         SegHistArgs ha{kin,      large,    chunk_seg, (uint32_t)L.max_chunks, seg_chunk(total),
                        ctrl,     seg_hist, seg_base,  seg_flags,              kmap};
@@ -1033,46 +1031,52 @@ static rs_status run_segmented(rs_context *ctx, const void *kin, const void *vin
         const uint32_t gs = std::min<uint32_t>(grid_of(op.scan_kernel, 256), nseg);
         launch(ctx, s, "k_seg_scan", [&] { op.scan(ha, gs, s); });
     }
-    const bool in_place = kin == (const void *)kout || (HAS_V && vin == (const void *)vout);
-    const bool copy_back = in_place && (L.d & 1);
-    {
-        const uint32_t g = grid_of(op.pass_kernel, op.threads);
-        const void *src_k = kin, *src_v = vin;
-        for (int p = 0; p < L.d; ++p) {
-            const bool to_out = copy_back ? (p & 1) != 0 : ((L.d - 1 - p) & 1) == 0;
-            SegPassArgs pa{};
-            pa.src_k = src_k;
-            pa.src_v = src_v;
-            pa.dst_k = to_out ? kout : tmp_k;
-            pa.dst_v = to_out ? vout : tmp_v;
-            pa.large = large;
-            pa.tile_seg = tile_seg;
-            pa.seg_base = seg_base;
-            pa.seg_flags = seg_flags;
-            pa.ctrl = ctrl;
-            pa.status = status + (uint64_t)p * L.max_tiles * L.bins;
-            pa.claims = status + (uint64_t)L.d * L.max_tiles * L.bins + (uint64_t)p * L.claim_words;
-            pa.max_tiles = (uint32_t)L.max_tiles;
-            pa.pass = p;
-            pa.shift = p * op.r;
-            pa.d = L.d;
-            pa.map_load = p == 0 ? kmap : 0u;
-            pa.map_store = (p == L.d - 1 && to_out) ? kmap : 0u;
-            pa.spin_limit = ctx->spin_limit;
-            pa.stall = ctx->stall;
-            launch(ctx, s, sizeof(K) == 4 ? "k_seg_pass_u32" : "k_seg_pass_u64",
-                   [&] { op.pass(pa, g, s); });
-            src_k = pa.dst_k;
-            src_v = pa.dst_v;
-        }
+    SegPassArgs pa{};
+    pa.b = Bufs{kin, vin, kout, vout, tmp_k, tmp_v};
+    pa.keys_in_place = kin == (const void *)kout;
+    pa.vals_in_place = HAS_V && vin == (const void *)vout;
+    pa.large = large;
+    pa.tile_seg = tile_seg;
+    pa.seg_base = seg_base;
+    pa.seg_flags = seg_flags;
+    pa.ctrl = ctrl;
+    pa.max_tiles = (uint32_t)L.max_tiles;
+    pa.kmap = kmap;
+    pa.spin_limit = ctx->spin_limit;
+    pa.stall = ctx->stall;
+    const bool in_place = pa.keys_in_place || pa.vals_in_place;
+    const uint32_t pass_grid = grid_of(op.pass_kernel, op.threads);
+    for (int p = 0; p < L.d; ++p) {
+        pa.status = status + (uint64_t)p * L.max_tiles * L.bins;
+        pa.claims = status + (uint64_t)L.d * L.max_tiles * L.bins + (uint64_t)p * L.claim_words;
+        pa.pass = p;
+        launch(ctx, s, sizeof(K) == 4 ? "k_seg_pass_u32" : "k_seg_pass_u64",
+               [&] { op.pass(pa, pass_grid, s); });
     }
-    if (copy_back) {
-        SegCopyArgs cp{tmp_k, tmp_v, kout, vout, large, tile_seg, ctrl, (uint32_t)L.max_tiles,
-                       (uint32_t)op.tile, kmap};
+    if (op.finish) {
+        // the list of long runs takes the place of the passes' look-back
+        // words: more than a word pair for every 65 elements
+        uint2 *list = (uint2 *)status;
+        const uint32_t list_cap = (uint32_t)std::min<uint64_t>(
+            0xFFFFFFFFu, (uint64_t)L.d * L.max_tiles * L.bins / 2);
+        const uint32_t per = (uint32_t)op.tile / (kFinishThreads * kFinishItems);
+        const uint32_t most = grid_of(op.finish_kernel, kFinishThreads);
+        uint32_t group = per;
+        while (group % 2 == 0 && total / op.tile * (per / group) < 2 * most)
+            group /= 2;
+        const SegFinishArgs fa{pa.b, large, tile_seg, seg_flags, ctrl, pa.max_tiles,
+                               (uint32_t)op.tile, group, list, list_cap, kmap, in_place};
+        const uint32_t fg = (uint32_t)std::min<uint64_t>(L.max_tiles * (per / group), most);
+        launch(ctx, s, "k_seg_finish", [&] { op.finish(fa, fg, s); });
+        pa.status = status;
+        const SegLastArgs la{pa, L.max_tiles * L.bins, list, list_cap};
+        launch(ctx, s, "k_seg_last", [&] { op.last(la, pass_grid, s); });
+    }
+    if (in_place) {
+        const SegCopyArgs cp{pa.b, large, tile_seg, seg_flags, ctrl, pa.max_tiles,
+                             (uint32_t)op.tile, kmap};
         const uint32_t g = (uint32_t)std::min<uint64_t>(L.max_tiles, 4096);
-        launch(ctx, s, "k_seg_copy", [&] {
-            hipLaunchKernelGGL((k_seg_copy<K, HAS_V>), dim3(g), dim3(256), 0, s, cp);
-        });
+        launch(ctx, s, "k_seg_copy", [&] { op.copy(cp, g, s); });
     }
     const hipError_t e = hipGetLastError();
     if (e != hipSuccess)

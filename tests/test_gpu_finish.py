@@ -175,3 +175,76 @@ def test_graph_replay(rs, oracle_lib):
         ok, ov = oracle_lib.sort(k, datagen.values(n, 32))
         assert np.array_equal(ko.cpu().numpy(), ok) and np.array_equal(vo.cpu().numpy(), ov)
     ctx.close()
+
+
+PASS_MASK, ANY_FINISH = 49, 1 << 16
+
+
+def batch_checked(rs, oracle_lib, parts, pairs, in_place=False, order="unsigned",
+                  descending=False):
+    keys = np.concatenate(parts)
+    bits = keys.dtype.itemsize * 8
+    off = np.zeros(len(parts) + 1, dtype=np.uint64)
+    off[1:] = np.cumsum([p.size for p in parts])
+    vals = datagen.values(keys.size, bits) if pairs else None
+    ctx = rs.Context(0)
+    ws = torch.empty(ctx.segmented_workspace_bytes(bits, pairs, keys.size, len(parts)),
+                     dtype=torch.uint8, device="cuda")
+    kd, vd = dev(keys), dev(vals) if pairs else None
+    ko, vo = rs.segmented_sort(kd, vd, dev(off.view(np.int64)), kd if in_place else None,
+                               vd if in_place else None, ctx=ctx, workspace=ws, order=order,
+                               descending=descending)
+    assert ctx.status(ws) == rs.RS_OK
+    ok, ov = oracle_lib.segmented_sort_ordered(keys, vals, off, order=order, descending=descending)
+    assert np.array_equal(ko.cpu().numpy(), ok), "keys differ"
+    if pairs:
+        assert np.array_equal(vo.cpu().numpy(), ov), "values differ"
+    words = ws[:256].cpu().numpy().view(np.uint32)
+    ctx.close()
+    return words
+
+
+@pytest.mark.parametrize("in_place", [False, True])
+@pytest.mark.parametrize("order,descending", [("unsigned", False), ("float", True)])
+@pytest.mark.parametrize("bits,pairs", KINDS)
+def test_segments_of_every_route(rs, oracle_lib, bits, pairs, order, descending, in_place):
+    """Large segments side by side whose plans differ: two or more passes and
+    the sweep, every digit, one pass fewer, none at all; small ones between."""
+    g = np.random.RandomState(8)
+
+    def uni(n, seed):
+        return datagen.keys("uniform", n, bits, seed=seed)
+
+    one = uni(40000, 5)
+    one[:] = one[0]
+    groups = uni(2000, 6)[g.randint(0, 2000, 64000)]
+    uneven = uni(50001, 7)
+    uneven[g.rand(50001) < 0.4] = uneven[3]
+    few = uni(30000, 9) % uni(1, 1).dtype.type(1 << 18)
+    parts = [uni(16385, 1), uni(70001, 2), uni(3, 3), one, uni(20000, 4), groups, uneven,
+             uni(5000, 8), few, datagen.keys("sorted", 100000, bits, seed=10),
+             datagen.keys("gaussian", 300007, bits, seed=11), clusters(300007, bits, 3, 300, 24, 12),
+             clusters(400000, bits, 1, 700, 24, 13)]
+    print(f"case bits={bits} pairs={pairs} order={order} in_place={in_place}", flush=True)
+    w = batch_checked(rs, oracle_lib, parts, pairs, in_place, order, descending)
+    assert w[PASS_MASK] & ANY_FINISH
+    if order == "unsigned":
+        assert w[UNSORTED] and w[LONG_LEN] >= 4
+
+
+@pytest.mark.parametrize("in_place", [False, True])
+@pytest.mark.parametrize("pairs", [False, True])
+def test_segment_with_a_run_longer_than_a_tile(rs, oracle_lib, pairs, in_place):
+    parts = [datagen.keys("uniform", 20000, 64, seed=1), clusters(1 << 23, 64, 1, 17000, 24, 2),
+             datagen.keys("gaussian", 60000, 64, seed=3)]
+    print(f"case pairs={pairs} in_place={in_place}", flush=True)
+    w = batch_checked(rs, oracle_lib, parts, pairs, in_place, "signed", True)
+    assert w[GIANT] == 1 and w[LONGER_LEN] >= 1
+
+
+@pytest.mark.parametrize("bits", [32, 64])
+def test_batches_that_do_not_move(rs, oracle_lib, bits):
+    parts = [np.full(n, n, dtype=np.uint32 if bits == 32 else np.uint64) for n in (20000, 40001)]
+    w = batch_checked(rs, oracle_lib, parts, True)
+    assert w[PASS_MASK] == 1 << (bits // 8 - 1)
+    batch_checked(rs, oracle_lib, parts, True, in_place=True)
