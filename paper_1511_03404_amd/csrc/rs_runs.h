@@ -124,7 +124,8 @@ __device__ __forceinline__ int32_t run_move(const K *s_k, uint32_t at, K key, ui
                                : next ? kWave - 1 - lane + __builtin_ctzll(next)
                                       : 2 * kWave;
         *whole = back + ahead < kRunMax;
-        dist = __ballot(*whole) ? kRunMax - 1 : 0;
+        // the longest run ordered here: the others need no distance
+        dist = __builtin_amdgcn_readlane(wave_max(*whole ? back + ahead : 0u), kWave - 1);
         clear = 0;
     }
     uint32_t up = 0, down = 0;

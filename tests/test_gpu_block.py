@@ -33,6 +33,9 @@ def make(name, n, bits, seed):
         at = g.permutation(n)[: max(2, n // 3)]
         low = dt((1 << (bits - 20)) - 1)
         k[at] = (k[at[0]] & ~low) | (k[at] & low)
+    elif name == "two_keys_run":  # two keys, many of each, in one run out of order
+        at = g.permutation(n)[: max(2, n // 3)]
+        k[at] = k[at[0]] ^ (g.randint(0, 2, at.size).astype(k.dtype) << dt(bits // 4))
     elif name == "equal_run":  # the same, but all its keys equal
         k[g.permutation(n)[: max(2, n // 3)]] = k[0]
     elif name == "mid_bits":  # differing bits 17..34 (64-bit) or 5..21, ones above
@@ -48,7 +51,7 @@ def make(name, n, bits, seed):
     return k
 
 
-NAMES = ["uniform", "high_run", "equal_run", "mid_bits", "top_byte_and_low", "small", "one"]
+NAMES = ["uniform", "high_run", "two_keys_run", "equal_run", "mid_bits", "top_byte_and_low", "small", "one"]
 SIZES = [2, 65, 1024, 1025, 2048, 2049, 4095, 4097, 8192, 8193, 16384]
 
 
