@@ -274,10 +274,10 @@ rs_status rs_segmented_tiny_cap_get(const rs_context *ctx, uint32_t *cap);
  * given order (position i holds the pair with the i-th smallest key,
  * equal keys in input order).
  *
- * On the device: tiles of 8192 elements are sorted in one workgroup's LDS
- * (a stable odd-even transposition network per thread, then merge-path
- * merges in LDS), then ceil(log2(n / 8192)) merge levels each read and
- * write every element once.  keys_in may equal keys_out (and vals_in
+ * On the device: tiles are sorted in one workgroup's LDS, then merge levels,
+ * one for every doubling from the tile's length to n, each read and write
+ * every element once.  A tile is 8192 elements up to n = 2^21, above that
+ * 16384 (8192 for 64-bit pairs).  keys_in may equal keys_out (and vals_in
  * vals_out): in place.  ws: a device buffer of at least
  * rs_merge_workspace_bytes() bytes (scratch copies of keys and values and
  * one split word per 2048 outputs), 256-byte aligned, or NULL for the

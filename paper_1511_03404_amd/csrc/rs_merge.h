@@ -2,10 +2,8 @@
 // each, merge sorted runs with a stable merge until one remains), the
 // comparison-based counterpart of the radix path.
 //
-//   k_merge_tile   one workgroup sorts a tile of THREADS x ITEMS elements:
-//                  each thread sorts its ITEMS in registers with an odd-even
-//                  transposition network, then the workgroup merges runs of
-//                  ITEMS, 2 ITEMS, ... in LDS until the tile is one run;
+//   k_merge_tile   one workgroup sorts a tile of THREADS x ITEMS elements in
+//                  LDS (block_sort, rs_block.h): the runs to merge;
 //   k_merge_split  for one merge level (runs of w elements merged pairwise),
 //                  the merge-path split of every output tile: how many of the
 //                  tile's first outputs come from the left run;
@@ -19,24 +17,25 @@
 // load, undone on the last store).  Positions are 32-bit (n < 2^30).
 #pragma once
 
+#include "rs_block.h"
 #include "rs_device.h"
 
 namespace rs {
 
-// Shapes measured on MI355X (2^26 32-bit and 2^25 64-bit pairs): short
-// per-thread merges and many waves hide the LDS latency of the merge better
-// than long ones; more than one merge chain per thread (interleaved chains,
-// each with its own split) costs more ALU than it hides.  Tile sorts of 8192
-// elements; merge-pass workgroups of 2048 outputs.
+// Shapes measured on MI355X.  The merge passes run at the copy rate, so what
+// counts at large n is their number: tiles of up to 16384 elements (8192
+// 64-bit pairs), what LDS holds.  In a merge pass short per-thread merges and
+// many waves hide the LDS latency better than long ones; more than one merge
+// chain per thread (interleaved chains, each with its own split) costs more
+// ALU than it hides.
 template <typename K, bool HAS_V>
 struct MergeShape {
     static constexpr int kTileThreads = 1024;
-    static constexpr int kTileItems = 8;
-    static constexpr int kTileChains = 1;  // independent merge chains per thread
+    static constexpr int kTileItems = sizeof(K) == 8 && HAS_V ? 8 : 16;
     static constexpr int kPassThreads = sizeof(K) == 8 ? 512 : 256;
     static constexpr int kPassItems = sizeof(K) == 8 ? 4 : 8;
     static constexpr int kPassChains = 1;
-    static constexpr int kTile = kTileThreads * kTileItems;      // elements per tile sort
+    static constexpr int kMaxTile = kTileThreads * kTileItems;   // elements per tile sort
     static constexpr int kPassTile = kPassThreads * kPassItems;  // outputs per merge-pass tile
 };
 
@@ -127,148 +126,54 @@ __device__ __forceinline__ void merge_chains(const K *s_k, uint32_t base, uint32
     }
 }
 
-// Stable odd-even transposition sort of ITEMS registers: ITEMS rounds of
-// compare-exchanges between neighbours, exchanging only strictly greater
-// keys, so equal keys never pass each other.
-template <typename K, typename V, bool HAS_V, int ITEMS>
-__device__ __forceinline__ void register_sort(K (&key)[ITEMS], V (&val)[HAS_V ? ITEMS : 1])
-{
-#pragma unroll
-    for (int r = 0; r < ITEMS; ++r) {
-#pragma unroll
-        for (int j = r & 1; j + 1 < ITEMS; j += 2) {
-            const bool sw = key[j] > key[j + 1];
-            const K lo = sw ? key[j + 1] : key[j];
-            const K hi = sw ? key[j] : key[j + 1];
-            key[j] = lo;
-            key[j + 1] = hi;
-            if constexpr (HAS_V) {
-                const V vl = sw ? val[j + 1] : val[j];
-                const V vh = sw ? val[j] : val[j + 1];
-                val[j] = vl;
-                val[j + 1] = vh;
-            }
-        }
-    }
-}
-
 struct MergeTileArgs {
     const void *kin;
     const void *vin;
     void *kout;
     void *vout;
     uint32_t n;
+    uint32_t tile;       // elements per workgroup, at most THREADS x ITEMS
     uint32_t map_load;   // key order applied on load
     uint32_t map_store;  // key order undone on store (when no merge level follows)
 };
 
-template <typename K, typename V, bool HAS_V, int THREADS, int ITEMS, int CHAINS>
+// A tile sort is bound by LDS: per 8-bit digit every element takes an atomic
+// on its lane-mask word, two reads and a write there.  Merging in LDS from 8
+// sorted elements per thread instead, ten rounds, 2^24 32-bit pairs took 223 us
+// in tiles of 8192, and one more merge level (62 us with its splits); tiles of
+// 16384 in two counting sorts and a sweep take 167.  A tile whose runs of equal
+// high bits are long and out of order needs every digit and takes longer than
+// the merges did: 2^24 keys drawn from a power law and spread by a
+// multiplicative hash, the whole sort 624 -> 731 us (32-bit), 825 -> 929
+// (64-bit), where uniform keys went 631 -> 536 and 834 -> 720.
+template <typename K, typename V, bool HAS_V, int THREADS, int ITEMS>
 __global__ __launch_bounds__(THREADS) void k_merge_tile(MergeTileArgs a)
 {
-    constexpr uint32_t T = THREADS * ITEMS;
-    constexpr int SLOTS = PaddedLen<T, ITEMS>::value;
-    __shared__ K s_k[SLOTS];
-    __shared__ V s_v[HAS_V ? SLOTS : 1];
-
-    const uint32_t t = threadIdx.x;
-    const uint32_t base = blockIdx.x * T;
-    const uint32_t valid = min(T, a.n - base);
+    __shared__ BlockLds<K, HAS_V, THREADS, ITEMS> L;
+    const uint32_t base = blockIdx.x * a.tile;
+    const BlockItems<THREADS, ITEMS> it(min(a.tile, a.n - base));
     const K *kin = (const K *)a.kin + base;
     const V *vin = HAS_V ? (const V *)a.vin + base : nullptr;
-
-    // coalesced load into LDS; padding keys (all ones) stay behind every
-    // real key because they come last and every merge is stable
-    {
-        K key[ITEMS];
-        V val[HAS_V ? ITEMS : 1];
-#pragma unroll
-        for (int j = 0; j < ITEMS; ++j) {
-            const uint32_t e = j * THREADS + t;
-            key[j] = e < valid ? kin[e] : KeyTraits<K>::kPad;
-            if constexpr (HAS_V)
-                val[j] = e < valid ? vin[e] : (V)0;
-        }
-        if (a.map_load) {
-#pragma unroll
-            for (int j = 0; j < ITEMS; ++j) {
-                const K mk = map_in(key[j], a.map_load);
-                key[j] = j * THREADS + t < valid ? mk : key[j];
-            }
-        }
-#pragma unroll
-        for (int j = 0; j < ITEMS; ++j) {
-            const uint32_t e = j * THREADS + t;
-            s_k[lds_slot<ITEMS>(e)] = key[j];
-            if constexpr (HAS_V)
-                s_v[lds_slot<ITEMS>(e)] = val[j];
-        }
-    }
-    __syncthreads();
-
-    // each thread: its ITEMS consecutive elements, sorted in registers
     K key[ITEMS];
     V val[HAS_V ? ITEMS : 1];
-#pragma unroll
-    for (int j = 0; j < ITEMS; ++j) {
-        key[j] = s_k[lds_slot<ITEMS>(t * ITEMS + j)];
+    it.each([&](int j) {
+        key[j] = it.has(j) ? kin[it.at(j)] : (K)0;
         if constexpr (HAS_V)
-            val[j] = s_v[lds_slot<ITEMS>(t * ITEMS + j)];
-    }
-    register_sort<K, V, HAS_V, ITEMS>(key, val);
-
-    // merge runs of w elements pairwise in LDS, w = ITEMS, 2 ITEMS, ...
-    // While a pair of runs (2w elements) lies within one wave's kWave x ITEMS
-    // elements, a round reads only what its own wave wrote: a wave-level
-    // fence orders it (LDS accesses of one wave complete in order once the
-    // compiler waits for them); larger rounds need the workgroup barrier.
-    constexpr uint32_t kWaveSpan = kWave * ITEMS;
-    for (uint32_t w = ITEMS; w < T; w *= 2) {
-        const bool in_wave = 2 * w <= kWaveSpan;
-        if (in_wave)
-            wave_lds_fence();
-        else
-            __syncthreads();  // every read of the previous round is done
-#pragma unroll
-        for (int j = 0; j < ITEMS; ++j) {
-            s_k[lds_slot<ITEMS>(t * ITEMS + j)] = key[j];
-            if constexpr (HAS_V)
-                s_v[lds_slot<ITEMS>(t * ITEMS + j)] = val[j];
-        }
-        if (in_wave)
-            wave_lds_fence();
-        else
-            __syncthreads();
-        const uint32_t o = t * ITEMS;          // first output of this thread
-        const uint32_t pb = o & ~(2 * w - 1);  // its pair of runs
-        uint32_t src[ITEMS];
-        merge_chains<K, ITEMS, CHAINS, ITEMS>(s_k, pb, w, w, o - pb, key, src);
-        if constexpr (HAS_V) {
-#pragma unroll
-            for (int j = 0; j < ITEMS; ++j)
-                val[j] = s_v[lds_slot<ITEMS>(src[j])];
-        }
-    }
-
-    // blocked registers -> LDS -> coalesced store
-    __syncthreads();
-#pragma unroll
-    for (int j = 0; j < ITEMS; ++j) {
-        s_k[lds_slot<ITEMS>(t * ITEMS + j)] = key[j];
-        if constexpr (HAS_V)
-            s_v[lds_slot<ITEMS>(t * ITEMS + j)] = val[j];
-    }
-    __syncthreads();
+            val[j] = it.has(j) ? vin[it.at(j)] : (V)0;
+    });
+    if (a.map_load)
+        it.each([&](int j) { key[j] = map_in(key[j], a.map_load); });
+    uint32_t to[ITEMS];
+    block_sort<K, V, HAS_V, THREADS, ITEMS>(L, it, key, val, to);
     K *kout = (K *)a.kout + base;
     V *vout = HAS_V ? (V *)a.vout + base : nullptr;
-#pragma unroll
-    for (int j = 0; j < ITEMS; ++j) {
-        const uint32_t e = j * THREADS + t;
-        if (e < valid) {
-            kout[e] = map_out(s_k[lds_slot<ITEMS>(e)], a.map_store);
+    it.each([&](int j) {
+        if (it.has(j)) {
+            kout[to[j]] = map_out(key[j], a.map_store);
             if constexpr (HAS_V)
-                vout[e] = s_v[lds_slot<ITEMS>(e)];
+                vout[to[j]] = val[j];
         }
-    }
+    });
 }
 
 // One merge level: runs [q 2w, q 2w + w) and [q 2w + w, q 2w + 2w) (clipped
@@ -300,16 +205,19 @@ __device__ __forceinline__ PairRuns pair_runs(uint32_t g, uint32_t w, uint32_t n
     return p;
 }
 
-// One thread per split: a binary search for the first x in [lo, hi) with
-// A[x] > B[diag - 1 - x] (hi if none), the merge-path split of merge_chains.
-// Measured on MI355X, searches with several probes per step (8 per thread,
-// or 64 per wave) fetch so many more scattered lines that they take longer
-// than this one, whose deep probes mostly hit lines shared by neighbouring
-// splits.
+// kSplitLanes lanes per split: a search with kSplitLanes probes per step for
+// the first x in [lo, hi) with A[x] > B[diag - 1 - x] (hi if none), the
+// merge-path split of merge_chains.  A step is one trip to memory, so the
+// steps are what it takes: of 2^24 32-bit pairs 11.4 us a level by halving, 7.8
+// by fifths.  With 8 or 64 probes a step the scattered lines that they fetch
+// cost more than the steps saved.  One wave per workgroup spreads those
+// fetches over the chip.
+constexpr uint32_t kSplitLanes = 4;
+
 template <typename K, int TILE>
-__global__ __launch_bounds__(256) void k_merge_split(MergeLevelArgs a)
+__global__ __launch_bounds__(kWave) void k_merge_split(MergeLevelArgs a)
 {
-    const uint32_t b = blockIdx.x * 256 + threadIdx.x;
+    const uint32_t b = (blockIdx.x * kWave + threadIdx.x) / kSplitLanes;
     if (b >= a.tiles)
         return;
     // the split at the start of output tile b (tiles never straddle a pair:
@@ -321,13 +229,21 @@ __global__ __launch_bounds__(256) void k_merge_split(MergeLevelArgs a)
     const uint32_t diag = g - p.base;
     uint32_t lo = diag > p.nb ? diag - p.nb : 0u;
     uint32_t hi = diag < p.na ? diag : p.na;
+    const uint32_t lane = threadIdx.x % kSplitLanes;
+    const auto probe = [&](uint32_t i) {  // the i-th cut of [lo, hi), in it for i <= kSplitLanes
+        return lo + (uint32_t)((uint64_t)(hi - lo) * i / (kSplitLanes + 1));
+    };
     while (lo < hi) {
-        const uint32_t mid = (lo + hi) >> 1;
-        if (A[mid] <= B[diag - 1 - mid])
-            lo = mid + 1;
-        else
-            hi = mid;
+        const uint32_t x = probe(lane + 1);
+        const uint64_t took = __ballot(A[x] <= B[diag - 1 - x]);  // a prefix of the lanes
+        const uint32_t c = __popc((uint32_t)(took >> (threadIdx.x & ~(kSplitLanes - 1))) &
+                                  ((1u << kSplitLanes) - 1));
+        const uint32_t from = c ? probe(c) + 1 : lo;
+        hi = c < kSplitLanes ? probe(c + 1) : hi;
+        lo = from;
     }
+    if (lane)
+        return;
     a.split[b] = p.base + lo;
 }
 
@@ -408,10 +324,10 @@ __global__ __launch_bounds__(THREADS) void k_merge_pass(MergeLevelArgs a)
 
 // Host-side table of the merge sort's kernels for one kind.
 struct MergeOps {
-    int tile;       // elements per tile sort
+    int max_tile;   // elements per tile sort, at most
     int pass_tile;  // outputs per merge-pass workgroup
     void (*tile_sort)(const MergeTileArgs &, uint32_t grid, hipStream_t);
-    void (*split)(const MergeLevelArgs &, uint32_t grid, hipStream_t);
+    void (*split)(const MergeLevelArgs &, hipStream_t);
     void (*pass)(const MergeLevelArgs &, uint32_t grid, hipStream_t);
 };
 

@@ -9,19 +9,20 @@ struct MergeLaunch {
     using S = MergeShape<K, HAS_V>;
     static void tile_sort(const MergeTileArgs &a, uint32_t grid, hipStream_t s)
     {
-        hipLaunchKernelGGL((k_merge_tile<K, K, HAS_V, S::kTileThreads, S::kTileItems, S::kTileChains>), dim3(grid),
+        hipLaunchKernelGGL((k_merge_tile<K, K, HAS_V, S::kTileThreads, S::kTileItems>), dim3(grid),
                            dim3(S::kTileThreads), 0, s, a);
     }
-    static void split(const MergeLevelArgs &a, uint32_t grid, hipStream_t s)
+    static void split(const MergeLevelArgs &a, hipStream_t s)
     {
-        hipLaunchKernelGGL((k_merge_split<K, S::kPassTile>), dim3(grid), dim3(256), 0, s, a);
+        hipLaunchKernelGGL((k_merge_split<K, S::kPassTile>), 
+                           dim3((a.tiles * kSplitLanes + kWave - 1) / kWave), dim3(kWave), 0, s, a);
     }
     static void pass(const MergeLevelArgs &a, uint32_t grid, hipStream_t s)
     {
         hipLaunchKernelGGL((k_merge_pass<K, K, HAS_V, S::kPassThreads, S::kPassItems, S::kPassChains>), dim3(grid),
                            dim3(S::kPassThreads), 0, s, a);
     }
-    static MergeOps ops() { return MergeOps{S::kTile, S::kPassTile, &tile_sort, &split, &pass}; }
+    static MergeOps ops() { return MergeOps{S::kMaxTile, S::kPassTile, &tile_sort, &split, &pass}; }
 };
 
 const MergeOps &merge_ops(int key_bytes, bool has_values)

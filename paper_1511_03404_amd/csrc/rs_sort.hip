@@ -743,6 +743,7 @@ static rs_status run_sort(rs_context *ctx, const K *kin, const K *vin, K *kout, 
 // scratch copy so that the last level writes the output.
 
 struct MergeLayout {
+    uint64_t tile;        // elements per tile sort
     uint64_t tiles;       // tile sorts
     uint64_t pass_tiles;  // merge-pass workgroups per level
     int levels;           // merge levels: runs double from the tile size until >= n
@@ -753,9 +754,15 @@ static MergeLayout make_merge_layout(int key_bytes, bool has_values, uint64_t n,
                                      const MergeOps &op)
 {
     MergeLayout L{};
-    L.tiles = (n + op.tile - 1) / op.tile;
+    // Tiles of 8192 while that gives every CU at most one: half as long a tile
+    // sort against one more level, whose launches take about the same (2^16
+    // 32-bit keys: 51 us by tiles of 8192, 53 by 16384; 2^20: 113 and 114), and
+    // keys that need every digit of a tile lose less (2^16: 78 and 105).
+    constexpr uint64_t kSmallTile = 8192, kCus = 256;
+    L.tile = n <= kSmallTile * kCus ? kSmallTile : op.max_tile;
+    L.tiles = (n + L.tile - 1) / L.tile;
     L.pass_tiles = (n + op.pass_tile - 1) / op.pass_tile;
-    for (uint64_t w = op.tile; w < n; w *= 2)
+    for (uint64_t w = L.tile; w < n; w *= 2)
         ++L.levels;
     uint64_t o = 0;
     L.off_split = o;
@@ -812,7 +819,8 @@ static rs_status run_merge(rs_context *ctx, const K *kin, const K *vin, K *kout,
     K *bk[2] = {kout, wb ? (K *)(wb + L.off_tmp_k) : nullptr};
     K *bv[2] = {vout, (wb && HAS_V) ? (K *)(wb + L.off_tmp_v) : nullptr};
     int cur = L.levels & 1;
-    MergeTileArgs ta{kin, vin, bk[cur], bv[cur], (uint32_t)n, kmap, L.levels == 0 ? kmap : 0u};
+    MergeTileArgs ta{kin,           vin,  bk[cur], bv[cur], (uint32_t)n, (uint32_t)L.tile, kmap,
+                     L.levels == 0 ? kmap : 0u};
     launch(ctx, s, "k_merge_tile", [&] { op.tile_sort(ta, (uint32_t)L.tiles, s); });
     uint32_t *split = wb ? (uint32_t *)(wb + L.off_split) : nullptr;
     for (int lvl = 0; lvl < L.levels; ++lvl) {
@@ -823,11 +831,10 @@ static rs_status run_merge(rs_context *ctx, const K *kin, const K *vin, K *kout,
         la.dv = bv[cur ^ 1];
         la.split = split;
         la.n = (uint32_t)n;
-        la.w = (uint32_t)op.tile << lvl;
+        la.w = (uint32_t)L.tile << lvl;
         la.tiles = (uint32_t)L.pass_tiles;
         la.map_store = lvl == L.levels - 1 ? kmap : 0u;
-        launch(ctx, s, "k_merge_split",
-               [&] { op.split(la, (uint32_t)((L.pass_tiles + 255) / 256), s); });
+        launch(ctx, s, "k_merge_split", [&] { op.split(la, s); });
         launch(ctx, s, merge_pass_name<K, HAS_V>(),
                [&] { op.pass(la, (uint32_t)L.pass_tiles, s); });
         cur ^= 1;

@@ -117,3 +117,19 @@ def test_merge_benchmark_size_certificate(rs, bits):
     ko, vo = rs.merge_sort(kd, vd)
     torch.cuda.synchronize()
     assert certify_stable_sort(keys, host(ko), host(vo)) is None
+
+
+@pytest.mark.parametrize("bits,pairs", KINDS)
+def test_merge_tile_lengths(rs, oracle_lib, bits, pairs):
+    """Tiles of 8192 up to 2^21 elements, the largest that fit above: the last size
+    of the one, and of the other a tail of one element and a ragged one."""
+    for n in (1 << 21, (1 << 21) + 1, (1 << 21) + 5 * PASS_TILE + 77):
+        for dist in ("uniform", "bucket"):
+            print(f"case merge bits={bits} pairs={pairs} n={n} {dist}", flush=True)
+            keys = datagen.keys(dist, n, bits, seed=n % 11)
+            vals = datagen.values(n, bits) if pairs else None
+            ok, ov = oracle_lib.merge_sort(keys, vals)
+            gk, gv = gpu_merge(rs, keys, vals, in_place=dist == "bucket")
+            assert np.array_equal(gk, ok), f"keys differ n={n} {dist}"
+            if pairs:
+                assert np.array_equal(gv, ov), f"values differ n={n} {dist}"
