@@ -33,10 +33,9 @@ struct FinishArgs {
 
 constexpr int kFinishThreads = 256;
 constexpr int kFinishItems = 4;
-// sorts of up to kFinishSmall elements take smaller tiles, so that every
-// compute unit has one
-constexpr int kFinishItemsSmall = 2;
-constexpr uint32_t kFinishSmall = 1u << 19;
+// sorts of up to kFinishFused elements sweep in a pass's launch
+constexpr int kFinishItemsFused = 2;
+constexpr uint32_t kFinishFused = 1u << 20;
 
 // Workgroups loop over tiles of THREADS x ITEMS elements; a tile's keys and
 // the chunk before and after it are held in LDS.  A chunk is the 64 elements
@@ -193,13 +192,10 @@ __device__ __forceinline__ void finish_tile(FinishLds<K, THREADS, ITEMS> &L, con
 }
 
 template <typename K, typename V, bool HAS_V, int THREADS, int ITEMS>
-__global__ __launch_bounds__(THREADS) void k_finish(FinishArgs a)
+__device__ __forceinline__ void finish_all(FinishLds<K, THREADS, ITEMS> &L, FinishArgs a,
+                                           uint32_t word)
 {
     constexpr uint32_t T = THREADS * ITEMS;
-    __shared__ FinishLds<K, THREADS, ITEMS> L;
-    const uint32_t word = __builtin_amdgcn_readfirstlane(a.ctrl[kCtrlFinish]);
-    if (!(word & kFinishRun))
-        return;
     const uint32_t src = (word >> kFinishSrcShift) & 3u;
     const uint32_t dst = (word >> kFinishDstShift) & 3u;
     const int shift = (int)(word >> kFinishShift);
@@ -219,6 +215,42 @@ __global__ __launch_bounds__(THREADS) void k_finish(FinishArgs a)
                                                      if (l < cap)
                                                          list[l] = i;
                                                  });
+}
+
+template <typename K, typename V, bool HAS_V, int THREADS, int ITEMS>
+__global__ __launch_bounds__(THREADS) void k_finish(FinishArgs a)
+{
+    __shared__ FinishLds<K, THREADS, ITEMS> L;
+    const uint32_t word = __builtin_amdgcn_readfirstlane(a.ctrl[kCtrlFinish]);
+    if (word & kFinishRun)
+        finish_all<K, V, HAS_V, THREADS, ITEMS>(L, a, word);
+}
+
+struct PassFinishArgs {
+    PassArgs p;
+    FinishArgs f;
+    uint32_t pass_grid;  // workgroups that the pass wants; the sweep takes all
+};
+
+// The slot before the last of a sort of up to kFinishFused elements: its
+// pass, or the sweep (a sort that sweeps has saved two passes at least, so
+// that slot's is one of them).  With a launch for each, one of the two did
+// nothing, for 2 us: 98304 64-bit pairs 47.6 -> 45.6 us, 2^15 32-bit keys of 64
+// values 45 -> 44.  The sweep's own smaller workgroups are the faster ones
+// where they fill the chip (2^22 64-bit keys 116 us, in this launch 124).
+template <typename K, typename V, bool HAS_V, typename C>
+__global__ __launch_bounds__(C::kThreads) void k_pass_finish(PassFinishArgs a)
+{
+    static_assert(!C::kWide && kFinishSaves >= 2, "8-bit digits; the slot is free when the sweep runs");
+    __shared__ union {
+        PassLds<K, C, HAS_V> pass;
+        FinishLds<K, C::kThreads, kFinishItemsFused> finish;
+    } L;
+    const uint32_t word = __builtin_amdgcn_readfirstlane(a.f.ctrl[kCtrlFinish]);
+    if (word & kFinishRun)
+        finish_all<K, V, HAS_V, C::kThreads, kFinishItemsFused>(L.finish, a.f, word);
+    else if (blockIdx.x < a.pass_grid)
+        pass_slot<K, V, HAS_V, C>(a.p, L.pass);
 }
 
 struct LastArgs {

@@ -417,7 +417,7 @@ __global__ __launch_bounds__(kRadix * 4) void k_plan(PlanArgs a)
         s_trivial[t] = 0;
         s_max[t] = 0;
     }
-    // the sampled keys and a clear table for them (8-bit digits only)
+    // the sampled keys and tables for them (8-bit digits only)
     __shared__ uint32_t s_tag[R == 8 ? kSampleTab : 1], s_tag_same[R == 8 ? kSampleTab : 1];
     __shared__ uint32_t s_repeats, s_same;
     K sample[kSampleMax] = {};
@@ -426,10 +426,6 @@ __global__ __launch_bounds__(kRadix * 4) void k_plan(PlanArgs a)
         for (uint32_t j = 0; j < kSampleMax; ++j)
             if (j * kSampleThreads + t < a.sample_count)
                 sample[j] = ((const K *)a.sample)[j * kSampleThreads + t];
-        for (uint32_t i = t; i < kSampleTab; i += kSampleThreads) {
-            s_tag[i] = 0;
-            s_tag_same[i] = 0;
-        }
         if (t == 0) {
             s_repeats = 0;
             s_same = 0;
@@ -546,6 +542,11 @@ __global__ __launch_bounds__(kRadix * 4) void k_plan(PlanArgs a)
         if (a.finish) {
             low = stop_at<D>(a.n, s_trivial, s_max, kFinishMean);
             if (low) {
+                for (uint32_t i = t; i < kSampleTab; i += kSampleThreads) {
+                    s_tag[i] = 0;
+                    s_tag_same[i] = 0;
+                }
+                __syncthreads();
                 sample_repeats<K, kSampleMax, kSampleThreads>(sample, a.sample_count, 0, s_tag_same, &s_same);
                 sample_repeats<K, kSampleMax, kSampleThreads>(sample, a.sample_count, low * R, s_tag, &s_repeats);
                 __syncthreads();

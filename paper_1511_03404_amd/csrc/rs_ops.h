@@ -22,9 +22,10 @@ struct SortOps {
     const void *pass_kernel;  // for occupancy queries
     // 8-bit digits only (null otherwise): the end of a sort whose passes stop
     // at a high digit position (rs_finish.h)
-    void (*finish)(const FinishArgs &, int items, uint32_t grid, hipStream_t);
+    void (*finish)(const FinishArgs &, uint32_t grid, hipStream_t);
+    void (*pass_finish)(const PassFinishArgs &, uint32_t grid, hipStream_t);
     void (*last)(const LastArgs &, uint32_t grid, hipStream_t);
-    const void *finish_kernel;  // the larger tile
+    const void *finish_kernel, *pass_finish_kernel;
 };
 
 struct SegOps {
@@ -61,14 +62,14 @@ struct SortLaunch {
     {
         hipLaunchKernelGGL((k_pass<K, K, HAS_V, C>), dim3(grid), dim3(THREADS), 0, s, a);
     }
-    static void finish(const FinishArgs &a, int items, uint32_t grid, hipStream_t s)
+    static void finish(const FinishArgs &a, uint32_t grid, hipStream_t s)
     {
-        if (items == kFinishItems)
-            hipLaunchKernelGGL((k_finish<K, K, HAS_V, kFinishThreads, kFinishItems>), dim3(grid),
-                               dim3(kFinishThreads), 0, s, a);
-        else
-            hipLaunchKernelGGL((k_finish<K, K, HAS_V, kFinishThreads, kFinishItemsSmall>),
-                               dim3(grid), dim3(kFinishThreads), 0, s, a);
+        hipLaunchKernelGGL((k_finish<K, K, HAS_V, kFinishThreads, kFinishItems>), dim3(grid),
+                           dim3(kFinishThreads), 0, s, a);
+    }
+    static void pass_finish(const PassFinishArgs &a, uint32_t grid, hipStream_t s)
+    {
+        hipLaunchKernelGGL((k_pass_finish<K, K, HAS_V, C>), dim3(grid), dim3(THREADS), 0, s, a);
     }
     static void last(const LastArgs &a, uint32_t grid, hipStream_t s)
     {
@@ -77,9 +78,11 @@ struct SortLaunch {
     static SortOps ops()
     {
         SortOps o{R, THREADS, ITEMS, C::kTile, num_passes<K, R>(), &hist, &plan, &pass,
-                  (const void *)k_pass<K, K, HAS_V, C>, nullptr, nullptr, nullptr};
+                  (const void *)k_pass<K, K, HAS_V, C>, nullptr, nullptr, nullptr, nullptr, nullptr};
         if constexpr (R == kRadixBits) {
             o.finish = &finish;
+            o.pass_finish = &pass_finish;
+            o.pass_finish_kernel = (const void *)k_pass_finish<K, K, HAS_V, C>;
             o.last = &last;
             o.finish_kernel = (const void *)k_finish<K, K, HAS_V, kFinishThreads, kFinishItems>;
         }

@@ -702,25 +702,36 @@ static rs_status run_sort(rs_context *ctx, const K *kin, const K *vin, K *kout, 
     pa.stall = ctx->stall;
     // the pass slots; the last one copies the input when no pass moves data,
     // or follows up on k_finish
+    // the list of long runs takes the place of the passes' look-back words
+    const uint32_t list_cap = (uint32_t)std::min<uint64_t>(n, (uint64_t)L.d * L.tiles * L.bins);
+    const FinishArgs fa{b, (uint32_t)n, ctrl, status, list_cap, kmap};
+    const bool fused = n <= kFinishFused;
     for (int p = 0; p < slots; ++p) {
         pa.pass = p;
         pa.status = status + (uint64_t)p * L.tiles * L.bins;
         pa.claims = status + (uint64_t)L.d * L.tiles * L.bins + (uint64_t)p * L.claim_words;
         pa.gagg = status + (uint64_t)L.d * (L.tiles * L.bins + L.claim_words) +
                   (uint64_t)p * L.groups * L.bins;
+        if (finish && fused && p == slots - 2) {
+            const uint32_t tile = (uint32_t)op.threads * kFinishItemsFused;
+            const uint32_t grid = (uint32_t)std::min<uint64_t>(
+                (n + tile - 1) / tile,
+                (uint64_t)resident_blocks(op.pass_finish_kernel, op.threads) * ctx_cus(ctx));
+            launch(ctx, s, "k_pass_finish",
+                   [&] { op.pass_finish({pa, fa, pass_grid}, std::max(grid, pass_grid), s); });
+            continue;
+        }
         if (!finish || p < slots - 1) {
             launch(ctx, s, pass_name<K, HAS_V>(), [&] { op.pass(pa, pass_grid, s); });
             continue;
         }
-        // the list of long runs takes the place of the passes' look-back words
-        const uint32_t list_cap =
-            (uint32_t)std::min<uint64_t>(n, (uint64_t)L.d * L.tiles * L.bins);
-        FinishArgs fa{b, (uint32_t)n, ctrl, status, list_cap, kmap};
-        const int items = n <= kFinishSmall ? kFinishItemsSmall : kFinishItems;
-        const uint32_t fgrid = (uint32_t)std::min<uint64_t>(
-            (n + kFinishThreads * items - 1) / (kFinishThreads * items),
-            (uint64_t)resident_blocks(op.finish_kernel, kFinishThreads) * ctx_cus(ctx));
-        launch(ctx, s, "k_finish", [&] { op.finish(fa, items, fgrid, s); });
+        if (!fused) {
+            const uint32_t tile = kFinishThreads * kFinishItems;
+            const uint32_t grid = (uint32_t)std::min<uint64_t>(
+                (n + tile - 1) / tile,
+                (uint64_t)resident_blocks(op.finish_kernel, kFinishThreads) * ctx_cus(ctx));
+            launch(ctx, s, "k_finish", [&] { op.finish(fa, grid, s); });
+        }
         LastArgs la{pa, status, (uint32_t)L.d, status, list_cap};
         launch(ctx, s, "k_last", [&] { op.last(la, pass_grid, s); });
     }
