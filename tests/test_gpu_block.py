@@ -94,3 +94,22 @@ def test_segments(rs, oracle_lib, bits, pairs, order, descending, tiny_cap):
     if pairs:
         assert np.array_equal(vo.cpu().numpy(), ov)
     ctx.close()
+
+
+@pytest.mark.parametrize("bits,pairs", KINDS)
+def test_batches_of_one_class(rs, oracle_lib, bits, pairs):
+    """Batches whose total is at the edge of a size class, as one segment and
+    cut in two: the launches of the longer classes are left out."""
+    for total in (1, 1024, 1025, 4096, 4097, 8192, 8193, 16384, 16385):
+        for cut in (0, total // 3):
+            print(f"case bits={bits} pairs={pairs} total={total} cut={cut}", flush=True)
+            keys = make("uniform", total, bits, seed=total % 17)
+            vals = datagen.values(total, bits) if pairs else None
+            off = np.array([0, cut, total], dtype=np.uint64)
+            ko, vo = rs.segmented_sort(dev(keys), dev(vals) if pairs else None,
+                                       dev(off.view(np.int64)))
+            ok, ov = oracle_lib.segmented_sort_ordered(keys, vals, off, order="unsigned",
+                                                       descending=False)
+            assert np.array_equal(ko.cpu().numpy(), ok)
+            if pairs:
+                assert np.array_equal(vo.cpu().numpy(), ov)
