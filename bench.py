@@ -46,6 +46,9 @@ ROOT = os.path.dirname(os.path.abspath(__file__))
 # on other sources are stale
 KERNEL_SOURCES = ("paper_1511_03404_amd/csrc/rs_kernels.h", "paper_1511_03404_amd/csrc/rs_device.h")
 MERGE_SOURCES = ("paper_1511_03404_amd/csrc/rs_merge.h", "paper_1511_03404_amd/csrc/rs_device.h")
+# words of the control block at the start of a workspace (csrc/rs_device.h)
+CTRL_FINISH, CTRL_SLOTS = 49, 55
+SEG_PASS_MASK = 49
 TRAFFIC_FILE = os.path.join(ROOT, "profiles", "traffic.json")
 
 
@@ -518,7 +521,11 @@ def measure_segmented(args, torch, rs, datagen, dev, with_cpu=True, quick=False)
         del bk, bv
 
     large = sizes[sizes > 16384]
-    pass_ms = kern.get("k_seg_pass_u32", [])
+    cfg_passes = -(-32 // cfg["radix_bits"])
+    # the launches of passes in which a segment moves (the rest end at once)
+    active = int(ws[:256].cpu().numpy().view(np.uint32)[SEG_PASS_MASK]) & 0xFFFF
+    pass_ms = [ms for j, ms in enumerate(kern.get("k_seg_pass_u32", []))
+               if active >> (j % cfg_passes) & 1]
     roofline = None
     if pass_ms:
         avg = sum(pass_ms) / len(pass_ms)
@@ -528,6 +535,7 @@ def measure_segmented(args, torch, rs, datagen, dev, with_cpu=True, quick=False)
                     "unit": "GB/s", "frac": round(achieved / HBM_PEAK_GBS, 4), "traffic": None,
                     "kernel": "k_seg_pass_u32", "avg_launch_ms": round(avg, 5),
                     "launches": len(pass_ms), "bytes_per_launch": bpl,
+                    "passes_active": bin(active).count("1"),
                     "elements_in_large_segments": int(large.sum())}
     tiny = sizes[(sizes > 1) & (sizes <= tiny_cap)]
     tiny_ms = kern.get("k_seg_bitonic", [])
@@ -694,8 +702,11 @@ def bench_merge(args, torch, rs, datagen, dev):
                                        f"{'512, 4' if bits == 64 else '256, 8'}, 1>",
                     "avg_launch_ms": round(avg, 5), "launches": len(pass_ms),
                     "bytes_per_launch": bytes_per_launch, "input": dists[ref]}
+    # as the library: tiles of 8192 up to 2^21 elements, above that 16384
+    # (8192 for 64-bit pairs)
+    tile = 8192 if n <= 1 << 21 or (bits == 64 and has_v) else 16384
     levels = 0
-    while (8192 << levels) < n:
+    while (tile << levels) < n:
         levels += 1
     if roofline is not None:
         roofline["traffic"] = measured_traffic("merge_" + args.merge_kind, None)
@@ -706,7 +717,7 @@ def bench_merge(args, torch, rs, datagen, dev):
         "ms_per_step": round(elapsed / args.steps * 1e3, 4), "higher_is_better": True,
         "scaling": "weak", "vs_baseline": None, "dtype": f"u{bits}", "data": "synthetic",
         "config": {"workload": f"merge sort of {wdesc}; one sort per distribution per step "
-                               f"({', '.join(dists)}); MT19937 seed 1; tiles of 8192 sorted "
+                               f"({', '.join(dists)}); MT19937 seed 1; tiles of {tile} sorted "
                                f"in LDS, then {levels} merge levels of 2048-output workgroups",
                    "n": n, "key_bits": bits, "value_bits": bits if has_v else 0,
                    "distributions": dists, "merge_levels": levels},
@@ -960,6 +971,22 @@ def measure_sorts(args, torch, rs, datagen, dev, workload, steps, warmup, with_c
     keys_total = n * len(dists) * steps
     value = keys_total / elapsed / 1e6
 
+    # the passes and sweeps that each input's sort ran, from the control block
+    # that it leaves in the workspace: passes stop at a high digit where one
+    # sweep can order the rest, and those after it are launched but move nothing
+    ran = {}
+    for i, d in enumerate(dists):
+        _, k, v = ins[i]
+        if has_v:
+            rs.sort_pairs(k, v, ko, vo, ctx=ctx, workspace=ws)
+        else:
+            rs.sort_keys(k, ko, ctx=ctx, workspace=ws)
+        if n > rs.BLOCK_SORT_CAP[bits, has_v]:
+            words = ws[:256].cpu().numpy().view(np.uint32)
+            ran[d] = int(words[CTRL_SLOTS]), int(words[CTRL_FINISH] & 1)
+        else:
+            ran[d] = moving[d], 0
+
     # per-distribution times from the events (sum of the kernels of one sort)
     per = {}
     for i, d in enumerate(dists):
@@ -969,13 +996,14 @@ def measure_sorts(args, torch, rs, datagen, dev, workload, steps, warmup, with_c
         per_launch = len(mine) // steps
         sorts = [sum(mine[j * per_launch:(j + 1) * per_launch]) for j in range(steps)]
         b_alg = kb * 2 * n * (kb + vb)  # P8 passes x 2 x n x (k + v)
-        # bytes the executed passes move (a copy when every pass is skipped)
-        b_exec = max(moving[d], 1) * 2 * n * (kb + vb)
+        # bytes the passes and the sweep that ran move (a copy when none did)
+        b_exec = max(sum(ran[d]), 1) * 2 * n * (kb + vb)
         per[d] = {"ms_per_sort": round(sort_ms, 4),
                   "ms_per_sort_median": round(statistics.median(sorts), 4),
                   "Mkeys_s": round(n / sort_ms / 1e3, 1),
                   "hbm_frac_alg": round(b_alg / (sort_ms * 1e-3) / (HBM_PEAK_GBS * 1e9), 4),
                   "passes_moving": moving[d],
+                  "passes_run": ran[d][0], "sweeps_run": ran[d][1],
                   "bytes_executed": b_exec,
                   "hbm_frac_executed": round(b_exec / (sort_ms * 1e-3) / (HBM_PEAK_GBS * 1e9), 4)}
         kern = {}
@@ -985,10 +1013,13 @@ def measure_sorts(args, torch, rs, datagen, dev, workload, steps, warmup, with_c
         per[d]["kernels_ms"] = {k: round(sum(v) / steps, 4) for k, v in kern.items()}
 
     # roofline of the dominant kernel: the digit pass, on the input where
-    # every pass moves data (uniform), per launch
+    # every digit differs (uniform), per launch that moves data (a sort's
+    # moving passes are its first)
     pass_name = f"k_pass_u{bits}_{'pairs' if has_v else 'keys'}"
     ref = dists.index("uniform") if "uniform" in dists else 0
     pass_ms = [ms for name, tag, ms in recs if tag == ref and name == pass_name]
+    slots = max(1, len(pass_ms) // steps)
+    pass_ms = [ms for j, ms in enumerate(pass_ms) if j % slots < ran[dists[ref]][0]]
     roofline = None
     if pass_ms:
         avg = sum(pass_ms) / len(pass_ms)

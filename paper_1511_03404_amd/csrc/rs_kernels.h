@@ -14,7 +14,8 @@
 //              and is skipped) and which buffer each pass reads and writes
 //   k_pass     one per digit position: a single sweep over the data that
 //              counts, scans (decoupled look-back across tiles) and places
-//              each tile; see rs_device.h.
+//              each tile; see rs_device.h.  With 8-bit digits the plan may
+//              leave the low digits to rs_finish.h.
 //   k_seg_hist / k_seg_scan / k_seg_pass
 //              the same for the large segments of a segmented sort, every
 //              segment with its own histograms and look-back chain.

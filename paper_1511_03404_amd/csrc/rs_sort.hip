@@ -9,7 +9,9 @@
 //               k_hist adds into one histogram; small sorts skip it)
 //   k_hist      all digit histograms in one read; clears the look-back words
 //   k_plan      digit_base scans, skipped passes, buffer ping-pong
-//   k_pass x d  one sweep per digit
+//   k_pass x d  one sweep per digit; where the plan may leave the low digits,
+//               the last launch is k_last, and k_finish comes before it (up to
+//               2^20 elements k_pass_finish is the launch before the last)
 //   k_finalize  in-place sorts with an odd number of moving passes only
 //
 // Everything after argument validation is enqueued on the caller's stream
