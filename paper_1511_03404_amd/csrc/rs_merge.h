@@ -205,19 +205,21 @@ __device__ __forceinline__ PairRuns pair_runs(uint32_t g, uint32_t w, uint32_t n
     return p;
 }
 
-// kSplitLanes lanes per split: a search with kSplitLanes probes per step for
-// the first x in [lo, hi) with A[x] > B[diag - 1 - x] (hi if none), the
-// merge-path split of merge_chains.  A step is one trip to memory, so the
-// steps are what it takes: of 2^24 32-bit pairs 11.4 us a level by halving, 7.8
-// by fifths.  With 8 or 64 probes a step the scattered lines that they fetch
-// cost more than the steps saved.  One wave per workgroup spreads those
-// fetches over the chip.
+// LANES lanes per split: a search with LANES probes per step for the first x in
+// [lo, hi) with A[x] > B[diag - 1 - x] (hi if none), the merge-path split of
+// merge_chains.  A step is one trip to memory, so for few splits the steps are
+// what it takes: of 2^24 32-bit pairs 11.4 us a level by halving, 7.8 by fifths
+// (2^20 keys in all 130 -> 117).  With more splits the scattered lines that the
+// probes fetch cost more than the steps saved: 2^26 keys 2608 us by halving,
+// 2697 by fifths, and so do 8 or 64 probes a step at any size.  One wave per
+// workgroup spreads the fetches over the chip.
 constexpr uint32_t kSplitLanes = 4;
+constexpr uint32_t kSplitTiles = 8192;  // at most, for kSplitLanes
 
-template <typename K, int TILE>
+template <typename K, int TILE, uint32_t LANES>
 __global__ __launch_bounds__(kWave) void k_merge_split(MergeLevelArgs a)
 {
-    const uint32_t b = (blockIdx.x * kWave + threadIdx.x) / kSplitLanes;
+    const uint32_t b = (blockIdx.x * kWave + threadIdx.x) / LANES;
     if (b >= a.tiles)
         return;
     // the split at the start of output tile b (tiles never straddle a pair:
@@ -229,17 +231,17 @@ __global__ __launch_bounds__(kWave) void k_merge_split(MergeLevelArgs a)
     const uint32_t diag = g - p.base;
     uint32_t lo = diag > p.nb ? diag - p.nb : 0u;
     uint32_t hi = diag < p.na ? diag : p.na;
-    const uint32_t lane = threadIdx.x % kSplitLanes;
-    const auto probe = [&](uint32_t i) {  // the i-th cut of [lo, hi), in it for i <= kSplitLanes
-        return lo + (uint32_t)((uint64_t)(hi - lo) * i / (kSplitLanes + 1));
+    const uint32_t lane = threadIdx.x % LANES;
+    const auto probe = [&](uint32_t i) {  // the i-th cut of [lo, hi), in it for i <= LANES
+        return lo + (uint32_t)((uint64_t)(hi - lo) * i / (LANES + 1));
     };
     while (lo < hi) {
         const uint32_t x = probe(lane + 1);
         const uint64_t took = __ballot(A[x] <= B[diag - 1 - x]);  // a prefix of the lanes
-        const uint32_t c = __popc((uint32_t)(took >> (threadIdx.x & ~(kSplitLanes - 1))) &
-                                  ((1u << kSplitLanes) - 1));
+        const uint32_t c = __popc((uint32_t)(took >> (threadIdx.x & ~(LANES - 1))) &
+                                  ((1u << LANES) - 1));
         const uint32_t from = c ? probe(c) + 1 : lo;
-        hi = c < kSplitLanes ? probe(c + 1) : hi;
+        hi = c < LANES ? probe(c + 1) : hi;
         lo = from;
     }
     if (lane)

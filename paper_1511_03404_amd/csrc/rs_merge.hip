@@ -14,8 +14,13 @@ struct MergeLaunch {
     }
     static void split(const MergeLevelArgs &a, hipStream_t s)
     {
-        hipLaunchKernelGGL((k_merge_split<K, S::kPassTile>), 
-                           dim3((a.tiles * kSplitLanes + kWave - 1) / kWave), dim3(kWave), 0, s, a);
+        if (a.tiles <= kSplitTiles)
+            hipLaunchKernelGGL((k_merge_split<K, S::kPassTile, kSplitLanes>),
+                               dim3((a.tiles * kSplitLanes + kWave - 1) / kWave), dim3(kWave), 0, s,
+                               a);
+        else
+            hipLaunchKernelGGL((k_merge_split<K, S::kPassTile, 1>),
+                               dim3((a.tiles + kWave - 1) / kWave), dim3(kWave), 0, s, a);
     }
     static void pass(const MergeLevelArgs &a, uint32_t grid, hipStream_t s)
     {
