@@ -48,7 +48,7 @@ KERNEL_SOURCES = ("paper_1511_03404_amd/csrc/rs_kernels.h", "paper_1511_03404_am
 MERGE_SOURCES = ("paper_1511_03404_amd/csrc/rs_merge.h", "paper_1511_03404_amd/csrc/rs_device.h")
 # words of the control block at the start of a workspace (csrc/rs_device.h)
 CTRL_FINISH, CTRL_SLOTS = 49, 55
-SEG_PASS_MASK = 49
+SEG_LARGE = 2  # segmented: number of large segments
 TRAFFIC_FILE = os.path.join(ROOT, "profiles", "traffic.json")
 
 
@@ -102,6 +102,8 @@ def summarize_pmc(root):
     def mean(path, prefix):
         v = [float(r["Counter_Value"]) for r in csv.DictReader(open(path))
              if r["Kernel_Name"].startswith(prefix)]
+        # without the launches of passes that move nothing
+        v = [x for x in v if x > max(v) / 2]
         return (sum(v) / len(v), len(v)) if v else (None, 0)
 
     cf, _ = mean(os.path.join(root, "copy", "FETCH_SIZE", "run_counter_collection.csv"),
@@ -521,21 +523,22 @@ def measure_segmented(args, torch, rs, datagen, dev, with_cpu=True, quick=False)
         del bk, bv
 
     large = sizes[sizes > 16384]
-    cfg_passes = -(-32 // cfg["radix_bits"])
-    # the launches of passes in which a segment moves (the rest end at once)
-    active = int(ws[:256].cpu().numpy().view(np.uint32)[SEG_PASS_MASK]) & 0xFFFF
+    # the elements that each pass moved, from the large segments' records and
+    # plans in the workspace (each segment has its own: csrc/rs_segmented.h)
+    moved = segment_moves(ws, S, cfg["radix_bits"])
     pass_ms = [ms for j, ms in enumerate(kern.get("k_seg_pass_u32", []))
-               if active >> (j % cfg_passes) & 1]
+               if moved[j % len(moved)]]
     roofline = None
     if pass_ms:
         avg = sum(pass_ms) / len(pass_ms)
-        bpl = 2 * int(large.sum()) * 8
+        # per launch that moves anything, on average
+        bpl = 2 * sum(moved) * 8 // sum(m > 0 for m in moved)
         achieved = bpl / (avg * 1e-3) / 1e9
         roofline = {"bound": "hbm", "achieved": round(achieved, 1), "peak": HBM_PEAK_GBS,
                     "unit": "GB/s", "frac": round(achieved / HBM_PEAK_GBS, 4), "traffic": None,
                     "kernel": "k_seg_pass_u32", "avg_launch_ms": round(avg, 5),
                     "launches": len(pass_ms), "bytes_per_launch": bpl,
-                    "passes_active": bin(active).count("1"),
+                    "elements_moved_by_pass": moved,
                     "elements_in_large_segments": int(large.sum())}
     tiny = sizes[(sizes > 1) & (sizes <= tiny_cap)]
     tiny_ms = kern.get("k_seg_bitonic", [])
@@ -594,6 +597,21 @@ def measure_segmented(args, torch, rs, datagen, dev, with_cpu=True, quick=False)
     if with_cpu:
         out["cpu_baseline"] = segmented_cpu_baseline(keys, vals, off, S, quick)
     return out
+
+
+def segment_moves(ws, nseg, r):
+    """Elements of the large segments that each digit pass of the batched sort
+    of 32-bit keys in workspace `ws` moved."""
+    def up(x):
+        return -(-x // 256) * 256
+    d = -(-32 // r)
+    large = 256 + 3 * up(16 * nseg)              # after the three shorter classes' lists
+    flags = large + up(16 * nseg) + up(nseg * d * (4 << r))
+    n = int(ws[:256].cpu().numpy().view(np.uint32)[SEG_LARGE])
+    size = ws[large:large + 16 * n].cpu().numpy().view(np.uint32).reshape(n, 4)[:, 2]
+    f = ws[flags:flags + 4 * n].cpu().numpy().view(np.uint32)
+    low = (f >> 8) & 15 if r == 8 else 0
+    return [int(size[((f >> p & 1) == 0) & (p >= low)].sum(dtype=np.int64)) for p in range(d)]
 
 
 def segmented_cpu_baseline(keys, vals, off, S, quick):
