@@ -910,8 +910,13 @@ static SegLayout make_seg_layout(int key_bytes, bool has_values, uint64_t total,
     o = align_up(o + (uint64_t)nseg * 4, 256);
     L.off_tile_seg = o;
     o = align_up(o + L.max_tiles * 4, 256);
-    L.max_chunks = total / seg_chunk(total) + nseg + 1;
+    // The chunk map: where the batch's chunks are smaller than the largest, and
+    // so more than this region holds, it lies in the scratch copy of the keys,
+    // which the first pass overwrites once the map has been used.  So the size
+    // stays what it was with large chunks only, which programs may have
+    // stored, and with narrow digits too a larger batch needs no less.
     L.off_chunk_seg = o;
+    L.max_chunks = total / kSegChunkMax + nseg + 1;
     o = align_up(o + L.max_chunks * 4, 256);
     // zeroed region: look-back words, claim counters, segment histograms
     L.off_status = o;
@@ -920,6 +925,12 @@ static SegLayout make_seg_layout(int key_bytes, bool has_values, uint64_t total,
     L.status_bytes += align_up((uint64_t)nseg * L.d * L.bins * 4, 16);
     o = align_up(o + L.status_bytes, 256);
     L.off_tmp_k = o;
+    if (seg_chunk(total) != kSegChunkMax) {
+        // room for every chunk of segments that do not overlap: each large one
+        // has more elements than 8192, and a chunk 2^14 but for its last
+        L.off_chunk_seg = L.off_tmp_k;
+        L.max_chunks = total * key_bytes / 4;
+    }
     o = align_up(o + total * key_bytes, 256);
     L.off_tmp_v = o;
     o = align_up(o + (has_values ? total * key_bytes : 0), 256);
@@ -1064,7 +1075,8 @@ static rs_status run_segmented(rs_context *ctx, const void *kin, const void *vin
     {
         SegHistArgs ha{kin,      large,    chunk_seg, (uint32_t)L.max_chunks, seg_chunk(total),
                        ctrl,     seg_hist, seg_base,  seg_flags,              kmap};
-        const uint32_t g = std::min<uint64_t>(grid_of(op.hist_kernel, kSegHistThreads), L.max_chunks);
+        const uint32_t g = std::min<uint64_t>(grid_of(op.hist_kernel, kSegHistThreads),
+                                              total / seg_chunk(total) + nseg + 1);
         launch(ctx, s, "k_seg_hist", [&] { op.hist(ha, g, s); });
         const uint32_t gs = std::min<uint32_t>(grid_of(op.scan_kernel, 256), nseg);
         launch(ctx, s, "k_seg_scan", [&] { op.scan(ha, gs, s); });
