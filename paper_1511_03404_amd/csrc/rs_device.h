@@ -44,21 +44,16 @@ constexpr uint32_t kCountMask = (1u << 30) - 1;
 // Control block (u32 words at the start of the workspace).
 constexpr int kCtrlTileCounter = 0;  // [0, 16): dynamic tile id per pass slot
 constexpr int kCtrlPlan = 16;        // [16, 32): plan word per pass slot
-constexpr int kCtrlStageDone = 32;   // [32, 48): tiles done per stage of k_last
 constexpr int kCtrlFinal = 48;       // final copy: 0 none, 1 tmp -> out
 constexpr int kCtrlFinish = 49;      // run finish word (kFinish*), 0: none
-constexpr int kCtrlUnsorted = 50;    // a long run is out of order: k_last has work
-constexpr int kCtrlLongLen = 51;     // long runs listed by k_finish
-constexpr int kCtrlGiant = 52;       // an unsorted run is too long for one workgroup
+constexpr int kCtrlUnsorted = 50;    // places where long runs are out of order, as listed by
+                                     // k_finish: without any k_last has no work
+constexpr int kCtrlLongLen = 51;     // long runs met by k_finish, in order or not
+constexpr int kCtrlGiant = 52;       // an unsorted run is longer than a tile
 constexpr int kCtrlDigits = 53;      // bit p: digit position p moves data
 constexpr int kCtrlSkew = 54;        // bit p: digit position p is skewed
 constexpr int kCtrlSlots = 55;       // pass slots in use
-constexpr int kCtrlRestClaim = 57;   // work claims of k_last: (stage, tile) items,
-constexpr int kCtrlLongClaim = 58;   // long runs,
-constexpr int kCtrlLongDone = 59;    // and long runs finished;
-constexpr int kCtrlLongerLen = 60;   // those too long for a wave: listed,
-constexpr int kCtrlLongerClaim = 61; // claimed
-constexpr int kCtrlLongerDone = 62;  // and finished
+constexpr int kCtrlLongerLen = 60;   // unsorted runs too long for a wave
 constexpr int kCtrlWords = 64;
 
 // Run finish word: the array is sorted by its bits from kFinishShift up; the

@@ -8,13 +8,13 @@
 //
 //   k_finish   one sweep over the array: every element of a run of up to 64
 //              counts the run's elements that go before it and is written to
-//              that place; a longer run is copied and, if it is out of order
-//              anywhere, reported;
+//              that place; a longer run is copied and, where it is out of
+//              order, reported;
 //   k_last     the last pass slot.  After a sweep that slot is free, and it
-//              does what the sweep could not, normally nothing: long runs
-//              out of order are sorted by a wave or a workgroup each, and if
-//              one is longer than a tile (or there are too many) the whole
-//              array is sorted again by every digit.
+//              does what the sweep could not, normally nothing: the reported
+//              runs are sorted by a wave or a workgroup each, and if one is
+//              longer than a tile (or there are too many) the whole array is
+//              sorted again by every digit.
 #pragma once
 
 #include "rs_kernels.h"
@@ -22,12 +22,48 @@
 
 namespace rs {
 
+// What the sweep reports and the follow-up works on, in the look-back words of
+// the passes, which are done by then (rest_area).
+struct RestArea {
+    uint32_t *rows;   // look-back words [row][256] of a sort again
+    uint4 *runs;      // runs to sort: start, length, segment, unused; from the
+                      // front those for a wave, from the end the longer ones
+    uint2 *list;      // where runs are out of order: element, segment
+    uint32_t cap;     // entries of each
+    uint32_t *words;  // counters (kRest*), then a bit for every 64 elements: the
+                      // run that starts among them has been taken
+    uint32_t num_words;  // (cleared by the sweep)
+};
+constexpr int kRestFindClaim = 0;   // entries of list claimed
+constexpr int kRestFindDone = 1;    // and looked up;
+constexpr int kRestShortLen = 2;    // runs for a wave: listed,
+constexpr int kRestShortClaim = 3;  // and claimed;
+constexpr int kRestLongerClaim = 4; // longer runs claimed
+constexpr int kRestItemClaim = 5;   // (stage, tile) items claimed
+constexpr int kRestStageDone = 8;   // [8, 24): items done per stage
+constexpr int kRestTaken = 32;
+
+// Lays the area out over the look-back words of `tiles` tiles, 256 a tile for
+// each of four or eight digits.  A tile holds at most 24576 elements, so the
+// bits take 12 words a tile, and with 512 for the rows and 6 for each of 64
+// runs four digits' words hold it all.
+inline RestArea rest_area(uint32_t *look_back, uint64_t tiles, uint64_t elements)
+{
+    RestArea a;
+    a.rows = look_back;
+    a.cap = (uint32_t)std::min<uint64_t>(64 * tiles, 0xFFFFFFFFu);
+    a.runs = (uint4 *)(a.rows + 2 * tiles * kRadix);
+    a.list = (uint2 *)(a.runs + a.cap);
+    a.words = (uint32_t *)(a.list + a.cap);
+    a.num_words = kRestTaken + (uint32_t)(elements / (32 * kWave)) + 1;
+    return a;
+}
+
 struct FinishArgs {
     Bufs b;
     uint32_t n;
     uint32_t *ctrl;
-    uint32_t *list;     // starts of the runs longer than kRunMax
-    uint32_t list_cap;
+    RestArea rest;
     uint32_t kmap;      // key order undone when the sweep writes the output
 };
 
@@ -57,16 +93,73 @@ struct FinishLds {
     // chunks before and after the tile.  The same for the words of adjacent
     // elements out of order.
     uint64_t head[2 * W + 2], inv[2 * W + 2];
+    uint32_t longs;    // longer runs met
+    uint32_t pending;  // places reported; the first ones wait here
+    uint2 pend[kWave];
 };
 
+// The workgroup's part in clearing the follow-up's counters, and the start of
+// its own (the first tile's barriers come before their use).
+template <typename K, int THREADS, int ITEMS>
+__device__ __forceinline__ void finish_begin(FinishLds<K, THREADS, ITEMS> &L, const RestArea &rest)
+{
+    if (threadIdx.x == 0) {
+        L.longs = 0;
+        L.pending = 0;
+    }
+    for (uint32_t i = blockIdx.x * THREADS + threadIdx.x; i < rest.num_words;
+         i += gridDim.x * THREADS)
+        rest.words[i] = 0;
+}
+
+// Reports that element i of segment seg is smaller than the one before it, in
+// a run that is too long to be ordered here.  Reports wait in LDS for the
+// workgroup's end: atomics on one word end one after another, 14 ns apart
+// (2^25 64-bit keys, 100 of each: with an atomic for each of 335,000 long runs
+// the sweep took 5 ms).
+template <typename K, int THREADS, int ITEMS>
+__device__ __forceinline__ void finish_report(FinishLds<K, THREADS, ITEMS> &L, uint32_t *ctrl,
+                                              const RestArea &rest, uint32_t i, uint32_t seg)
+{
+    const uint32_t slot = atomicAdd(&L.pending, 1u);
+    if (slot < (uint32_t)kWave) {
+        L.pend[slot] = make_uint2(i, seg);
+    } else {
+        const uint32_t l = atomicAdd(&ctrl[kCtrlUnsorted], 1u);
+        if (l < rest.cap)
+            rest.list[l] = make_uint2(i, seg);
+    }
+}
+
+// After the last tile's barrier.
+template <typename K, int THREADS, int ITEMS>
+__device__ __forceinline__ void finish_end(FinishLds<K, THREADS, ITEMS> &L, uint32_t *ctrl,
+                                           const RestArea &rest)
+{
+    __syncthreads();  // there may have been no tile
+    const uint32_t t = threadIdx.x;
+    if (t >= (uint32_t)kWave)
+        return;
+    const uint32_t count = min(L.pending, (uint32_t)kWave);
+    if (count) {
+        uint32_t l = 0;
+        if (t == 0)
+            l = atomicAdd(&ctrl[kCtrlUnsorted], count);
+        l = __builtin_amdgcn_readfirstlane(l) + t;
+        if (t < count && l < rest.cap)
+            rest.list[l] = L.pend[t];
+    }
+    if (t == 0 && L.longs)
+        atomicAdd(&ctrl[kCtrlLongLen], L.longs);
+}
+
 // The tile of an array of n elements that starts at tb: from sk, sv to dk,
-// dv, every short run in order.  *unsorted is set if a longer one is not in
-// order; list_run(i) is called for every longer run, which starts at i.
-template <typename K, typename V, bool HAS_V, int THREADS, int ITEMS, typename List>
+// dv, every short run in order.  report(i) is called where a longer run is out
+// of order, at one place at least of every such run.
+template <typename K, typename V, bool HAS_V, int THREADS, int ITEMS, typename Report>
 __device__ __forceinline__ void finish_tile(FinishLds<K, THREADS, ITEMS> &L, const K *sk,
                                             const V *sv, K *dk, V *dv, uint32_t n, uint32_t tb,
-                                            int shift, uint32_t map, uint32_t *unsorted,
-                                            List &&list_run)
+                                            int shift, uint32_t map, Report &&report)
 {
     constexpr uint32_t T = THREADS * ITEMS;
     constexpr uint32_t H = kWave;
@@ -162,17 +255,27 @@ __device__ __forceinline__ void finish_tile(FinishLds<K, THREADS, ITEMS> &L, con
     for (int j = 0; j < ITEMS; ++j) {
         const uint32_t e = e0 + j * kWave;
         const uint32_t at = H + e;  // this element's LDS slot
-        uint32_t pos = tb + e;
+        const uint32_t pos0 = tb + e;
+        uint32_t pos = pos0;
         const uint64_t here = head[j + 1], prev = head[j], next = head[j + 2];
         // nothing adjacent out of order in the three chunks: in place
         if ((inv[j] | inv[j + 1] | inv[j + 2]) != 0) {
             bool whole;
             pos += (uint32_t)run_move(s_k, at, key[j], lane, here, prev, next, &whole);
-            if (!whole) {
-                const bool in_run =
-                    (lane < kWave - 1 ? (here >> (lane + 1)) & 1ull : next & 1ull) == 0;
-                if (in_run && key[j] > s_k[at + 1])
-                    __hip_atomic_store(unsorted, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            // elements of longer runs below the one before them: in the run
+            // that comes in from the chunk before, unless that chunk has seen
+            // one in it too, and in the one that goes on into the next
+            const uint64_t low = inv[j + 1] & __ballot(!whole);
+            if (low) {
+                const uint64_t in = here ? (here & (0 - here)) - 1 : ~0ull;
+                const uint64_t tail = prev ? ~0ull << (kWave - 1 - __builtin_clzll(prev)) : ~0ull;
+                const uint64_t first = inv[j] & tail ? 0ull : low & in, last = low & ~in;
+                if (lane == 0) {
+                    if (first)
+                        report(pos0 + (uint32_t)__builtin_ctzll(first));
+                    if (last)
+                        report(pos0 + (uint32_t)__builtin_ctzll(last));
+                }
             }
         }
         if (pos < n && (full || tb + e < n)) {
@@ -180,13 +283,11 @@ __device__ __forceinline__ void finish_tile(FinishLds<K, THREADS, ITEMS> &L, con
             if constexpr (HAS_V)
                 store_at(dv, pos, val[j]);
         }
-        // the starts of the runs that are too long, in order or not
+        // runs that are too long, in order or not
         const uint32_t ends = here ? __builtin_clzll(here) : 0;
-        if (here && ends + (next ? __builtin_ctzll(next) : kWave) >= kRunMax) {
-            const uint32_t i = tb + e;
-            if (lane == kWave - 1 - ends && i < n)
-                list_run(i);
-        }
+        if (here && ends + (next ? __builtin_ctzll(next) : kWave) >= kRunMax &&
+            lane == kWave - 1 - ends && pos0 < n)
+            atomicAdd(&L.longs, 1u);
     }
     __syncthreads();  // the next tile overwrites the LDS
 }
@@ -204,17 +305,13 @@ __device__ __forceinline__ void finish_all(FinishLds<K, THREADS, ITEMS> &L, Fini
     const V *sv = HAS_V ? pick<const V>(a.b, src, true) : nullptr;
     K *dk = pick<K>(a.b, dst, false);
     V *dv = HAS_V ? pick<V>(a.b, dst, true) : nullptr;
-    uint32_t *ctrl = a.ctrl, *list = a.list;
-    const uint32_t cap = a.list_cap;
+    finish_begin(L, a.rest);
     const uint32_t tiles = (a.n + T - 1) / T;
     for (uint32_t tile = blockIdx.x; tile < tiles; tile += gridDim.x)
-        finish_tile<K, V, HAS_V, THREADS, ITEMS>(L, sk, sv, dk, dv, a.n, tile * T, shift, map,
-                                                 &ctrl[kCtrlUnsorted], [=](uint32_t i) {
-                                                     const uint32_t l =
-                                                         atomicAdd(&ctrl[kCtrlLongLen], 1u);
-                                                     if (l < cap)
-                                                         list[l] = i;
-                                                 });
+        finish_tile<K, V, HAS_V, THREADS, ITEMS>(
+            L, sk, sv, dk, dv, a.n, tile * T, shift, map,
+            [&](uint32_t i) { finish_report(L, a.ctrl, a.rest, i, 0); });
+    finish_end(L, a.ctrl, a.rest);
 }
 
 template <typename K, typename V, bool HAS_V, int THREADS, int ITEMS>
@@ -254,16 +351,9 @@ __global__ __launch_bounds__(C::kThreads) void k_pass_finish(PassFinishArgs a)
 }
 
 struct LastArgs {
-    PassArgs p;        // of the last slot
-    uint32_t *status;  // look-back words of every slot
-    uint32_t d;        // digit positions (and sets of look-back words)
-    uint32_t *list;    // k_finish's long runs
-    uint32_t list_cap;
+    PassArgs p;  // of the last slot
+    RestArea rest;
 };
-
-// Runs too long for a workgroup are checked for order over this many tiles;
-// one that is longer still counts as out of order.
-constexpr uint32_t kRestScanTiles = 32;
 
 // Waits until *word >= want; bounded like every wait on other workgroups.
 // Called by one thread; false when the bound was reached.
@@ -295,30 +385,87 @@ __device__ __forceinline__ bool hand_on_and_wait(uint32_t *done, uint32_t add, u
     return wait_count(done, want, a);
 }
 
-// A listed run: its first element, the elements from there to the end of its
-// array, the bits from `shift` up that its elements share, the digit
-// positions below that move data, and the key order of the stored keys.
+// An array with runs to sort (the plain sort's, or a large segment): where it
+// lies, its length, the bits from `shift` up that the elements of a run share,
+// the digit positions below that move data, the key order of the stored
+// keys, and its first element's place among all arrays.
 template <typename K, typename V>
-struct LongRun {
+struct RunArray {
     K *k;
     V *v;
     uint32_t n;
     int shift;
     uint32_t digits;
     uint32_t map;
+    uint64_t base;
 };
+
+// How far element p's run reaches back (BACK) or ahead, by the whole wave: 64
+// probes at a time, at distances that grow 64-fold until one leaves the run
+// and shrink again.
+template <bool BACK, typename K>
+__device__ __forceinline__ uint32_t run_reach(const K *k, uint32_t n, uint32_t p, int shift,
+                                              uint32_t map, K lead, uint32_t lane)
+{
+    const uint32_t room = BACK ? p : n - 1 - p;
+    uint32_t far = 0;
+    uint64_t step = 1;
+    bool grow = true;
+    while (true) {
+        const uint64_t d = far + step * (lane + 1);
+        const bool in = d <= room && (map_in(k[BACK ? p - d : p + d], map) >> shift) == lead;
+        const uint64_t out = ~__ballot(in);
+        const uint32_t c = out ? (uint32_t)__builtin_ctzll(out) : (uint32_t)kWave;
+        far += (uint32_t)step * c;
+        if (c == (uint32_t)kWave && grow) {
+            step *= kWave;
+            continue;
+        }
+        grow = false;
+        if (step == 1)
+            return far;
+        step /= kWave;
+    }
+}
 
 // Runs of up to kRestWaveRun elements are sorted by a wave each, in
 // registers: every element counts the run's elements that go before it, the
-// run's keys broadcast one after another.  Longer ones are listed again,
-// from the list's end.  Returns how many runs this wave took.
+// run's keys broadcast one after another.
 constexpr uint32_t kRestSlots = 8;
 constexpr uint32_t kRestWaveRun = kRestSlots * kWave;
+
+// One place where a run is out of order: finds the run and, if no other place
+// of it was first, lists it.  By one wave.
+template <typename K, typename V>
+__device__ __forceinline__ void rest_find(const RunArray<K, V> &arr, uint2 entry, uint32_t tile,
+                                          uint32_t *ctrl, const RestArea &rest)
+{
+    const uint32_t lane = threadIdx.x % kWave;
+    const K lead = map_in(arr.k[entry.x], arr.map) >> arr.shift;
+    const uint32_t back = run_reach<true>(arr.k, arr.n, entry.x, arr.shift, arr.map, lead, lane);
+    const uint32_t ahead = run_reach<false>(arr.k, arr.n, entry.x, arr.shift, arr.map, lead, lane);
+    const uint32_t start = entry.x - back, m = back + 1 + ahead;
+    if (lane != 0)
+        return;
+    // runs listed are longer than 64, so no two start among the same 64
+    const uint64_t bit = (arr.base + start) / kWave;
+    const uint32_t mask = 1u << (bit % 32);
+    if (atomicOr(&rest.words[kRestTaken + bit / 32], mask) & mask)
+        return;
+    const uint4 run = make_uint4(start, m, entry.y, 0);
+    if (m <= kRestWaveRun) {
+        rest.runs[atomicAdd(&rest.words[kRestShortLen], 1u)] = run;
+    } else {
+        rest.runs[rest.cap - 1 - atomicAdd(&ctrl[kCtrlLongerLen], 1u)] = run;
+        if (m > tile)
+            __hip_atomic_store(&ctrl[kCtrlGiant], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
+}
 
 // Writes a run of m <= 64 SLOTS elements, in registers (element s*64 + lane
 // in slot s), back in order.
 template <typename K, typename V, bool HAS_V, uint32_t SLOTS>
-__device__ __forceinline__ void rest_place(const LongRun<K, V> &run, uint32_t m,
+__device__ __forceinline__ void rest_place(K *rk, V *rv, uint32_t map, uint32_t m,
                                            const K (&x)[kRestSlots],
                                            const V (&v)[HAS_V ? kRestSlots : 1])
 {
@@ -340,253 +487,262 @@ __device__ __forceinline__ void rest_place(const LongRun<K, V> &run, uint32_t m,
 #pragma unroll
     for (uint32_t s = 0; s < SLOTS; ++s) {
         if (s * kWave + lane < m) {
-            run.k[before[s]] = map_out(x[s], run.map);
+            rk[before[s]] = map_out(x[s], map);
             if constexpr (HAS_V)
-                run.v[before[s]] = v[s];
+                rv[before[s]] = v[s];
         }
     }
 }
 
-template <typename K, typename V, bool HAS_V, typename E, typename Resolve>
-__device__ __forceinline__ uint32_t rest_wave_runs(uint32_t *ctrl, E *list, uint32_t list_cap,
-                                                   uint32_t len, Resolve &&resolve)
+// A run of up to kRestWaveRun elements, by one wave.
+template <typename K, typename V, bool HAS_V>
+__device__ __forceinline__ void rest_wave_run(const RunArray<K, V> &arr, uint4 run)
 {
     const uint32_t lane = threadIdx.x % kWave;
-    uint32_t taken = 0;
-    while (true) {
-        uint32_t item = 0;
-        if (lane == 0)
-            item = atomicAdd(&ctrl[kCtrlLongClaim], 1u);
-        item = __builtin_amdgcn_readfirstlane(item);
-        if (item >= len)
-            return taken;
-        ++taken;
-        const E entry = list[item];
-        const LongRun<K, V> run = resolve(entry);
-        K x[kRestSlots];
+    const uint32_t m = run.y;
+    K *rk = arr.k + run.x;
+    V *rv = HAS_V ? arr.v + run.x : nullptr;
+    K x[kRestSlots];
+    V v[HAS_V ? kRestSlots : 1];
 #pragma unroll
-        for (uint32_t s = 0; s < kRestSlots; ++s) {
-            const uint32_t e = s * kWave + lane;
-            x[s] = e < run.n ? run.k[e] : (K)0;
-        }
-        if (run.map) {
-#pragma unroll
-            for (uint32_t s = 0; s < kRestSlots; ++s)
-                x[s] = map_in(x[s], run.map);
-        }
-        const K lead = read_lane(x[0], 0) >> run.shift;
-        uint32_t m = 0;  // the run's length, as far as it was read
-#pragma unroll
-        for (uint32_t s = 0; s < kRestSlots; ++s) {
-            const uint64_t in =
-                __ballot(s * kWave + lane < run.n && (x[s] >> run.shift) == lead);
-            if (m == s * kWave)
-                m += ~in ? (uint32_t)__builtin_ctzll(~in) : kWave;
-        }
-        if (m == kRestWaveRun) {
-            if (lane == 0)
-                list[list_cap - 1 - atomicAdd(&ctrl[kCtrlLongerLen], 1u)] = entry;
-            continue;
-        }
-        V v[HAS_V ? kRestSlots : 1];
-        if constexpr (HAS_V) {
-#pragma unroll
-            for (uint32_t s = 0; s < kRestSlots; ++s)
-                v[s] = s * kWave + lane < m ? run.v[s * kWave + lane] : (V)0;
-        }
-        if (m <= 2 * kWave)
-            rest_place<K, V, HAS_V, 2>(run, m, x, v);
-        else if (m <= 4 * kWave)
-            rest_place<K, V, HAS_V, 4>(run, m, x, v);
-        else
-            rest_place<K, V, HAS_V, 8>(run, m, x, v);
+    for (uint32_t s = 0; s < kRestSlots; ++s) {
+        const uint32_t e = s * kWave + lane;
+        x[s] = e < m ? rk[e] : (K)0;
+        if constexpr (HAS_V)
+            v[s] = e < m ? rv[e] : (V)0;
     }
+    if (arr.map) {
+#pragma unroll
+        for (uint32_t s = 0; s < kRestSlots; ++s)
+            x[s] = map_in(x[s], arr.map);
+    }
+    if (m <= 2 * kWave)
+        rest_place<K, V, HAS_V, 2>(rk, rv, arr.map, m, x, v);
+    else if (m <= 4 * kWave)
+        rest_place<K, V, HAS_V, 4>(rk, rv, arr.map, m, x, v);
+    else
+        rest_place<K, V, HAS_V, 8>(rk, rv, arr.map, m, x, v);
 }
 
 struct RestShared {
-    uint32_t item, len, ok, giant, held;
+    uint32_t item, ok;
 };
 
-// The listed runs, by every workgroup of the launch: waves take the shorter
-// ones, then workgroups the longer ones, up to a tile.  A run longer than a
-// tile that is out of order is passed to giant(entry), and then, or if there
-// are more than `limit` of the longer ones, the result is true: the whole
-// array has to be sorted again (every workgroup gets the same answer, and
-// sees what the others wrote).
-template <typename K, typename V, bool HAS_V, typename C, typename E, typename Resolve,
-          typename Giant>
-__device__ __forceinline__ bool rest_long_runs(
-    BlockLds<K, HAS_V, C::kThreads, C::kItems> &L, RestShared &S, uint32_t *ctrl, E *list,
-    uint32_t list_cap, uint32_t limit, const PassArgs &wait, Resolve &&resolve, Giant &&giant)
+// Hands out [0, len) to the waves of the launch's workgroups, a wave each, from
+// the counter *claim: one atomic for all waves of a workgroup (with one for
+// each of 4096 waves the follow-up took 30 us for a single run).  Returns, to
+// thread 0, how many this workgroup took.
+template <int THREADS, typename F>
+__device__ __forceinline__ uint32_t rest_by_waves(RestShared &S, uint32_t *claim, uint32_t len,
+                                                  F &&f)
+{
+    constexpr uint32_t W = THREADS / kWave;
+    const uint32_t w = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+    uint32_t taken = 0;
+    while (true) {
+        __syncthreads();
+        if (threadIdx.x == 0)
+            S.item = atomicAdd(claim, W);
+        __syncthreads();
+        const uint32_t item = __builtin_amdgcn_readfirstlane(S.item);
+        if (item >= len)
+            return taken;
+        taken += min(W, len - item);
+        if (item + w < len)
+            f(item + w);
+    }
+}
+
+// The runs out of order, by every workgroup of the launch: all look up where
+// the sweep reported one and wait for each other; then waves take the shorter
+// runs and workgroups the longer ones.  If a run is longer than a tile, or
+// there are too many, nothing is sorted and the result is true: everything has
+// to be sorted again (every workgroup gets the same answer).  resolve(segment)
+// is the array that holds a run.
+template <typename K, typename V, bool HAS_V, typename C, typename Resolve>
+__device__ __forceinline__ bool rest_runs(BlockLds<K, HAS_V, C::kThreads, C::kItems> &L,
+                                          RestShared &S, uint32_t *ctrl, const RestArea &rest,
+                                          const PassArgs &wait, Resolve &&resolve)
 {
     constexpr uint32_t T = C::kTile;
     constexpr int THREADS = C::kThreads;
     constexpr int ITEMS = C::kItems;
     const uint32_t t = threadIdx.x;
-    const uint32_t len = __builtin_amdgcn_readfirstlane(ctrl[kCtrlLongLen]);
-    if (len > list_cap)
+    const uint32_t len = __builtin_amdgcn_readfirstlane(ctrl[kCtrlUnsorted]);
+    if (len > rest.cap)
         return true;
-    if (t == 0)
-        S.held = 0;
-    __syncthreads();
-    const uint32_t held = rest_wave_runs<K, V, HAS_V>(ctrl, list, list_cap, len, resolve);
-    if (t % kWave == 0 && held)
-        atomicAdd(&S.held, held);
-    __syncthreads();
+    const uint32_t found =
+        rest_by_waves<THREADS>(S, &rest.words[kRestFindClaim], len, [&](uint32_t i) {
+            const uint2 entry = rest.list[i];
+            rest_find(resolve(entry.y), entry, T, ctrl, rest);
+        });
     if (t == 0) {
-        S.ok = hand_on_and_wait(&ctrl[kCtrlLongDone], S.held, len, wait) ? 1u : 0u;
-        S.len = __hip_atomic_load(&ctrl[kCtrlLongerLen], __ATOMIC_RELAXED,
-                                  __HIP_MEMORY_SCOPE_AGENT);
+        S.ok = hand_on_and_wait(&rest.words[kRestFindDone], found, len, wait) ? 1u : 0u;
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
     }
     __syncthreads();
-    const uint32_t longer = S.len;
-    if (!S.ok || longer == 0)
+    if (!S.ok)
         return false;
-    if (t == 0)
-        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
-    if (longer > limit) {
-        __syncthreads();
+    const auto count = [](uint32_t *word) {
+        return __builtin_amdgcn_readfirstlane(
+            __hip_atomic_load(word, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
+    };
+    if (count(&ctrl[kCtrlGiant]))
         return true;
-    }
-    uint32_t mine = 0;
+    const uint32_t shorts = count(&rest.words[kRestShortLen]);
+    const uint32_t longer = count(&ctrl[kCtrlLongerLen]);
+    rest_by_waves<THREADS>(S, &rest.words[kRestShortClaim], shorts, [&](uint32_t i) {
+        const uint4 run = rest.runs[i];
+        rest_wave_run<K, V, HAS_V>(resolve(run.z), run);
+    });
     while (true) {
         __syncthreads();
-        if (t == 0) {
-            S.item = atomicAdd(&ctrl[kCtrlLongerClaim], 1u);
-            S.len = T;
-        }
+        if (t == 0)
+            S.item = atomicAdd(&rest.words[kRestLongerClaim], 1u);
         __syncthreads();
-        if (S.item >= longer)
-            break;
-        ++mine;
-        const E entry = list[list_cap - 1 - S.item];
-        const LongRun<K, V> run = resolve(entry);
-        const K lead = map_in(run.k[0], run.map) >> run.shift;
-        uint32_t end = T;
-        for (uint32_t e = t; e < T; e += THREADS)
-            if (e >= run.n || (map_in(run.k[e], run.map) >> run.shift) != lead)
-                end = min(end, e);
-        if (end < T)
-            atomicMin(&S.len, end);
-        __syncthreads();
-        const uint32_t m = S.len;
-        if (m == T && run.n > T && (map_in(run.k[T], run.map) >> run.shift) == lead) {
-            // longer than a tile: only its order is checked here
-            bool bad = true;
-            for (uint32_t tl = 0; tl < kRestScanTiles; ++tl) {
-                bool out = false, ends = false;
-                for (uint32_t e = t; e < T; e += THREADS) {
-                    const uint64_t i = (uint64_t)tl * T + e;
-                    if (i + 1 >= run.n) {
-                        ends = true;
-                        continue;
-                    }
-                    const K x = map_in(run.k[i], run.map), y = map_in(run.k[i + 1], run.map);
-                    if ((x >> run.shift) != lead)
-                        ends = true;
-                    else
-                        out = out || ((y >> run.shift) == lead && x > y);
-                }
-                if (__syncthreads_or(out))
-                    break;
-                if (__syncthreads_or(ends)) {
-                    bad = false;
-                    break;
-                }
-            }
-            if (bad && t == 0) {
-                giant(entry);
-                __hip_atomic_store(&ctrl[kCtrlGiant], 1u, __ATOMIC_RELAXED,
-                                   __HIP_MEMORY_SCOPE_AGENT);
-            }
-        } else {
-            const BlockItems<THREADS, ITEMS> it(m);
-            K key[ITEMS];
-            V val[HAS_V ? ITEMS : 1];
-            it.each([&](int j) {
-                key[j] = it.has(j) ? map_in(run.k[it.at(j)], run.map) : (K)0;
+        const uint32_t item = __builtin_amdgcn_readfirstlane(S.item);
+        if (item >= longer)
+            return false;
+        const uint4 run = rest.runs[rest.cap - 1 - item];
+        const RunArray<K, V> arr = resolve(run.z);
+        K *rk = arr.k + run.x;
+        V *rv = HAS_V ? arr.v + run.x : nullptr;
+        const BlockItems<THREADS, ITEMS> it(run.y);
+        K key[ITEMS];
+        V val[HAS_V ? ITEMS : 1];
+        it.each([&](int j) {
+            key[j] = it.has(j) ? map_in(rk[it.at(j)], arr.map) : (K)0;
+            if constexpr (HAS_V)
+                val[j] = it.has(j) ? rv[it.at(j)] : (V)0;
+        });
+        __syncthreads();  // everything is read before it is overwritten
+        block_sort_digits<K, V, HAS_V, THREADS, ITEMS>(L, it, key, val, arr.digits);
+        it.each([&](int j) {
+            if (it.has(j)) {
+                rk[it.at(j)] = map_out(key[j], arr.map);
                 if constexpr (HAS_V)
-                    val[j] = it.has(j) ? run.v[it.at(j)] : (V)0;
-            });
-            __syncthreads();  // everything is read before it is overwritten
-            block_sort_digits<K, V, HAS_V, THREADS, ITEMS>(L, it, key, val, run.digits);
-            it.each([&](int j) {
-                if (it.has(j)) {
-                    run.k[it.at(j)] = map_out(key[j], run.map);
-                    if constexpr (HAS_V)
-                        run.v[it.at(j)] = val[j];
-                }
-            });
-        }
+                    rv[it.at(j)] = val[j];
+            }
+        });
     }
-    __syncthreads();
-    if (t == 0) {
-        S.ok = hand_on_and_wait(&ctrl[kCtrlLongerDone], mine, longer, wait) ? 1u : 0u;
-        S.giant = __hip_atomic_load(&ctrl[kCtrlGiant], __ATOMIC_RELAXED,
-                                    __HIP_MEMORY_SCOPE_AGENT);
-    }
-    __syncthreads();
-    if (!S.ok || S.giant == 0)
-        return false;
-    if (t == 0)
-        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
-    __syncthreads();
-    return true;
 }
 
 // The next item of stages of `tiles` items each, or false when there is none
 // (or a wait reached its bound).  Called by every thread after a barrier that
-// ends its last item, which it counts as done (stage_done: one zeroed word
-// per stage); an item waits for the stage before its own.
+// ends its last item; an item waits for the stage before its own.  A workgroup
+// counts its items as done when it goes on to another stage: a release writes
+// a cache back, so one for every item made a stage take as long as two.
 struct RestItem {
     uint32_t stage = 0, tile = 0;
-    bool held = false;
+    uint32_t held = 0;  // items of `stage` finished or at work
 };
 
-__device__ __forceinline__ bool rest_next(RestItem &it, RestShared &S, uint32_t *ctrl,
-                                          uint32_t *stage_done, uint32_t stages, uint32_t tiles,
-                                          const PassArgs &wait)
+__device__ __forceinline__ bool rest_next(RestItem &it, RestShared &S, uint32_t *words,
+                                          uint32_t stages, uint32_t tiles, const PassArgs &wait)
 {
-    // One thread reports the last item, claims the next and waits, in one
+    uint32_t *stage_done = words + kRestStageDone;
+    // One thread reports the last items, claims the next and waits, in one
     // place: with the report at the end of the caller's loop the compiler
     // sends the other threads of its wave to the barrier ahead of it.
     if (threadIdx.x == 0) {
-        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
-        if (it.held)
-            atomicAdd(&stage_done[it.stage], 1u);
-        const uint32_t item = atomicAdd(&ctrl[kCtrlRestClaim], 1u);
+        const uint32_t item = atomicAdd(&words[kRestItemClaim], 1u);
         const uint32_t st = item / tiles;
         S.item = item;
-        S.ok = st == 0 || st >= stages || wait_count(&stage_done[st - 1], tiles, wait);
-        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
+        S.ok = 1;
+        if (st != it.stage || it.held == 0) {
+            if (it.held) {
+                __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
+                atomicAdd(&stage_done[it.stage], it.held);
+            }
+            S.ok = st == 0 || st >= stages || wait_count(&stage_done[st - 1], tiles, wait);
+            __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
+        }
     }
     __syncthreads();
-    it.held = true;
-    it.stage = __builtin_amdgcn_readfirstlane(S.item / tiles);
+    const uint32_t stage = __builtin_amdgcn_readfirstlane(S.item / tiles);
+    it.held = stage == it.stage ? it.held + 1 : 1;
+    it.stage = stage;
     it.tile = __builtin_amdgcn_readfirstlane(S.item % tiles);
     return it.stage < stages && S.ok != 0;
 }
 
-// One launch of persistent workgroups.  Work is claimed in order, (stage,
-// tile) after (stage, tile), and an item waits only for the stage before its
-// own, whose items are all claimed by running workgroups: no wait depends on
-// a workgroup that has not started (nor do those for the long runs: a
-// workgroup counts its runs as done before it waits for the others').
-// Stages hand their data on through memory within the launch
-// (hand_on_and_wait).
-template <typename K, typename V, bool HAS_V, typename C>
-__global__ __launch_bounds__(C::kThreads) void k_last(LastArgs a)
+// An array to sort again by every digit in `digits`: its buffers (it lies in the
+// first of each, and ends there), its length, its first row, the digits that
+// are skewed, the key order of the stored keys, and every digit's offsets.
+template <typename K, typename V>
+struct AgainArray {
+    K *k[2];
+    V *v[2];
+    uint32_t n;
+    uint32_t first;
+    uint32_t digits;
+    uint32_t skew;
+    uint32_t map;
+    const uint32_t *base;  // [digit][256]
+};
+
+// Sorts arrays again, in `rows` rows of a tile each; resolve(row) is the array
+// of a row.  Two stages a digit, one that clears the rows' look-back words and a
+// pass; the lowest digit twice if their number is odd, so that the result ends
+// where it began (sorting by a digit twice changes nothing).
+template <typename K, typename V, bool HAS_V, typename C, typename Resolve>
+__device__ __forceinline__ void sort_again(PassLds<K, C, HAS_V> &L, RestShared &S,
+                                           const RestArea &rest, uint32_t rows,
+                                           const PassArgs &wait, Resolve &&resolve)
 {
     constexpr uint32_t T = C::kTile;
     constexpr uint32_t NB = C::kBins;
     constexpr int R = C::kRadixBits;
     constexpr int THREADS = C::kThreads;
-    static_assert(R == kRadixBits, "8-bit digits");
-    using Block = BlockLds<K, HAS_V, THREADS, C::kItems>;
-    using Pass = PassLds<K, C, HAS_V>;
+    constexpr uint32_t D = num_passes<K, R>();
+    static_assert(R == kRadixBits && D % 2 == 0 && kRestStageDone + 2 * D <= kRestTaken,
+                  "8-bit digits; a word for every stage");
+    const uint32_t t = threadIdx.x;
+    RestItem it;
+    while (rest_next(it, S, rest.words, 2 * D, rows, wait)) {
+        const AgainArray<K, V> a = resolve(it.tile);
+        const uint32_t q = (uint32_t)__popc(a.digits);
+        const uint32_t sets = q + (q & 1), set = it.stage / 2;
+        if (set >= sets) {
+            __syncthreads();
+            continue;
+        }
+        if (it.stage % 2 == 0) {
+            for (uint32_t i = t; i < NB; i += THREADS)
+                rest.rows[(uint64_t)it.tile * NB + i] = 0;
+            __syncthreads();
+            continue;
+        }
+        uint32_t left = a.digits;
+        for (uint32_t i = q & 1; i < set; ++i)
+            left &= left - 1;
+        const uint32_t digit = (uint32_t)__builtin_ctz(left);
+        const uint32_t from = set & 1, into = from ^ 1;
+        const uint32_t tb = (it.tile - a.first) * T;
+        const uint32_t valid = a.n > tb ? min(T, a.n - tb) : 0u;
+        const uint32_t dbase = t < NB ? a.base[digit * NB + t] : 0u;
+        pass_tile<K, V, HAS_V, C>(L, a.k[from] + tb, HAS_V ? a.v[from] + tb : nullptr, a.k[into],
+                                  HAS_V ? a.v[into] : nullptr, valid, a.n, it.tile, a.first,
+                                  rest.rows, nullptr, dbase, (int)digit * R,
+                                  ((a.skew >> digit) & 1u) != 0, set == 0 ? a.map : 0u,
+                                  set + 1 == sets ? a.map : 0u, wait, [](uint32_t) {});
+    }
+}
+
+// One launch of persistent workgroups.  Work is claimed in order, (stage,
+// tile) after (stage, tile), and an item waits only for the stage before its
+// own, whose items are all claimed by running workgroups: no wait depends on
+// a workgroup that has not started (nor does the one in rest_runs: a
+// workgroup counts what it has looked up as done before it waits for the
+// others).  Stages hand their data on through memory within the launch
+// (hand_on_and_wait).
+template <typename K, typename V, bool HAS_V, typename C>
+__global__ __launch_bounds__(C::kThreads) void k_last(LastArgs a)
+{
+    static_assert(C::kRadixBits == kRadixBits, "8-bit digits");
     __shared__ union {
-        Pass pass;
-        Block block;
+        PassLds<K, C, HAS_V> pass;
+        BlockLds<K, HAS_V, C::kThreads, C::kItems> block;
     } L;
     __shared__ RestShared S;
 
@@ -598,63 +754,26 @@ __global__ __launch_bounds__(C::kThreads) void k_last(LastArgs a)
     }
     if (ctrl[kCtrlUnsorted] == 0)
         return;
-    const uint32_t t = threadIdx.x;
     const uint32_t n = a.p.n;
     const uint32_t buf = (finish >> kFinishDstShift) & 3u;  // where k_finish wrote
     const uint32_t digits = __builtin_amdgcn_readfirstlane(ctrl[kCtrlDigits]);
-    const uint32_t skew = __builtin_amdgcn_readfirstlane(ctrl[kCtrlSkew]);
-    const uint32_t tiles = a.p.num_tiles;
     // the output holds unmapped keys, the scratch copy mapped ones
     const uint32_t map = buf == kBufOut ? a.p.kmap : 0u;
-    const int run_shift = (int)(finish >> kFinishShift);
+    const int shift = (int)(finish >> kFinishShift);
     K *bk = pick<K>(a.p.b, buf, false);
     V *bv = HAS_V ? pick<V>(a.p.b, buf, true) : nullptr;
-    const uint32_t low = digits & ((1u << (run_shift / R)) - 1u);
-    // a longer run takes a workgroup about one tile's time per digit below
-    // the finish shift: past this many the whole array is sorted again
-    if (!rest_long_runs<K, V, HAS_V, C>(
-            L.block, S, ctrl, a.list, a.list_cap, max(512u, a.d * tiles), a.p,
-            [=](uint32_t start) {
-                return LongRun<K, V>{bk + start, HAS_V ? bv + start : nullptr, n - start,
-                                     run_shift, low, map};
-            },
-            [](uint32_t) {}))
+    const uint32_t low = digits & ((1u << (shift / C::kRadixBits)) - 1u);
+    if (!rest_runs<K, V, HAS_V, C>(
+            L.block, S, ctrl, a.rest, a.p,
+            [=](uint32_t) { return RunArray<K, V>{bk, bv, n, shift, low, map, 0}; }))
         return;
-
-    // again by every digit: one stage that clears the look-back words, then
-    // the digits, the lowest one twice if their number is odd, so that the
-    // result ends where k_finish wrote (sorting by a digit twice changes
-    // nothing)
-    const uint32_t q = (uint32_t)__popc(digits);
-    const uint32_t sets = q + (q & 1);
     const uint32_t other = buf == kBufOut ? kBufTmp : kBufOut;
-    RestItem it;
-    while (rest_next(it, S, ctrl, ctrl + kCtrlStageDone, 1 + sets, tiles, a.p)) {
-        if (it.stage == 0) {
-            for (uint32_t set = 0; set < sets; ++set)
-                for (uint32_t i = t; i < NB; i += THREADS)
-                    a.status[((uint64_t)set * tiles + it.tile) * NB + i] = 0;
-            __syncthreads();
-            continue;
-        }
-        const uint32_t set = it.stage - 1;
-        uint32_t left = digits;
-        for (uint32_t i = q & 1; i < set; ++i)
-            left &= left - 1;
-        const uint32_t digit = (uint32_t)__builtin_ctz(left);
-        const uint32_t from = set & 1 ? other : buf;
-        const uint32_t into = set & 1 ? buf : other;
-        const K *sk = pick<const K>(a.p.b, from, false);
-        const V *sv = HAS_V ? pick<const V>(a.p.b, from, true) : nullptr;
-        const uint32_t tb = it.tile * T;
-        const uint32_t dbase = t < NB ? a.p.digit_base[digit * NB + t] : 0u;
-        pass_tile<K, V, HAS_V, C>(
-            L.pass, sk + tb, HAS_V ? sv + tb : nullptr, pick<K>(a.p.b, into, false),
-            HAS_V ? pick<V>(a.p.b, into, true) : nullptr, min(T, n - tb), n, it.tile, 0,
-            a.status + (uint64_t)set * tiles * NB, nullptr, dbase, (int)digit * R,
-            (skew >> digit) & 1u, set == 0 ? map : 0u, set + 1 == sets ? map : 0u, a.p,
-            [](uint32_t) {});
-    }
+    K *ok = pick<K>(a.p.b, other, false);
+    V *ov = HAS_V ? pick<V>(a.p.b, other, true) : nullptr;
+    const uint32_t skew = __builtin_amdgcn_readfirstlane(ctrl[kCtrlSkew]);
+    sort_again<K, V, HAS_V, C>(L.pass, S, a.rest, a.p.num_tiles, a.p, [=](uint32_t) {
+        return AgainArray<K, V>{{bk, ok}, {bv, ov}, n, 0, digits, skew, map, a.p.digit_base};
+    });
 }
 
 // ---------------------------------------------------------------------------
@@ -673,8 +792,7 @@ struct SegFinishArgs {
     uint32_t max_tiles;
     uint32_t tile;      // elements per tile of the passes, a multiple of the sweep's
     uint32_t group;     // sweep tiles that a workgroup takes together, of one tile
-    uint2 *list;        // long runs: start within the segment, segment
-    uint32_t list_cap;
+    RestArea rest;
     uint32_t kmap;
     int in_place;
 };
@@ -686,10 +804,8 @@ __global__ __launch_bounds__(THREADS) void k_seg_finish(SegFinishArgs a)
     __shared__ FinishLds<K, THREADS, ITEMS> L;
     if (!(a.ctrl[kSegPassMask] & kSegAnyFinish))
         return;
-    uint32_t *ctrl = a.ctrl;
-    uint2 *list = a.list;
-    const uint32_t cap = a.list_cap;
-    const uint32_t tiles = std::min(ctrl[kSegTiles], a.max_tiles);
+    finish_begin(L, a.rest);
+    const uint32_t tiles = std::min(a.ctrl[kSegTiles], a.max_tiles);
     // groups of sweep tiles: a segment's record takes three dependent loads
     const uint32_t per = a.tile / (T * a.group);
     for (uint32_t item = blockIdx.x; item < tiles * per; item += gridDim.x) {
@@ -711,113 +827,78 @@ __global__ __launch_bounds__(THREADS) void k_seg_finish(SegFinishArgs a)
         for (uint32_t g = 0; g < a.group && tb < size; ++g, tb += T)
             finish_tile<K, V, HAS_V, THREADS, ITEMS>(
                 L, sk, sv, dk, dv, size, tb, (int)(m.low * kRadixBits),
-                dst == kBufOut ? a.kmap : 0u, &ctrl[kCtrlUnsorted], [=](uint32_t i) {
-                    const uint32_t l = atomicAdd(&ctrl[kCtrlLongLen], 1u);
-                    if (l < cap)
-                        list[l] = make_uint2(i, seg);
-                });
+                dst == kBufOut ? a.kmap : 0u,
+                [&](uint32_t i) { finish_report(L, a.ctrl, a.rest, i, seg); });
     }
+    finish_end(L, a.ctrl, a.rest);
 }
 
 struct SegLastArgs {
-    SegPassArgs p;  // status: the look-back words of every pass
-    uint64_t status_stride;
-    uint2 *list;
-    uint32_t list_cap;
+    SegPassArgs p;
+    RestArea rest;
 };
 
 template <typename K, typename V, bool HAS_V, typename C>
 __global__ __launch_bounds__(C::kThreads) void k_seg_last(SegLastArgs a)
 {
-    constexpr uint32_t T = C::kTile;
     constexpr uint32_t NB = C::kBins;
     constexpr int R = C::kRadixBits;
     constexpr int D = num_passes<K, R>();
-    constexpr int THREADS = C::kThreads;
-    static_assert(R == kRadixBits && D % 2 == 0, "8-bit digits");
     __shared__ union {
         PassLds<K, C, HAS_V> pass;
-        BlockLds<K, HAS_V, THREADS, C::kItems> block;
+        BlockLds<K, HAS_V, C::kThreads, C::kItems> block;
     } L;
     __shared__ RestShared S;
     uint32_t *ctrl = a.p.ctrl;
     if (ctrl[kCtrlUnsorted] == 0)
         return;
-    const uint32_t t = threadIdx.x;
     const bool in_place = a.p.keys_in_place || a.p.vals_in_place;
-    const uint32_t tiles = std::min(ctrl[kSegTiles], a.p.max_tiles);
     const SegLarge *large = a.p.large;
-    uint32_t *seg_flags = a.p.seg_flags;
+    const uint32_t *seg_flags = a.p.seg_flags;
     const Bufs b = a.p.b;
     const uint32_t kmap = a.p.kmap;
     PassArgs wait{};
     wait.err = ctrl + kSegError;
     wait.spin_limit = a.p.spin_limit;
     wait.stall = a.p.stall;
-    if (!rest_long_runs<K, V, HAS_V, C>(
-            L.block, S, ctrl, a.list, a.list_cap, ~0u, wait,
-            [=](uint2 entry) {
-                const SegLarge rec = large[entry.y];
-                const uint32_t flags = seg_flags[entry.y];
-                const SegMoves m = seg_moves<K, R>(flags, in_place);
-                const uint32_t buf = m.dst(m.moves - 1);
-                const uint64_t at = rec.start + entry.x;
-                return LongRun<K, V>{
-                    pick<K>(b, buf, false) + at,
-                    HAS_V ? pick<V>(b, buf, true) + at : nullptr,
-                    (uint32_t)__builtin_amdgcn_readfirstlane(rec.size - entry.x),
-                    (int)__builtin_amdgcn_readfirstlane(m.low * R),
-                    (uint32_t)__builtin_amdgcn_readfirstlane(~flags & ((1u << m.low) - 1u)),
-                    buf == kBufOut ? kmap : 0u};
-            },
-            [=](uint2 entry) { atomicOr(&seg_flags[entry.y], kSegGiant); }))
+    const auto uniform = [](uint32_t x) {
+        return (uint32_t)__builtin_amdgcn_readfirstlane(x);
+    };
+    if (!rest_runs<K, V, HAS_V, C>(L.block, S, ctrl, a.rest, wait, [=](uint32_t seg) {
+            const SegLarge rec = large[seg];
+            const uint32_t flags = seg_flags[seg];
+            const SegMoves m = seg_moves<K, R>(flags, in_place);
+            const uint32_t buf = m.dst(m.moves - 1);
+            return RunArray<K, V>{pick<K>(b, buf, false) + rec.start,
+                                  HAS_V ? pick<V>(b, buf, true) + rec.start : nullptr,
+                                  uniform(rec.size),
+                                  (int)uniform(m.low * R),
+                                  uniform(~flags & ((1u << m.low) - 1u)),
+                                  buf == kBufOut ? kmap : 0u,
+                                  rec.start};
+        }))
         return;
 
-    // segments with a giant run: again by every digit, as in k_last
-    RestItem it;
-    while (rest_next(it, S, ctrl, ctrl + kSegStageDone, 1 + D, tiles, wait)) {
-        const uint32_t seg = a.p.tile_seg[it.tile];
+    // every segment that was swept is sorted again
+    const uint32_t tiles = std::min(ctrl[kSegTiles], a.p.max_tiles);
+    const uint32_t *tile_seg = a.p.tile_seg, *seg_base = a.p.seg_base;
+    sort_again<K, V, HAS_V, C>(L.pass, S, a.rest, tiles, wait, [=](uint32_t tile) {
+        const uint32_t seg = tile_seg[tile];
         const SegLarge rec = large[seg];
-        const uint32_t flags = __builtin_amdgcn_readfirstlane(__hip_atomic_load(
-            &seg_flags[seg], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
+        const uint32_t flags = uniform(seg_flags[seg]);
         const SegMoves m = seg_moves<K, R>(flags, in_place);
-        const uint32_t digits = ~flags & ((1u << D) - 1u);
-        const uint32_t q = (uint32_t)__popc(digits);
-        const uint32_t sets = q + (q & 1);
-        if (!(flags & kSegGiant) || it.stage > sets) {
-            __syncthreads();
-            continue;
-        }
-        if (it.stage == 0) {
-            for (uint32_t set = 0; set < sets; ++set)
-                for (uint32_t i = t; i < NB; i += THREADS)
-                    a.p.status[set * a.status_stride + (uint64_t)it.tile * NB + i] = 0;
-            __syncthreads();
-            continue;
-        }
-        const uint32_t set = it.stage - 1;
-        uint32_t left = digits;
-        for (uint32_t i = q & 1; i < set; ++i)
-            left &= left - 1;
-        const uint32_t digit = (uint32_t)__builtin_ctz(left);
-        const uint32_t buf = m.dst(m.moves - 1);
-        const uint32_t other = buf == kBufOut ? kBufTmp : kBufOut;
-        const uint32_t from = set & 1 ? other : buf, into = set & 1 ? buf : other;
-        const uint32_t map = buf == kBufOut ? kmap : 0u;
-        const uint32_t first = (it.tile - rec.tile_start) * T;
-        const uint32_t valid = rec.size > first ? min(T, rec.size - first) : 0u;
-        const uint64_t off = rec.start + first;
-        const uint32_t dbase =
-            t < NB ? a.p.seg_base[((uint64_t)seg * D + digit) * NB + t] : 0u;
-        pass_tile<K, V, HAS_V, C>(
-            L.pass, pick<const K>(b, from, false) + off,
-            HAS_V ? pick<const V>(b, from, true) + off : nullptr,
-            pick<K>(b, into, false) + rec.start,
-            HAS_V ? pick<V>(b, into, true) + rec.start : nullptr, valid, rec.size, it.tile,
-            rec.tile_start, a.p.status + set * a.status_stride, nullptr, dbase, (int)digit * R,
-            ((flags >> (kSegSkewShift + digit)) & 1u) != 0, set == 0 ? map : 0u,
-            set + 1 == sets ? map : 0u, wait, [](uint32_t) {});
-    }
+        const uint32_t buf = m.dst(m.moves - 1), other = buf == kBufOut ? kBufTmp : kBufOut;
+        return AgainArray<K, V>{{pick<K>(b, buf, false) + rec.start,
+                                 pick<K>(b, other, false) + rec.start},
+                                {HAS_V ? pick<V>(b, buf, true) + rec.start : nullptr,
+                                 HAS_V ? pick<V>(b, other, true) + rec.start : nullptr},
+                                uniform(rec.size),
+                                uniform(rec.tile_start),
+                                m.low ? ~flags & ((1u << D) - 1u) : 0u,
+                                flags >> kSegSkewShift,
+                                buf == kBufOut ? kmap : 0u,
+                                seg_base + (uint64_t)seg * D * NB};
+    });
 }
 
 }  // namespace rs

@@ -1259,7 +1259,7 @@ struct SegHistArgs {
     uint32_t *seg_flags;  // [large segment]: first its first chunk (k_seg_hist), then
                           // (k_seg_scan) bit p pass p's digit is the same for the
                           // whole segment; bit 16 + p pass p's digits are skewed;
-                          // with 8-bit digits kSegLowShift and kSegGiant too
+                          // with 8-bit digits kSegLowShift too
     uint32_t kmap;        // key order applied to every key read
 };
 
@@ -1267,7 +1267,6 @@ constexpr int kSegSkewShift = 16;
 // 8-bit digits (at most eight positions) leave bits free:
 constexpr int kSegLowShift = 8;             // 4 bits: the lowest position sorted by passes when
                                             // k_seg_finish orders the rest, else 0
-constexpr uint32_t kSegGiant = 1u << 31;    // an unsorted run longer than a tile (k_seg_last)
 // kSegPassMask: bit p: a segment moves in pass p; and
 constexpr uint32_t kSegAnyFinish = 1u << 16;
 
@@ -1508,7 +1507,7 @@ struct SegPassArgs {
     const SegLarge *large;
     const uint32_t *tile_seg;
     const uint32_t *seg_base;  // [large segment][d][2^R]
-    uint32_t *seg_flags;       // [large segment] (k_seg_scan)
+    const uint32_t *seg_flags; // [large segment] (k_seg_scan)
     uint32_t *ctrl;            // segmented control block
     uint32_t *status;          // look-back words of this pass
     uint32_t *claims;          // claim counters of this pass

@@ -45,7 +45,6 @@ constexpr int kSegTinyClaim = 9;
 constexpr int kSegPassCounter = 32; // [32, 48): group counter per pass
 constexpr int kSegChunks = 16;      // histogram chunks of the large segments
 constexpr int kSegChunkClaim = 17;
-constexpr int kSegStageDone = 18;   // [18, 27): items done per stage of k_seg_last
 constexpr int kSegPassMask = 49;    // passes in which a segment moves, kSegAnyFinish
 constexpr int kSegWords = 64;       // (k_seg_finish and k_seg_last: the words of the plain
                                     // sort's control block from kCtrlUnsorted on)

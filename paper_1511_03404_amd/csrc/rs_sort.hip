@@ -704,9 +704,8 @@ static rs_status run_sort(rs_context *ctx, const K *kin, const K *vin, K *kout, 
     pa.stall = ctx->stall;
     // the pass slots; the last one copies the input when no pass moves data,
     // or follows up on k_finish
-    // the list of long runs takes the place of the passes' look-back words
-    const uint32_t list_cap = (uint32_t)std::min<uint64_t>(n, (uint64_t)L.d * L.tiles * L.bins);
-    const FinishArgs fa{b, (uint32_t)n, ctrl, status, list_cap, kmap};
+    const RestArea rest = rest_area(status, L.tiles, n);
+    const FinishArgs fa{b, (uint32_t)n, ctrl, rest, kmap};
     const bool fused = n <= kFinishFused;
     for (int p = 0; p < slots; ++p) {
         pa.pass = p;
@@ -734,7 +733,7 @@ static rs_status run_sort(rs_context *ctx, const K *kin, const K *vin, K *kout, 
                 (uint64_t)resident_blocks(op.finish_kernel, kFinishThreads) * ctx_cus(ctx));
             launch(ctx, s, "k_finish", [&] { op.finish(fa, grid, s); });
         }
-        LastArgs la{pa, status, (uint32_t)L.d, status, list_cap};
+        const LastArgs la{pa, rest};
         launch(ctx, s, "k_last", [&] { op.last(la, pass_grid, s); });
     }
     if (in_place) {
@@ -1104,22 +1103,17 @@ static rs_status run_segmented(rs_context *ctx, const void *kin, const void *vin
                [&] { op.pass(pa, pass_grid, s); });
     }
     if (op.finish) {
-        // the list of long runs takes the place of the passes' look-back
-        // words: more than a word pair for every 65 elements
-        uint2 *list = (uint2 *)status;
-        const uint32_t list_cap = (uint32_t)std::min<uint64_t>(
-            0xFFFFFFFFu, (uint64_t)L.d * L.max_tiles * L.bins / 2);
+        const RestArea rest = rest_area(status, L.max_tiles, total);
         const uint32_t per = (uint32_t)op.tile / (kFinishThreads * kFinishItems);
         const uint32_t most = grid_of(op.finish_kernel, kFinishThreads);
         uint32_t group = per;
         while (group % 2 == 0 && total / op.tile * (per / group) < 2 * most)
             group /= 2;
         const SegFinishArgs fa{pa.b, large, tile_seg, seg_flags, ctrl, pa.max_tiles,
-                               (uint32_t)op.tile, group, list, list_cap, kmap, in_place};
+                               (uint32_t)op.tile, group, rest, kmap, in_place};
         const uint32_t fg = (uint32_t)std::min<uint64_t>(L.max_tiles * (per / group), most);
         launch(ctx, s, "k_seg_finish", [&] { op.finish(fa, fg, s); });
-        pa.status = status;
-        const SegLastArgs la{pa, L.max_tiles * L.bins, list, list_cap};
+        const SegLastArgs la{pa, rest};
         launch(ctx, s, "k_seg_last", [&] { op.last(la, pass_grid, s); });
     }
     if (in_place) {
