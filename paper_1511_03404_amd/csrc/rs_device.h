@@ -49,7 +49,7 @@ constexpr int kCtrlFinish = 49;      // run finish word (kFinish*), 0: none
 constexpr int kCtrlUnsorted = 50;    // places where long runs are out of order, as listed by
                                      // k_finish: without any k_last has no work
 constexpr int kCtrlLongLen = 51;     // long runs met by k_finish, in order or not
-constexpr int kCtrlGiant = 52;       // an unsorted run is longer than a tile
+constexpr int kCtrlGiant = 52;       // unsorted runs longer than a tile
 constexpr int kCtrlDigits = 53;      // bit p: digit position p moves data
 constexpr int kCtrlSkew = 54;        // bit p: digit position p is skewed
 constexpr int kCtrlSlots = 55;       // pass slots in use

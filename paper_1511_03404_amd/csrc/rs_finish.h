@@ -12,9 +12,9 @@
 //              order, reported;
 //   k_last     the last pass slot.  After a sweep that slot is free, and it
 //              does what the sweep could not, normally nothing: the reported
-//              runs are sorted by a wave or a workgroup each, and if one is
-//              longer than a tile (or there are too many) the whole array is
-//              sorted again by every digit.
+//              runs are sorted by a wave or a workgroup each, longer ones by
+//              digit passes over the run alone; if there are too many, the
+//              whole array is sorted again by every digit.
 #pragma once
 
 #include "rs_kernels.h"
@@ -26,8 +26,11 @@ namespace rs {
 // the passes, which are done by then (rest_area).
 struct RestArea {
     uint32_t *rows;   // look-back words [row][256] of a sort again
-    uint4 *runs;      // runs to sort: start, length, segment, unused; from the
-                      // front those for a wave, from the end the longer ones
+    uint32_t *row_run;  // the run of each row, as counted from the end of runs
+    uint32_t max_rows;
+    uint4 *runs;      // runs to sort: start, length, segment, and its first row
+                      // if it is longer than a tile; from the front those for a
+                      // wave, from the end the longer ones
     uint2 *list;      // where runs are out of order: element, segment
     uint32_t cap;     // entries of each
     uint32_t *words;  // counters (kRest*), then a bit for every 64 elements: the
@@ -39,22 +42,26 @@ constexpr int kRestFindDone = 1;    // and looked up;
 constexpr int kRestShortLen = 2;    // runs for a wave: listed,
 constexpr int kRestShortClaim = 3;  // and claimed;
 constexpr int kRestLongerClaim = 4; // longer runs claimed
-constexpr int kRestItemClaim = 5;   // (stage, tile) items claimed
+constexpr int kRestItemClaim = 5;   // (stage, row) items claimed
+constexpr int kRestRows = 6;        // rows of the runs longer than a tile
 constexpr int kRestStageDone = 8;   // [8, 24): items done per stage
 constexpr int kRestTaken = 32;
 
 // Lays the area out over the look-back words of `tiles` tiles, 256 a tile for
 // each of four or eight digits.  A tile holds at most 24576 elements, so the
-// bits take 12 words a tile, and with 512 for the rows and 6 for each of 64
-// runs four digits' words hold it all.
+// bits take 12 words a tile, and with 512 for the rows (of runs longer than a
+// tile there are fewer than two for every whole tile they cover), 2 for their
+// map and 6 for each of 64 runs four digits' words hold it all.
 inline RestArea rest_area(uint32_t *look_back, uint64_t tiles, uint64_t elements)
 {
     RestArea a;
     a.rows = look_back;
+    a.max_rows = (uint32_t)std::min<uint64_t>(2 * tiles, 0xFFFFFFFFu);
     a.cap = (uint32_t)std::min<uint64_t>(64 * tiles, 0xFFFFFFFFu);
     a.runs = (uint4 *)(a.rows + 2 * tiles * kRadix);
     a.list = (uint2 *)(a.runs + a.cap);
-    a.words = (uint32_t *)(a.list + a.cap);
+    a.row_run = (uint32_t *)(a.list + a.cap);
+    a.words = a.row_run + 2 * tiles;
     a.num_words = kRestTaken + (uint32_t)(elements / (32 * kWave)) + 1;
     return a;
 }
@@ -445,21 +452,40 @@ __device__ __forceinline__ void rest_find(const RunArray<K, V> &arr, uint2 entry
     const uint32_t back = run_reach<true>(arr.k, arr.n, entry.x, arr.shift, arr.map, lead, lane);
     const uint32_t ahead = run_reach<false>(arr.k, arr.n, entry.x, arr.shift, arr.map, lead, lane);
     const uint32_t start = entry.x - back, m = back + 1 + ahead;
-    if (lane != 0)
-        return;
     // runs listed are longer than 64, so no two start among the same 64
     const uint64_t bit = (arr.base + start) / kWave;
     const uint32_t mask = 1u << (bit % 32);
-    if (atomicOr(&rest.words[kRestTaken + bit / 32], mask) & mask)
+    uint32_t taken = 0;
+    if (lane == 0)
+        taken = atomicOr(&rest.words[kRestTaken + bit / 32], mask) & mask;
+    if (__builtin_amdgcn_readfirstlane(taken))
         return;
-    const uint4 run = make_uint4(start, m, entry.y, 0);
+    uint4 run = make_uint4(start, m, entry.y, 0);
     if (m <= kRestWaveRun) {
-        rest.runs[atomicAdd(&rest.words[kRestShortLen], 1u)] = run;
-    } else {
-        rest.runs[rest.cap - 1 - atomicAdd(&ctrl[kCtrlLongerLen], 1u)] = run;
-        if (m > tile)
-            __hip_atomic_store(&ctrl[kCtrlGiant], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        if (lane == 0)
+            rest.runs[atomicAdd(&rest.words[kRestShortLen], 1u)] = run;
+        return;
     }
+    uint32_t idx = 0, row = 0;
+    const uint32_t rows = m > tile ? (m + tile - 1) / tile : 0u;
+    if (lane == 0) {
+        idx = atomicAdd(&ctrl[kCtrlLongerLen], 1u);
+        if (rows) {
+            row = atomicAdd(&rest.words[kRestRows], rows);
+            atomicAdd(&ctrl[kCtrlGiant], 1u);
+        }
+    }
+    idx = __builtin_amdgcn_readfirstlane(idx);
+    row = __builtin_amdgcn_readfirstlane(row);
+    // only overlapping segments can need more rows than there are: such a run
+    // keeps its rows but nothing is sorted
+    if (rows && (uint64_t)row + rows > rest.max_rows)
+        run.y = 0;
+    run.w = row;
+    for (uint32_t j = lane; j < rows && (uint64_t)row + j < rest.max_rows; j += kWave)
+        rest.row_run[row + j] = idx;
+    if (lane == 0)
+        rest.runs[rest.cap - 1 - idx] = run;
 }
 
 // Writes a run of m <= 64 SLOTS elements, in registers (element s*64 + lane
@@ -555,14 +581,17 @@ __device__ __forceinline__ uint32_t rest_by_waves(RestShared &S, uint32_t *claim
 
 // The runs out of order, by every workgroup of the launch: all look up where
 // the sweep reported one and wait for each other; then waves take the shorter
-// runs and workgroups the longer ones.  If a run is longer than a tile, or
-// there are too many, nothing is sorted and the result is true: everything has
-// to be sorted again (every workgroup gets the same answer).  resolve(segment)
-// is the array that holds a run.
+// runs and workgroups the longer ones, up to a tile.  Returns the rows of the
+// runs longer than that, which are left to sort_again, or kRestAll if there
+// are too many runs and everything is (every workgroup gets the same answer).
+// resolve(segment) is the array that holds a run.
+constexpr uint32_t kRestAll = 0xFFFFFFFFu;
+
 template <typename K, typename V, bool HAS_V, typename C, typename Resolve>
-__device__ __forceinline__ bool rest_runs(BlockLds<K, HAS_V, C::kThreads, C::kItems> &L,
-                                          RestShared &S, uint32_t *ctrl, const RestArea &rest,
-                                          const PassArgs &wait, Resolve &&resolve)
+__device__ __forceinline__ uint32_t rest_runs(BlockLds<K, HAS_V, C::kThreads, C::kItems> &L,
+                                              RestShared &S, uint32_t *ctrl,
+                                              const RestArea &rest, const PassArgs &wait,
+                                              Resolve &&resolve)
 {
     constexpr uint32_t T = C::kTile;
     constexpr int THREADS = C::kThreads;
@@ -570,7 +599,7 @@ __device__ __forceinline__ bool rest_runs(BlockLds<K, HAS_V, C::kThreads, C::kIt
     const uint32_t t = threadIdx.x;
     const uint32_t len = __builtin_amdgcn_readfirstlane(ctrl[kCtrlUnsorted]);
     if (len > rest.cap)
-        return true;
+        return kRestAll;
     const uint32_t found =
         rest_by_waves<THREADS>(S, &rest.words[kRestFindClaim], len, [&](uint32_t i) {
             const uint2 entry = rest.list[i];
@@ -582,15 +611,14 @@ __device__ __forceinline__ bool rest_runs(BlockLds<K, HAS_V, C::kThreads, C::kIt
     }
     __syncthreads();
     if (!S.ok)
-        return false;
+        return 0;
     const auto count = [](uint32_t *word) {
         return __builtin_amdgcn_readfirstlane(
             __hip_atomic_load(word, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
     };
-    if (count(&ctrl[kCtrlGiant]))
-        return true;
     const uint32_t shorts = count(&rest.words[kRestShortLen]);
     const uint32_t longer = count(&ctrl[kCtrlLongerLen]);
+    const uint32_t rows = min(count(&rest.words[kRestRows]), rest.max_rows);
     rest_by_waves<THREADS>(S, &rest.words[kRestShortClaim], shorts, [&](uint32_t i) {
         const uint4 run = rest.runs[i];
         rest_wave_run<K, V, HAS_V>(resolve(run.z), run);
@@ -602,8 +630,10 @@ __device__ __forceinline__ bool rest_runs(BlockLds<K, HAS_V, C::kThreads, C::kIt
         __syncthreads();
         const uint32_t item = __builtin_amdgcn_readfirstlane(S.item);
         if (item >= longer)
-            return false;
+            break;
         const uint4 run = rest.runs[rest.cap - 1 - item];
+        if (__builtin_amdgcn_readfirstlane(run.y) > T)
+            continue;
         const RunArray<K, V> arr = resolve(run.z);
         K *rk = arr.k + run.x;
         V *rv = HAS_V ? arr.v + run.x : nullptr;
@@ -625,6 +655,8 @@ __device__ __forceinline__ bool rest_runs(BlockLds<K, HAS_V, C::kThreads, C::kIt
             }
         });
     }
+    __syncthreads();
+    return rows;
 }
 
 // The next item of stages of `tiles` items each, or false when there is none
@@ -668,7 +700,8 @@ __device__ __forceinline__ bool rest_next(RestItem &it, RestShared &S, uint32_t 
 
 // An array to sort again by every digit in `digits`: its buffers (it lies in the
 // first of each, and ends there), its length, its first row, the digits that
-// are skewed, the key order of the stored keys, and every digit's offsets.
+// are skewed, the key order of the stored keys, and every digit's offsets (null:
+// they are counted).
 template <typename K, typename V>
 struct AgainArray {
     K *k[2];
@@ -682,9 +715,10 @@ struct AgainArray {
 };
 
 // Sorts arrays again, in `rows` rows of a tile each; resolve(row) is the array
-// of a row.  Two stages a digit, one that clears the rows' look-back words and a
-// pass; the lowest digit twice if their number is odd, so that the result ends
-// where it began (sorting by a digit twice changes nothing).
+// of a row.  Two stages a digit, one that clears the rows' look-back words (or
+// counts their digits) and a pass; the lowest digit twice if their number is
+// odd, so that the result ends where it began (sorting by a digit twice changes
+// nothing).
 template <typename K, typename V, bool HAS_V, typename C, typename Resolve>
 __device__ __forceinline__ void sort_again(PassLds<K, C, HAS_V> &L, RestShared &S,
                                            const RestArea &rest, uint32_t rows,
@@ -707,12 +741,6 @@ __device__ __forceinline__ void sort_again(PassLds<K, C, HAS_V> &L, RestShared &
             __syncthreads();
             continue;
         }
-        if (it.stage % 2 == 0) {
-            for (uint32_t i = t; i < NB; i += THREADS)
-                rest.rows[(uint64_t)it.tile * NB + i] = 0;
-            __syncthreads();
-            continue;
-        }
         uint32_t left = a.digits;
         for (uint32_t i = q & 1; i < set; ++i)
             left &= left - 1;
@@ -720,13 +748,55 @@ __device__ __forceinline__ void sort_again(PassLds<K, C, HAS_V> &L, RestShared &
         const uint32_t from = set & 1, into = from ^ 1;
         const uint32_t tb = (it.tile - a.first) * T;
         const uint32_t valid = a.n > tb ? min(T, a.n - tb) : 0u;
-        const uint32_t dbase = t < NB ? a.base[digit * NB + t] : 0u;
+        const uint32_t map_load = set == 0 ? a.map : 0u;
+        if (it.stage % 2 == 0) {
+            uint32_t sum = 0;
+            if (!a.base) {
+                uint32_t *wc = L.wcnt + t / kWave * NB;  // a wave's own
+                for (uint32_t i = t % kWave; i < NB; i += kWave)
+                    wc[i] = 0;
+                wave_lds_fence();
+                for (uint32_t e = t; e < valid; e += THREADS)
+                    atomicAdd(&wc[digit_of<R>(map_in(a.k[from][tb + e], map_load), digit * R)],
+                              1u);
+                __syncthreads();
+                if (t < NB) {
+                    for (uint32_t w = 0; w < THREADS / kWave; ++w)
+                        sum += L.wcnt[w * NB + t];
+                    sum |= kFlagAgg;
+                }
+            }
+            if (t < NB)
+                rest.rows[(uint64_t)it.tile * NB + t] = sum;
+            __syncthreads();
+            continue;
+        }
+        uint32_t dbase = 0;
+        if (a.base) {
+            dbase = t < NB ? a.base[digit * NB + t] : 0u;
+        } else {
+            // every row has its counts: their sum is the look-back from the end
+            const uint32_t end = a.first + (a.n + T - 1) / T;
+            const uint32_t total =
+                t < NB ? lookback_digit<16, C::kGroup>(rest.rows, nullptr, NB, t, end, a.first, wait)
+                       : 0u;
+            dbase = bins_exclusive_scan<NB>(total, L.tmp);
+        }
         pass_tile<K, V, HAS_V, C>(L, a.k[from] + tb, HAS_V ? a.v[from] + tb : nullptr, a.k[into],
                                   HAS_V ? a.v[into] : nullptr, valid, a.n, it.tile, a.first,
                                   rest.rows, nullptr, dbase, (int)digit * R,
-                                  ((a.skew >> digit) & 1u) != 0, set == 0 ? a.map : 0u,
+                                  ((a.skew >> digit) & 1u) != 0, map_load,
                                   set + 1 == sets ? a.map : 0u, wait, [](uint32_t) {});
     }
+}
+
+// The run of a row of sort_again (uniform).
+__device__ __forceinline__ uint4 rest_row(const RestArea &rest, uint32_t row)
+{
+    const uint4 run = rest.runs[rest.cap - 1 - rest.row_run[row]];
+    return make_uint4(
+        __builtin_amdgcn_readfirstlane(run.x), __builtin_amdgcn_readfirstlane(run.y),
+        __builtin_amdgcn_readfirstlane(run.z), __builtin_amdgcn_readfirstlane(run.w));
 }
 
 // One launch of persistent workgroups.  Work is claimed in order, (stage,
@@ -763,16 +833,31 @@ __global__ __launch_bounds__(C::kThreads) void k_last(LastArgs a)
     K *bk = pick<K>(a.p.b, buf, false);
     V *bv = HAS_V ? pick<V>(a.p.b, buf, true) : nullptr;
     const uint32_t low = digits & ((1u << (shift / C::kRadixBits)) - 1u);
-    if (!rest_runs<K, V, HAS_V, C>(
-            L.block, S, ctrl, a.rest, a.p,
-            [=](uint32_t) { return RunArray<K, V>{bk, bv, n, shift, low, map, 0}; }))
+    const uint32_t rows =
+        rest_runs<K, V, HAS_V, C>(L.block, S, ctrl, a.rest, a.p, [=](uint32_t) {
+            return RunArray<K, V>{bk, bv, n, shift, low, map, 0};
+        });
+    if (rows == 0)
         return;
     const uint32_t other = buf == kBufOut ? kBufTmp : kBufOut;
     K *ok = pick<K>(a.p.b, other, false);
     V *ov = HAS_V ? pick<V>(a.p.b, other, true) : nullptr;
     const uint32_t skew = __builtin_amdgcn_readfirstlane(ctrl[kCtrlSkew]);
-    sort_again<K, V, HAS_V, C>(L.pass, S, a.rest, a.p.num_tiles, a.p, [=](uint32_t) {
-        return AgainArray<K, V>{{bk, ok}, {bv, ov}, n, 0, digits, skew, map, a.p.digit_base};
+    const bool all = rows == kRestAll;
+    const RestArea rest = a.rest;
+    const uint32_t *base = a.p.digit_base;
+    sort_again<K, V, HAS_V, C>(L.pass, S, rest, all ? a.p.num_tiles : rows, a.p, [=](uint32_t row) {
+        if (all)
+            return AgainArray<K, V>{{bk, ok}, {bv, ov}, n, 0, digits, skew, map, base};
+        const uint4 run = rest_row(rest, row);
+        return AgainArray<K, V>{{bk + run.x, ok + run.x},
+                                {HAS_V ? bv + run.x : nullptr, HAS_V ? ov + run.x : nullptr},
+                                run.y,
+                                run.w,
+                                low,
+                                skew,
+                                map,
+                                nullptr};
     });
 }
 
@@ -864,7 +949,8 @@ __global__ __launch_bounds__(C::kThreads) void k_seg_last(SegLastArgs a)
     const auto uniform = [](uint32_t x) {
         return (uint32_t)__builtin_amdgcn_readfirstlane(x);
     };
-    if (!rest_runs<K, V, HAS_V, C>(L.block, S, ctrl, a.rest, wait, [=](uint32_t seg) {
+    const uint32_t rows =
+        rest_runs<K, V, HAS_V, C>(L.block, S, ctrl, a.rest, wait, [=](uint32_t seg) {
             const SegLarge rec = large[seg];
             const uint32_t flags = seg_flags[seg];
             const SegMoves m = seg_moves<K, R>(flags, in_place);
@@ -876,28 +962,33 @@ __global__ __launch_bounds__(C::kThreads) void k_seg_last(SegLastArgs a)
                                   uniform(~flags & ((1u << m.low) - 1u)),
                                   buf == kBufOut ? kmap : 0u,
                                   rec.start};
-        }))
+        });
+    if (rows == 0)
         return;
 
-    // every segment that was swept is sorted again
+    // the runs longer than a tile, or every segment that was swept
+    const bool all = rows == kRestAll;
     const uint32_t tiles = std::min(ctrl[kSegTiles], a.p.max_tiles);
     const uint32_t *tile_seg = a.p.tile_seg, *seg_base = a.p.seg_base;
-    sort_again<K, V, HAS_V, C>(L.pass, S, a.rest, tiles, wait, [=](uint32_t tile) {
-        const uint32_t seg = tile_seg[tile];
+    const RestArea rest = a.rest;
+    sort_again<K, V, HAS_V, C>(L.pass, S, rest, all ? tiles : rows, wait, [=](uint32_t row) {
+        const uint4 run = all ? make_uint4(0, 0, tile_seg[row], 0) : rest_row(rest, row);
+        const uint32_t seg = run.z;
         const SegLarge rec = large[seg];
         const uint32_t flags = uniform(seg_flags[seg]);
         const SegMoves m = seg_moves<K, R>(flags, in_place);
         const uint32_t buf = m.dst(m.moves - 1), other = buf == kBufOut ? kBufTmp : kBufOut;
-        return AgainArray<K, V>{{pick<K>(b, buf, false) + rec.start,
-                                 pick<K>(b, other, false) + rec.start},
-                                {HAS_V ? pick<V>(b, buf, true) + rec.start : nullptr,
-                                 HAS_V ? pick<V>(b, other, true) + rec.start : nullptr},
-                                uniform(rec.size),
-                                uniform(rec.tile_start),
-                                m.low ? ~flags & ((1u << D) - 1u) : 0u,
+        const uint64_t at = rec.start + run.x;
+        const uint32_t digits = ~flags & ((1u << (all ? D : m.low)) - 1u);
+        return AgainArray<K, V>{{pick<K>(b, buf, false) + at, pick<K>(b, other, false) + at},
+                                {HAS_V ? pick<V>(b, buf, true) + at : nullptr,
+                                 HAS_V ? pick<V>(b, other, true) + at : nullptr},
+                                all ? uniform(rec.size) : run.y,
+                                all ? uniform(rec.tile_start) : run.w,
+                                m.low ? digits : 0u,
                                 flags >> kSegSkewShift,
                                 buf == kBufOut ? kmap : 0u,
-                                seg_base + (uint64_t)seg * D * NB};
+                                all ? seg_base + (uint64_t)seg * D * NB : nullptr};
     });
 }
 

@@ -7,7 +7,7 @@ import torch
 
 import datagen
 from test_gpu_finish import (ANY_FINISH, FINISH, GIANT, KINDS, LONG_LEN, LONGER_LEN, PASS_MASK,
-                             UNSORTED, clusters, dev, sort_checked)
+                             UNSORTED, batch_checked, clusters, dev, sort_checked)
 
 pytestmark = pytest.mark.gpu
 
@@ -114,3 +114,43 @@ def test_batch_with_more_places_than_the_list_holds(rs, oracle_lib, bits, pairs,
     assert w[PASS_MASK] & ANY_FINISH
     assert w[UNSORTED] > 64 * (keys.size // 16384 + len(parts) + 1)
     ctx.close()
+
+
+def giants(n, sizes, keep, seed, clear=0):
+    """Uniform 64-bit keys without the bits in `clear`, of which groups of `sizes`
+    share their top `keep` bits."""
+    g = np.random.RandomState(seed)
+    k = datagen.keys("uniform", n, 64, seed=seed)
+    at = g.permutation(n)
+    low = np.uint64((1 << (64 - keep)) - 1)
+    for size in sizes:
+        a, at = at[:size], at[size:]
+        k[a] = (k[a[0]] & ~low) | (k[a] & low)
+    return k & ~np.uint64(clear)
+
+
+# runs of a tile (16384 elements, 8192 pairs), one more, and several tiles: each is
+# sorted by its own lower digits, an odd number of them or an even one
+@pytest.mark.parametrize("clear", [0, 0xFF00])
+@pytest.mark.parametrize("in_place", [False, True])
+@pytest.mark.parametrize("order,descending", [("unsigned", False), ("signed", True)])
+@pytest.mark.parametrize("pairs", [False, True])
+def test_runs_longer_than_a_tile(rs, oracle_lib, pairs, order, descending, in_place, clear):
+    tile = 8192 if pairs else 16384
+    keys = giants(1 << 22, (tile, tile + 1, 5 * tile // 2, 300), 24, 31, clear)
+    print(f"case pairs={pairs} order={order} in_place={in_place} clear={clear}", flush=True)
+    w = sort_checked(rs, oracle_lib, keys, pairs, in_place, order, descending)
+    assert w[FINISH] & 1
+    # another key may share the first run's 24 bits
+    assert w[LONGER_LEN] == 3 and w[GIANT] in (2, 3)
+
+
+@pytest.mark.parametrize("in_place", [False, True])
+@pytest.mark.parametrize("pairs", [False, True])
+def test_segments_with_runs_longer_than_a_tile(rs, oracle_lib, pairs, in_place):
+    tile = 8192 if pairs else 16384
+    parts = [giants(1 << 22, (tile + 100,), 24, 41), datagen.keys("uniform", 20000, 64, seed=1),
+             giants(1 << 22, (tile + 1,), 24, 42, 0xFF0000)]
+    print(f"case pairs={pairs} in_place={in_place}", flush=True)
+    w = batch_checked(rs, oracle_lib, parts, pairs, in_place, "float", True)
+    assert w[LONGER_LEN] == 2 and w[GIANT] == 2
