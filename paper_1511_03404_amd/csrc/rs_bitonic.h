@@ -118,47 +118,6 @@ __device__ __forceinline__ void bitonic_wave(const TinyArgs &a, uint64_t start, 
     }
 }
 
-// The same segment by the wave's LDS radix sort, R slots of 64 elements.
-template <typename K, typename V, bool HAS_V, int R>
-__device__ __forceinline__ void radix_wave(WaveLds<K, HAS_V> &L, const TinyArgs &a,
-                                           uint64_t start, uint32_t m, uint32_t lane)
-{
-    const K *kin = (const K *)a.kin + start;
-    K key[R];
-    uint32_t pos[HAS_V ? R : 1], to[R];
-#pragma unroll
-    for (int j = 0; j < R; ++j) {
-        const uint32_t e = j * kWave + lane;
-        key[j] = e < m ? kin[e] : (K)0;
-        if constexpr (HAS_V)
-            pos[j] = e;
-    }
-    if (a.kmap) {
-#pragma unroll
-        for (int j = 0; j < R; ++j)
-            key[j] = map_in(key[j], a.kmap);
-    }
-    wave_sort<K, HAS_V, R>(L, key, pos, m, lane, to);
-    // every value is read before any is written (in place: vin == vout)
-    V val[HAS_V ? R : 1];
-    if constexpr (HAS_V) {
-        const V *vin = (const V *)a.vin + start;
-#pragma unroll
-        for (int j = 0; j < R; ++j)
-            val[j] = j * kWave + lane < m ? vin[pos[j]] : (V)0;
-    }
-    K *kout = (K *)a.kout + start;
-    V *vout = HAS_V ? (V *)a.vout + start : nullptr;
-#pragma unroll
-    for (int j = 0; j < R; ++j) {
-        if (j * kWave + lane < m) {
-            kout[to[j]] = map_out(key[j], a.kmap);
-            if constexpr (HAS_V)
-                vout[to[j]] = val[j];
-        }
-    }
-}
-
 // Persistent workgroups of 4 waves; each wave takes one tiny segment at a
 // time until the list is exhausted.
 template <typename K, typename V, bool HAS_V>
@@ -184,14 +143,16 @@ __global__ __launch_bounds__(256) void k_seg_bitonic(TinyArgs a)
             break;
         const uint64_t start = a.list[item].start;
         const uint32_t m = a.list[item].size;
+        const WaveData<K, V> in{(const K *)a.kin + start, (const V *)a.vin + (HAS_V ? start : 0),
+                                (K *)a.kout + start, (V *)a.vout + (HAS_V ? start : 0)};
         if (m <= (uint32_t)kWave)
             bitonic_wave<K, V, HAS_V>(a, start, m, lane);
         else if (m <= 256)
-            radix_wave<K, V, HAS_V, 4>(L, a, start, m, lane);
+            radix_wave<K, V, HAS_V, 4>(L, in, m, lane, a.kmap);
         else if (m <= 512)
-            radix_wave<K, V, HAS_V, 8>(L, a, start, m, lane);
+            radix_wave<K, V, HAS_V, 8>(L, in, m, lane, a.kmap);
         else
-            radix_wave<K, V, HAS_V, 16>(L, a, start, m, lane);
+            radix_wave<K, V, HAS_V, 16>(L, in, m, lane, a.kmap);
     }
 }
 

@@ -19,6 +19,7 @@
 
 #include "rs_kernels.h"
 #include "rs_runs.h"
+#include "rs_wave.h"
 
 namespace rs {
 
@@ -26,21 +27,23 @@ namespace rs {
 // the passes, which are done by then (rest_area).
 struct RestArea {
     uint32_t *rows;   // look-back words [row][256] of a sort again
-    uint32_t *row_run;  // the run of each row, as counted from the end of runs
+    uint32_t *row_run;  // the longer run of each row
     uint32_t max_rows;
-    uint4 *runs;      // runs to sort: start, length, segment, and its first row
-                      // if it is longer than a tile; from the front those for a
-                      // wave, from the end the longer ones
-    uint2 *list;      // where runs are out of order: element, segment
-    uint32_t cap;     // entries of each
+    // where runs are out of order: element, segment; once looked up, a run for
+    // a wave: start, length (0: none, or listed elsewhere), segment
+    uint4 *list;
+    uint32_t cap;
+    // longer runs: start, length, segment, and its first row if it is longer
+    // than a tile
+    uint4 *longer;
+    uint32_t max_longer;
     uint32_t *words;  // counters (kRest*), then a bit for every 64 elements: the
                       // run that starts among them has been taken
-    uint32_t num_words;  // (cleared by the sweep)
+    uint32_t num_words;  // (zero when the follow-up starts)
 };
 constexpr int kRestFindClaim = 0;   // entries of list claimed
 constexpr int kRestFindDone = 1;    // and looked up;
-constexpr int kRestShortLen = 2;    // runs for a wave: listed,
-constexpr int kRestShortClaim = 3;  // and claimed;
+constexpr int kRestShortClaim = 3;  // and claimed to sort the run for a wave
 constexpr int kRestLongerClaim = 4; // longer runs claimed
 constexpr int kRestItemClaim = 5;   // (stage, row) items claimed
 constexpr int kRestRows = 6;        // rows of the runs longer than a tile
@@ -48,21 +51,28 @@ constexpr int kRestStageDone = 8;   // [8, 24): items done per stage
 constexpr int kRestTaken = 32;
 
 // Lays the area out over the look-back words of `tiles` tiles, 256 a tile for
-// each of four or eight digits.  A tile holds at most 24576 elements, so the
-// bits take 12 words a tile, and with 512 for the rows (of runs longer than a
-// tile there are fewer than two for every whole tile they cover), 2 for their
-// map and 6 for each of 64 runs four digits' words hold it all.
-inline RestArea rest_area(uint32_t *look_back, uint64_t tiles, uint64_t elements)
+// each of four or eight digits.  Four digits' words hold it all: 512 a tile for
+// the rows (of runs longer than a tile there are fewer than two for every whole
+// tile they cover) and 256 for the places; then, in the last quarter, the
+// counters, 12 words a tile for the bits (a tile holds at most 24576 elements),
+// 192 for the runs of more than 512 elements and 2 for the rows' map.
+//
+// In a plain sort the counters and bits are zero already: they lie in the words
+// of the last pass slot, which k_hist has cleared and no pass has used if a sweep
+// follows.  A batch's sweep clears them.
+inline RestArea rest_area(uint32_t *look_back, int digits, uint64_t tiles, uint64_t elements)
 {
+    const auto u32 = [](uint64_t x) { return (uint32_t)std::min<uint64_t>(x, 0xFFFFFFFFu); };
     RestArea a;
     a.rows = look_back;
-    a.max_rows = (uint32_t)std::min<uint64_t>(2 * tiles, 0xFFFFFFFFu);
-    a.cap = (uint32_t)std::min<uint64_t>(64 * tiles, 0xFFFFFFFFu);
-    a.runs = (uint4 *)(a.rows + 2 * tiles * kRadix);
-    a.list = (uint2 *)(a.runs + a.cap);
-    a.row_run = (uint32_t *)(a.list + a.cap);
-    a.words = a.row_run + 2 * tiles;
+    a.max_rows = u32(2 * tiles);
+    a.cap = u32(64 * tiles);
+    a.list = (uint4 *)(a.rows + 2 * tiles * kRadix);
+    a.words = look_back + (digits - 1) * tiles * kRadix;
     a.num_words = kRestTaken + (uint32_t)(elements / (32 * kWave)) + 1;
+    a.max_longer = u32(48 * tiles);
+    a.longer = (uint4 *)(a.words + (a.num_words + 3) / 4 * 4);
+    a.row_run = (uint32_t *)(a.longer + a.max_longer);
     return a;
 }
 
@@ -90,6 +100,13 @@ constexpr uint32_t kFinishFused = 1u << 20;
 // per lane cost more than the count (2^25 64-bit keys, runs of 2: 137 us, now
 // 117 us, 4.6 TB/s; 2^20 32-bit keys, runs of 16: 17.8 us, now 10.3 us).  It
 // is bound by the compares (VALU) for runs of 4 and more, by HBM below.
+//
+// The sweeps are held to 80 scalar registers: 16 are set aside for
+// each wave, and with 96 and those only 7 waves fit a SIMD, not 8, so that the
+// grid's last workgroups start when the first have ended (2^25 64-bit keys: 128
+// us, 113 with 80).
+#define RS_FINISH_SGPRS __attribute__((amdgpu_num_sgpr(80)))
+constexpr uint32_t kFinishPend = 16;
 template <typename K, int THREADS, int ITEMS>
 struct FinishLds {
     static constexpr uint32_t T = THREADS * ITEMS;
@@ -100,64 +117,79 @@ struct FinishLds {
     // chunks before and after the tile.  The same for the words of adjacent
     // elements out of order.
     uint64_t head[2 * W + 2], inv[2 * W + 2];
-    uint32_t longs;    // longer runs met
-    uint32_t pending;  // places reported; the first ones wait here
-    uint2 pend[kWave];
+    uint2 pend[W][kFinishPend];  // places that each wave has to report
+    uint32_t count[W], longs[W];
+    uint32_t done;  // waves that have written theirs
 };
 
-// The workgroup's part in clearing the follow-up's counters, and the start of
-// its own (the first tile's barriers come before their use).
-template <typename K, int THREADS, int ITEMS>
-__device__ __forceinline__ void finish_begin(FinishLds<K, THREADS, ITEMS> &L, const RestArea &rest)
-{
-    if (threadIdx.x == 0) {
-        L.longs = 0;
-        L.pending = 0;
-    }
-    for (uint32_t i = blockIdx.x * THREADS + threadIdx.x; i < rest.num_words;
-         i += gridDim.x * THREADS)
-        rest.words[i] = 0;
-}
+// What a wave has found in its tiles (uniform): places where a longer run is
+// out of order, and longer runs.
+struct FinishFound {
+    uint32_t places = 0;
+    uint32_t longs = 0;
+};
 
-// Reports that element i of segment seg is smaller than the one before it, in
-// a run that is too long to be ordered here.  Reports wait in LDS for the
-// workgroup's end: atomics on one word end one after another, 14 ns apart
-// (2^25 64-bit keys, 100 of each: with an atomic for each of 335,000 long runs
-// the sweep took 5 ms).
+// The wave reports that element i of segment seg is smaller than the one before
+// it, in a run that is too long to be ordered here.  The first reports wait in
+// LDS for the workgroup's end: atomics on one word end one after another, 14 ns
+// apart (2^25 64-bit keys, 100 of each: with an atomic for each of 335,000 long
+// runs the sweep took 5 ms).
 template <typename K, int THREADS, int ITEMS>
 __device__ __forceinline__ void finish_report(FinishLds<K, THREADS, ITEMS> &L, uint32_t *ctrl,
-                                              const RestArea &rest, uint32_t i, uint32_t seg)
+                                              const RestArea &rest, FinishFound &found, uint32_t i,
+                                              uint32_t seg)
 {
-    const uint32_t slot = atomicAdd(&L.pending, 1u);
-    if (slot < (uint32_t)kWave) {
-        L.pend[slot] = make_uint2(i, seg);
-    } else {
-        const uint32_t l = atomicAdd(&ctrl[kCtrlUnsorted], 1u);
-        if (l < rest.cap)
-            rest.list[l] = make_uint2(i, seg);
+    if (threadIdx.x % kWave == 0) {
+        if (found.places < kFinishPend) {
+            L.pend[threadIdx.x / kWave][found.places] = make_uint2(i, seg);
+        } else {
+            const uint32_t l = atomicAdd(&ctrl[kCtrlUnsorted], 1u);
+            if (l < rest.cap)
+                rest.list[l] = make_uint4(i, seg, 0, 0);
+        }
     }
+    ++found.places;
 }
 
-// After the last tile's barrier.
+// After the last tile.  The workgroup's last wave lists what all have found: no
+// barrier, which would make every wave wait for the slowest.  (L.done was zero
+// before a barrier.)
 template <typename K, int THREADS, int ITEMS>
 __device__ __forceinline__ void finish_end(FinishLds<K, THREADS, ITEMS> &L, uint32_t *ctrl,
-                                           const RestArea &rest)
+                                           const RestArea &rest, const FinishFound &found)
 {
-    __syncthreads();  // there may have been no tile
-    const uint32_t t = threadIdx.x;
-    if (t >= (uint32_t)kWave)
-        return;
-    const uint32_t count = min(L.pending, (uint32_t)kWave);
-    if (count) {
-        uint32_t l = 0;
-        if (t == 0)
-            l = atomicAdd(&ctrl[kCtrlUnsorted], count);
-        l = __builtin_amdgcn_readfirstlane(l) + t;
-        if (t < count && l < rest.cap)
-            rest.list[l] = L.pend[t];
+    constexpr uint32_t W = THREADS / kWave;
+    const uint32_t lane = threadIdx.x % kWave;
+    uint32_t done = 0;
+    if (lane == 0) {
+        const uint32_t w = threadIdx.x / kWave;
+        L.count[w] = min(found.places, kFinishPend);
+        L.longs[w] = found.longs;
+        done = __hip_atomic_fetch_add(&L.done, 1u, __ATOMIC_ACQ_REL, __HIP_MEMORY_SCOPE_WORKGROUP);
     }
-    if (t == 0 && L.longs)
-        atomicAdd(&ctrl[kCtrlLongLen], L.longs);
+    if (__builtin_amdgcn_readfirstlane(done) != W - 1)
+        return;
+    // a lane for each wave, then for each of its places
+    const uint32_t count = lane < W ? L.count[lane] : 0u;
+    const uint32_t met = lane < W ? L.longs[lane] : 0u;
+    if (__builtin_expect(__ballot(count | met) == 0, 1))
+        return;
+    const uint32_t upto = wave_inclusive_scan(count);
+    const uint32_t longs = wave_inclusive_scan(met);
+    uint32_t base = 0;
+    if (lane == kWave - 1) {
+        if (upto)
+            base = atomicAdd(&ctrl[kCtrlUnsorted], upto);
+        if (longs)
+            atomicAdd(&ctrl[kCtrlLongLen], longs);
+    }
+    base = __builtin_amdgcn_readlane(base, kWave - 1);
+    for (uint32_t w = 0; w < W; ++w) {
+        const uint32_t c = __builtin_amdgcn_readlane(count, w);
+        const uint32_t l = base + __builtin_amdgcn_readlane(upto, w) - c + lane;
+        if (lane < c && l < rest.cap)
+            rest.list[l] = make_uint4(L.pend[w][lane].x, L.pend[w][lane].y, 0, 0);
+    }
 }
 
 // The tile of an array of n elements that starts at tb: from sk, sv to dk,
@@ -166,7 +198,8 @@ __device__ __forceinline__ void finish_end(FinishLds<K, THREADS, ITEMS> &L, uint
 template <typename K, typename V, bool HAS_V, int THREADS, int ITEMS, typename Report>
 __device__ __forceinline__ void finish_tile(FinishLds<K, THREADS, ITEMS> &L, const K *sk,
                                             const V *sv, K *dk, V *dv, uint32_t n, uint32_t tb,
-                                            int shift, uint32_t map, Report &&report)
+                                            int shift, uint32_t map, uint32_t &longs,
+                                            Report &&report)
 {
     constexpr uint32_t T = THREADS * ITEMS;
     constexpr uint32_t H = kWave;
@@ -262,27 +295,25 @@ __device__ __forceinline__ void finish_tile(FinishLds<K, THREADS, ITEMS> &L, con
     for (int j = 0; j < ITEMS; ++j) {
         const uint32_t e = e0 + j * kWave;
         const uint32_t at = H + e;  // this element's LDS slot
-        const uint32_t pos0 = tb + e;
-        uint32_t pos = pos0;
+        uint32_t pos = tb + e;
         const uint64_t here = head[j + 1], prev = head[j], next = head[j + 2];
         // nothing adjacent out of order in the three chunks: in place
         if ((inv[j] | inv[j + 1] | inv[j + 2]) != 0) {
             bool whole;
             pos += (uint32_t)run_move(s_k, at, key[j], lane, here, prev, next, &whole);
-            // elements of longer runs below the one before them: in the run
-            // that comes in from the chunk before, unless that chunk has seen
-            // one in it too, and in the one that goes on into the next
+            // elements of longer runs that are below the one before them: in the
+            // run that comes in from the chunk before, unless that chunk has
+            // seen one in it too, and in the one that goes on into the next
             const uint64_t low = inv[j + 1] & __ballot(!whole);
-            if (low) {
+            if (__builtin_expect(low != 0, 0)) {
                 const uint64_t in = here ? (here & (0 - here)) - 1 : ~0ull;
                 const uint64_t tail = prev ? ~0ull << (kWave - 1 - __builtin_clzll(prev)) : ~0ull;
                 const uint64_t first = inv[j] & tail ? 0ull : low & in, last = low & ~in;
-                if (lane == 0) {
-                    if (first)
-                        report(pos0 + (uint32_t)__builtin_ctzll(first));
-                    if (last)
-                        report(pos0 + (uint32_t)__builtin_ctzll(last));
-                }
+                const uint32_t c = tb + (w * ITEMS + j) * kWave;
+                if (first)
+                    report(c + (uint32_t)__builtin_ctzll(first));
+                if (last)
+                    report(c + (uint32_t)__builtin_ctzll(last));
             }
         }
         if (pos < n && (full || tb + e < n)) {
@@ -292,9 +323,8 @@ __device__ __forceinline__ void finish_tile(FinishLds<K, THREADS, ITEMS> &L, con
         }
         // runs that are too long, in order or not
         const uint32_t ends = here ? __builtin_clzll(here) : 0;
-        if (here && ends + (next ? __builtin_ctzll(next) : kWave) >= kRunMax &&
-            lane == kWave - 1 - ends && pos0 < n)
-            atomicAdd(&L.longs, 1u);
+        if (here && ends + (next ? __builtin_ctzll(next) : kWave) >= kRunMax)
+            ++longs;
     }
     __syncthreads();  // the next tile overwrites the LDS
 }
@@ -312,17 +342,21 @@ __device__ __forceinline__ void finish_all(FinishLds<K, THREADS, ITEMS> &L, Fini
     const V *sv = HAS_V ? pick<const V>(a.b, src, true) : nullptr;
     K *dk = pick<K>(a.b, dst, false);
     V *dv = HAS_V ? pick<V>(a.b, dst, true) : nullptr;
-    finish_begin(L, a.rest);
     const uint32_t tiles = (a.n + T - 1) / T;
+    if (blockIdx.x >= tiles)
+        return;
+    if (threadIdx.x == 0)
+        L.done = 0;
+    FinishFound found;
     for (uint32_t tile = blockIdx.x; tile < tiles; tile += gridDim.x)
         finish_tile<K, V, HAS_V, THREADS, ITEMS>(
-            L, sk, sv, dk, dv, a.n, tile * T, shift, map,
-            [&](uint32_t i) { finish_report(L, a.ctrl, a.rest, i, 0); });
-    finish_end(L, a.ctrl, a.rest);
+            L, sk, sv, dk, dv, a.n, tile * T, shift, map, found.longs,
+            [&](uint32_t i) { finish_report(L, a.ctrl, a.rest, found, i, 0); });
+    finish_end(L, a.ctrl, a.rest, found);
 }
 
 template <typename K, typename V, bool HAS_V, int THREADS, int ITEMS>
-__global__ __launch_bounds__(THREADS) void k_finish(FinishArgs a)
+__global__ __launch_bounds__(THREADS) RS_FINISH_SGPRS void k_finish(FinishArgs a)
 {
     __shared__ FinishLds<K, THREADS, ITEMS> L;
     const uint32_t word = __builtin_amdgcn_readfirstlane(a.ctrl[kCtrlFinish]);
@@ -407,151 +441,101 @@ struct RunArray {
     uint64_t base;
 };
 
-// How far element p's run reaches back (BACK) or ahead, by the whole wave: 64
-// probes at a time, at distances that grow 64-fold until one leaves the run
-// and shrink again.
-template <bool BACK, typename K>
-__device__ __forceinline__ uint32_t run_reach(const K *k, uint32_t n, uint32_t p, int shift,
-                                              uint32_t map, K lead, uint32_t lane)
+// The ends of element p's run, by the whole wave: 64 probes at a time on either
+// side, 8 elements apart at first (one trip finds a run of 512), at distances
+// that grow 64-fold until one leaves the run and then shrink.
+template <typename K, typename V>
+__device__ __forceinline__ uint2 run_ends(const RunArray<K, V> &arr, uint32_t p, uint32_t lane)
 {
-    const uint32_t room = BACK ? p : n - 1 - p;
-    uint32_t far = 0;
-    uint64_t step = 1;
-    bool grow = true;
-    while (true) {
-        const uint64_t d = far + step * (lane + 1);
-        const bool in = d <= room && (map_in(k[BACK ? p - d : p + d], map) >> shift) == lead;
-        const uint64_t out = ~__ballot(in);
-        const uint32_t c = out ? (uint32_t)__builtin_ctzll(out) : (uint32_t)kWave;
-        far += (uint32_t)step * c;
-        if (c == (uint32_t)kWave && grow) {
-            step *= kWave;
-            continue;
+    const K lead = map_in(arr.k[p], arr.map) >> arr.shift;
+    const uint32_t room[2] = {p, arr.n - 1 - p};
+    uint32_t far[2] = {0, 0}, step[2] = {8, 8};  // step 0: found
+    bool grow[2] = {true, true};
+    while (step[0] | step[1]) {
+        K x[2];
+        bool in[2];
+#pragma unroll
+        for (int i = 0; i < 2; ++i) {
+            const uint64_t d = far[i] + (uint64_t)step[i] * (lane + 1);
+            in[i] = step[i] && d <= room[i];
+            x[i] = in[i] ? arr.k[i ? p + d : p - d] : (K)0;
         }
-        grow = false;
-        if (step == 1)
-            return far;
-        step /= kWave;
+#pragma unroll
+        for (int i = 0; i < 2; ++i) {
+            const uint64_t out = ~__ballot(in[i] && (map_in(x[i], arr.map) >> arr.shift) == lead);
+            const uint32_t c = out ? (uint32_t)__builtin_ctzll(out) : (uint32_t)kWave;
+            far[i] += step[i] * c;
+            grow[i] = grow[i] && c == (uint32_t)kWave;
+            step[i] = grow[i] ? step[i] * kWave : step[i] == 1 ? 0u : (step[i] + kWave - 1) / kWave;
+        }
     }
+    return make_uint2(p - far[0], p + far[1] + 1);
 }
 
-// Runs of up to kRestWaveRun elements are sorted by a wave each, in
-// registers: every element counts the run's elements that go before it, the
-// run's keys broadcast one after another.
-constexpr uint32_t kRestSlots = 8;
-constexpr uint32_t kRestWaveRun = kRestSlots * kWave;
+// Runs of up to kRestWaveRun elements are sorted by a wave each, in its LDS.
+// (In registers, each element counting the run's keys as they are broadcast,
+// a run of 200 64-bit keys took 20 us; now 4.)
+constexpr uint32_t kRestWaveRun = 512;
 
-// One place where a run is out of order: finds the run and, if no other place
-// of it was first, lists it.  By one wave.
-template <typename K, typename V>
-__device__ __forceinline__ void rest_find(const RunArray<K, V> &arr, uint2 entry, uint32_t tile,
-                                          uint32_t *ctrl, const RestArea &rest)
+// One place where a run is out of order, entry i of the list: finds the run and,
+// if no other place of it was first, makes it the wave's entry or lists it with
+// the longer ones.  By one wave.  (Listed by an atomic on one word, 11,700 runs
+// took 165 us of a batch's 640.)
+template <typename K, typename V, typename Resolve>
+__device__ __forceinline__ void rest_find(uint32_t i, uint32_t tile, uint32_t *ctrl,
+                                          const RestArea &rest, Resolve &&resolve)
 {
     const uint32_t lane = threadIdx.x % kWave;
-    const K lead = map_in(arr.k[entry.x], arr.map) >> arr.shift;
-    const uint32_t back = run_reach<true>(arr.k, arr.n, entry.x, arr.shift, arr.map, lead, lane);
-    const uint32_t ahead = run_reach<false>(arr.k, arr.n, entry.x, arr.shift, arr.map, lead, lane);
-    const uint32_t start = entry.x - back, m = back + 1 + ahead;
+    const uint4 entry = rest.list[i];
+    const RunArray<K, V> arr = resolve(entry.y);
+    const uint2 ends = run_ends(arr, entry.x, lane);
+    uint4 run = make_uint4(ends.x, ends.y - ends.x, entry.y, 0);
     // runs listed are longer than 64, so no two start among the same 64
-    const uint64_t bit = (arr.base + start) / kWave;
+    const uint64_t bit = (arr.base + run.x) / kWave;
     const uint32_t mask = 1u << (bit % 32);
     uint32_t taken = 0;
     if (lane == 0)
         taken = atomicOr(&rest.words[kRestTaken + bit / 32], mask) & mask;
-    if (__builtin_amdgcn_readfirstlane(taken))
+    taken = __builtin_amdgcn_readfirstlane(taken);
+    const bool longer = run.y > kRestWaveRun;
+    if (lane == 0)
+        rest.list[i] = make_uint4(run.x, taken || longer ? 0u : run.y, run.z, 0);
+    if (taken || !longer)
         return;
-    uint4 run = make_uint4(start, m, entry.y, 0);
-    if (m <= kRestWaveRun) {
-        if (lane == 0)
-            rest.runs[atomicAdd(&rest.words[kRestShortLen], 1u)] = run;
-        return;
-    }
-    uint32_t idx = 0, row = 0;
-    const uint32_t rows = m > tile ? (m + tile - 1) / tile : 0u;
-    if (lane == 0) {
+    uint32_t idx = 0;
+    if (lane == 0)
         idx = atomicAdd(&ctrl[kCtrlLongerLen], 1u);
-        if (rows) {
-            row = atomicAdd(&rest.words[kRestRows], rows);
+    idx = __builtin_amdgcn_readfirstlane(idx);
+    // only overlapping segments can need more room than there is: then such a
+    // run is not sorted
+    if (idx >= rest.max_longer)
+        return;
+    const uint32_t rows = run.y > tile ? (run.y + tile - 1) / tile : 0u;
+    if (rows) {
+        if (lane == 0) {
+            run.w = atomicAdd(&rest.words[kRestRows], rows);
             atomicAdd(&ctrl[kCtrlGiant], 1u);
         }
+        run.w = __builtin_amdgcn_readfirstlane(run.w);
+        if ((uint64_t)run.w + rows > rest.max_rows)
+            run.y = 0;
     }
-    idx = __builtin_amdgcn_readfirstlane(idx);
-    row = __builtin_amdgcn_readfirstlane(row);
-    // only overlapping segments can need more rows than there are: such a run
-    // keeps its rows but nothing is sorted
-    if (rows && (uint64_t)row + rows > rest.max_rows)
-        run.y = 0;
-    run.w = row;
-    for (uint32_t j = lane; j < rows && (uint64_t)row + j < rest.max_rows; j += kWave)
-        rest.row_run[row + j] = idx;
+    for (uint32_t j = lane; j < rows && (uint64_t)run.w + j < rest.max_rows; j += kWave)
+        rest.row_run[run.w + j] = idx;
     if (lane == 0)
-        rest.runs[rest.cap - 1 - idx] = run;
-}
-
-// Writes a run of m <= 64 SLOTS elements, in registers (element s*64 + lane
-// in slot s), back in order.
-template <typename K, typename V, bool HAS_V, uint32_t SLOTS>
-__device__ __forceinline__ void rest_place(K *rk, V *rv, uint32_t map, uint32_t m,
-                                           const K (&x)[kRestSlots],
-                                           const V (&v)[HAS_V ? kRestSlots : 1])
-{
-    const uint32_t lane = threadIdx.x % kWave;
-    uint32_t before[SLOTS] = {};
-#pragma unroll
-    for (uint32_t j = 0; j < SLOTS; ++j) {
-        const uint32_t end = m > j * kWave ? min(m - j * kWave, (uint32_t)kWave) : 0u;
-        for (uint32_t l = 0; l < end; ++l) {
-            const K k = read_lane(x[j], l);
-#pragma unroll
-            for (uint32_t s = 0; s < SLOTS; ++s) {
-                // an equal key goes first if it came first
-                const bool first = s > j || (s == j && l < lane);
-                before[s] += first ? k <= x[s] : k < x[s];
-            }
-        }
-    }
-#pragma unroll
-    for (uint32_t s = 0; s < SLOTS; ++s) {
-        if (s * kWave + lane < m) {
-            rk[before[s]] = map_out(x[s], map);
-            if constexpr (HAS_V)
-                rv[before[s]] = v[s];
-        }
-    }
-}
-
-// A run of up to kRestWaveRun elements, by one wave.
-template <typename K, typename V, bool HAS_V>
-__device__ __forceinline__ void rest_wave_run(const RunArray<K, V> &arr, uint4 run)
-{
-    const uint32_t lane = threadIdx.x % kWave;
-    const uint32_t m = run.y;
-    K *rk = arr.k + run.x;
-    V *rv = HAS_V ? arr.v + run.x : nullptr;
-    K x[kRestSlots];
-    V v[HAS_V ? kRestSlots : 1];
-#pragma unroll
-    for (uint32_t s = 0; s < kRestSlots; ++s) {
-        const uint32_t e = s * kWave + lane;
-        x[s] = e < m ? rk[e] : (K)0;
-        if constexpr (HAS_V)
-            v[s] = e < m ? rv[e] : (V)0;
-    }
-    if (arr.map) {
-#pragma unroll
-        for (uint32_t s = 0; s < kRestSlots; ++s)
-            x[s] = map_in(x[s], arr.map);
-    }
-    if (m <= 2 * kWave)
-        rest_place<K, V, HAS_V, 2>(rk, rv, arr.map, m, x, v);
-    else if (m <= 4 * kWave)
-        rest_place<K, V, HAS_V, 4>(rk, rv, arr.map, m, x, v);
-    else
-        rest_place<K, V, HAS_V, 8>(rk, rv, arr.map, m, x, v);
+        rest.longer[idx] = run;
 }
 
 struct RestShared {
     uint32_t item, ok;
+};
+
+// LDS of k_last: of a pass, of a run for a workgroup, of runs for its waves.
+template <typename K, typename C, bool HAS_V>
+union RestLds {
+    PassLds<K, C, HAS_V> pass;
+    BlockLds<K, HAS_V, C::kThreads, C::kItems> block;
+    WaveLds<K, HAS_V, kRestWaveRun> wave[C::kThreads / kWave];
 };
 
 // Hands out [0, len) to the waves of the launch's workgroups, a wave each, from
@@ -588,10 +572,9 @@ __device__ __forceinline__ uint32_t rest_by_waves(RestShared &S, uint32_t *claim
 constexpr uint32_t kRestAll = 0xFFFFFFFFu;
 
 template <typename K, typename V, bool HAS_V, typename C, typename Resolve>
-__device__ __forceinline__ uint32_t rest_runs(BlockLds<K, HAS_V, C::kThreads, C::kItems> &L,
-                                              RestShared &S, uint32_t *ctrl,
-                                              const RestArea &rest, const PassArgs &wait,
-                                              Resolve &&resolve)
+__device__ __forceinline__ uint32_t rest_runs(RestLds<K, C, HAS_V> &L, RestShared &S,
+                                              uint32_t *ctrl, const RestArea &rest,
+                                              const PassArgs &wait, Resolve &&resolve)
 {
     constexpr uint32_t T = C::kTile;
     constexpr int THREADS = C::kThreads;
@@ -602,8 +585,7 @@ __device__ __forceinline__ uint32_t rest_runs(BlockLds<K, HAS_V, C::kThreads, C:
         return kRestAll;
     const uint32_t found =
         rest_by_waves<THREADS>(S, &rest.words[kRestFindClaim], len, [&](uint32_t i) {
-            const uint2 entry = rest.list[i];
-            rest_find(resolve(entry.y), entry, T, ctrl, rest);
+            rest_find<K, V>(i, T, ctrl, rest, resolve);
         });
     if (t == 0) {
         S.ok = hand_on_and_wait(&rest.words[kRestFindDone], found, len, wait) ? 1u : 0u;
@@ -616,12 +598,22 @@ __device__ __forceinline__ uint32_t rest_runs(BlockLds<K, HAS_V, C::kThreads, C:
         return __builtin_amdgcn_readfirstlane(
             __hip_atomic_load(word, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
     };
-    const uint32_t shorts = count(&rest.words[kRestShortLen]);
-    const uint32_t longer = count(&ctrl[kCtrlLongerLen]);
+    const uint32_t longer = min(count(&ctrl[kCtrlLongerLen]), rest.max_longer);
     const uint32_t rows = min(count(&rest.words[kRestRows]), rest.max_rows);
-    rest_by_waves<THREADS>(S, &rest.words[kRestShortClaim], shorts, [&](uint32_t i) {
-        const uint4 run = rest.runs[i];
-        rest_wave_run<K, V, HAS_V>(resolve(run.z), run);
+    rest_by_waves<THREADS>(S, &rest.words[kRestShortClaim], len, [&](uint32_t i) {
+        const uint4 run = rest.list[i];
+        if (__builtin_amdgcn_readfirstlane(run.y) == 0)
+            return;
+        const RunArray<K, V> arr = resolve(run.z);
+        K *rk = arr.k + run.x;
+        V *rv = HAS_V ? arr.v + run.x : nullptr;
+        const uint32_t m = __builtin_amdgcn_readfirstlane(run.y);
+        const WaveData<K, V> in{rk, rv, rk, rv};
+        auto &lds = L.wave[__builtin_amdgcn_readfirstlane(t / kWave)];
+        if (m <= kRestWaveRun / 2)
+            radix_wave<K, V, HAS_V, kRestWaveRun / 2 / kWave>(lds, in, m, t % kWave, arr.map);
+        else
+            radix_wave<K, V, HAS_V, kRestWaveRun / kWave>(lds, in, m, t % kWave, arr.map);
     });
     while (true) {
         __syncthreads();
@@ -631,7 +623,7 @@ __device__ __forceinline__ uint32_t rest_runs(BlockLds<K, HAS_V, C::kThreads, C:
         const uint32_t item = __builtin_amdgcn_readfirstlane(S.item);
         if (item >= longer)
             break;
-        const uint4 run = rest.runs[rest.cap - 1 - item];
+        const uint4 run = rest.longer[item];
         if (__builtin_amdgcn_readfirstlane(run.y) > T)
             continue;
         const RunArray<K, V> arr = resolve(run.z);
@@ -646,7 +638,7 @@ __device__ __forceinline__ uint32_t rest_runs(BlockLds<K, HAS_V, C::kThreads, C:
                 val[j] = it.has(j) ? rv[it.at(j)] : (V)0;
         });
         __syncthreads();  // everything is read before it is overwritten
-        block_sort_digits<K, V, HAS_V, THREADS, ITEMS>(L, it, key, val, arr.digits);
+        block_sort_digits<K, V, HAS_V, THREADS, ITEMS>(L.block, it, key, val, arr.digits);
         it.each([&](int j) {
             if (it.has(j)) {
                 rk[it.at(j)] = map_out(key[j], arr.map);
@@ -793,7 +785,7 @@ __device__ __forceinline__ void sort_again(PassLds<K, C, HAS_V> &L, RestShared &
 // The run of a row of sort_again (uniform).
 __device__ __forceinline__ uint4 rest_row(const RestArea &rest, uint32_t row)
 {
-    const uint4 run = rest.runs[rest.cap - 1 - rest.row_run[row]];
+    const uint4 run = rest.longer[rest.row_run[row]];
     return make_uint4(
         __builtin_amdgcn_readfirstlane(run.x), __builtin_amdgcn_readfirstlane(run.y),
         __builtin_amdgcn_readfirstlane(run.z), __builtin_amdgcn_readfirstlane(run.w));
@@ -810,10 +802,7 @@ template <typename K, typename V, bool HAS_V, typename C>
 __global__ __launch_bounds__(C::kThreads) void k_last(LastArgs a)
 {
     static_assert(C::kRadixBits == kRadixBits, "8-bit digits");
-    __shared__ union {
-        PassLds<K, C, HAS_V> pass;
-        BlockLds<K, HAS_V, C::kThreads, C::kItems> block;
-    } L;
+    __shared__ RestLds<K, C, HAS_V> L;
     __shared__ RestShared S;
 
     uint32_t *ctrl = a.p.ctrl;
@@ -834,7 +823,7 @@ __global__ __launch_bounds__(C::kThreads) void k_last(LastArgs a)
     V *bv = HAS_V ? pick<V>(a.p.b, buf, true) : nullptr;
     const uint32_t low = digits & ((1u << (shift / C::kRadixBits)) - 1u);
     const uint32_t rows =
-        rest_runs<K, V, HAS_V, C>(L.block, S, ctrl, a.rest, a.p, [=](uint32_t) {
+        rest_runs<K, V, HAS_V, C>(L, S, ctrl, a.rest, a.p, [=](uint32_t) {
             return RunArray<K, V>{bk, bv, n, shift, low, map, 0};
         });
     if (rows == 0)
@@ -883,13 +872,19 @@ struct SegFinishArgs {
 };
 
 template <typename K, typename V, bool HAS_V, int THREADS, int ITEMS>
-__global__ __launch_bounds__(THREADS) void k_seg_finish(SegFinishArgs a)
+__global__ __launch_bounds__(THREADS) RS_FINISH_SGPRS void k_seg_finish(SegFinishArgs a)
 {
     constexpr uint32_t T = THREADS * ITEMS;
     __shared__ FinishLds<K, THREADS, ITEMS> L;
     if (!(a.ctrl[kSegPassMask] & kSegAnyFinish))
         return;
-    finish_begin(L, a.rest);
+    if (threadIdx.x == 0)
+        L.done = 0;
+    __syncthreads();
+    for (uint32_t i = blockIdx.x * THREADS + threadIdx.x; i < a.rest.num_words;
+         i += gridDim.x * THREADS)
+        a.rest.words[i] = 0;
+    FinishFound found;
     const uint32_t tiles = std::min(a.ctrl[kSegTiles], a.max_tiles);
     // groups of sweep tiles: a segment's record takes three dependent loads
     const uint32_t per = a.tile / (T * a.group);
@@ -912,10 +907,10 @@ __global__ __launch_bounds__(THREADS) void k_seg_finish(SegFinishArgs a)
         for (uint32_t g = 0; g < a.group && tb < size; ++g, tb += T)
             finish_tile<K, V, HAS_V, THREADS, ITEMS>(
                 L, sk, sv, dk, dv, size, tb, (int)(m.low * kRadixBits),
-                dst == kBufOut ? a.kmap : 0u,
-                [&](uint32_t i) { finish_report(L, a.ctrl, a.rest, i, seg); });
+                dst == kBufOut ? a.kmap : 0u, found.longs,
+                [&](uint32_t i) { finish_report(L, a.ctrl, a.rest, found, i, seg); });
     }
-    finish_end(L, a.ctrl, a.rest);
+    finish_end(L, a.ctrl, a.rest, found);
 }
 
 struct SegLastArgs {
@@ -929,10 +924,7 @@ __global__ __launch_bounds__(C::kThreads) void k_seg_last(SegLastArgs a)
     constexpr uint32_t NB = C::kBins;
     constexpr int R = C::kRadixBits;
     constexpr int D = num_passes<K, R>();
-    __shared__ union {
-        PassLds<K, C, HAS_V> pass;
-        BlockLds<K, HAS_V, C::kThreads, C::kItems> block;
-    } L;
+    __shared__ RestLds<K, C, HAS_V> L;
     __shared__ RestShared S;
     uint32_t *ctrl = a.p.ctrl;
     if (ctrl[kCtrlUnsorted] == 0)
@@ -950,7 +942,7 @@ __global__ __launch_bounds__(C::kThreads) void k_seg_last(SegLastArgs a)
         return (uint32_t)__builtin_amdgcn_readfirstlane(x);
     };
     const uint32_t rows =
-        rest_runs<K, V, HAS_V, C>(L.block, S, ctrl, a.rest, wait, [=](uint32_t seg) {
+        rest_runs<K, V, HAS_V, C>(L, S, ctrl, a.rest, wait, [=](uint32_t seg) {
             const SegLarge rec = large[seg];
             const uint32_t flags = seg_flags[seg];
             const SegMoves m = seg_moves<K, R>(flags, in_place);

@@ -704,7 +704,7 @@ static rs_status run_sort(rs_context *ctx, const K *kin, const K *vin, K *kout, 
     pa.stall = ctx->stall;
     // the pass slots; the last one copies the input when no pass moves data,
     // or follows up on k_finish
-    const RestArea rest = rest_area(status, L.tiles, n);
+    const RestArea rest = rest_area(status, L.d, L.tiles, n);
     const FinishArgs fa{b, (uint32_t)n, ctrl, rest, kmap};
     const bool fused = n <= kFinishFused;
     for (int p = 0; p < slots; ++p) {
@@ -1103,7 +1103,7 @@ static rs_status run_segmented(rs_context *ctx, const void *kin, const void *vin
                [&] { op.pass(pa, pass_grid, s); });
     }
     if (op.finish) {
-        const RestArea rest = rest_area(status, L.max_tiles, total);
+        const RestArea rest = rest_area(status, L.d, L.max_tiles, total);
         const uint32_t per = (uint32_t)op.tile / (kFinishThreads * kFinishItems);
         const uint32_t most = grid_of(op.finish_kernel, kFinishThreads);
         uint32_t group = per;

@@ -1,7 +1,8 @@
 // LDS radix sort of up to 1024 elements by one wave: the one-workgroup sort
 // (rs_block.h) with a single wave, so that no step needs a barrier.  Used for
 // the tiny segments of a segmented sort that are too long for the bitonic
-// network to win (rs_bitonic.h).
+// network to win (rs_bitonic.h), and for runs that a sweep could not order
+// (rs_finish.h).
 #pragma once
 
 #include <cstddef>
@@ -13,26 +14,27 @@ namespace rs {
 
 constexpr uint32_t kWaveSortMax = 1024;
 
-// LDS of one wave: the digit counters and the staged elements, with
-// run_move's neighbours on either side of the keys.  The lane-mask table
-// shares the keys' memory; positions need 16 bits.
-template <typename K, bool HAS_V>
+// LDS of one wave that sorts up to MAX elements: the digit counters and the
+// staged elements, with run_move's neighbours on either side of the keys.  The
+// lane-mask table shares the keys' memory; positions need 16 bits.
+template <typename K, bool HAS_V, uint32_t MAX = kWaveSortMax>
 struct WaveLds {
+    static_assert(MAX >= kRadix * 8 / sizeof(K) && MAX <= 1u << 16,
+                  "the lane-mask table lives in the staged keys");
     uint32_t wc[kRadix];
-    uint16_t pos[HAS_V ? kWaveSortMax : 2];
+    uint16_t pos[HAS_V ? MAX : 2];
     __attribute__((aligned(16))) K before[kRunMax];
-    K key[kWaveSortMax];
+    K key[MAX];
     K behind[kRunMax];
 };
 
 // One stable counting sort by the 8-bit digit at bit `shift`: item j of lane
 // l is element j*64 + l, before and after.  Only elements below m take part.
-template <typename K, bool HAS_V, int R>
-__device__ __forceinline__ void wave_sort_digit(WaveLds<K, HAS_V> &L, K (&key)[R],
+template <typename K, bool HAS_V, int R, uint32_t MAX>
+__device__ __forceinline__ void wave_sort_digit(WaveLds<K, HAS_V, MAX> &L, K (&key)[R],
                                                 uint32_t (&pos)[HAS_V ? R : 1], uint32_t m,
                                                 uint32_t lane, int shift)
 {
-    static_assert(sizeof L.key >= kRadix * 8, "the lane-mask table lives in the staged keys");
     uint64_t *wm = (uint64_t *)L.key;
     wave_lds_fence();
     ((uint4 *)L.wc)[lane] = make_uint4(0, 0, 0, 0);
@@ -88,8 +90,8 @@ __device__ __forceinline__ void wave_sort_digit(WaveLds<K, HAS_V> &L, K (&key)[R
 
 // Sorts a wave's m elements (m >= 1); to[j] is where item j then belongs.
 // As block_sort: two passes from the highest differing bit, then the runs.
-template <typename K, bool HAS_V, int R>
-__device__ __forceinline__ void wave_sort(WaveLds<K, HAS_V> &L, K (&key)[R],
+template <typename K, bool HAS_V, int R, uint32_t MAX>
+__device__ __forceinline__ void wave_sort(WaveLds<K, HAS_V, MAX> &L, K (&key)[R],
                                           uint32_t (&pos)[HAS_V ? R : 1], uint32_t m,
                                           uint32_t lane, uint32_t (&to)[R])
 {
@@ -109,16 +111,19 @@ __device__ __forceinline__ void wave_sort(WaveLds<K, HAS_V> &L, K (&key)[R],
         return;
     const int top = (kWave - 1) - __builtin_clzll(diff);
     const int shift = max(0, top - (2 * kRadixBits - 1));
-    wave_sort_digit<K, HAS_V, R>(L, key, pos, m, lane, shift);
+    wave_sort_digit<K, HAS_V, R, MAX>(L, key, pos, m, lane, shift);
     if (top >= kRadixBits)
-        wave_sort_digit<K, HAS_V, R>(L, key, pos, m, lane, shift + kRadixBits);
+        wave_sort_digit<K, HAS_V, R, MAX>(L, key, pos, m, lane, shift + kRadixBits);
     if (shift == 0 || (diff & (((uint64_t)1 << shift) - 1)) == 0)
         return;
     const K low_ones = ((K)1 << shift) - 1;
     const K *s_run = L.before + kRunMax;
-    using Lds = WaveLds<K, HAS_V>;
+    using Lds = WaveLds<K, HAS_V, MAX>;
+    static_assert(R * kWave <= (int)MAX, "the wave's elements are staged");
     static_assert(offsetof(Lds, key) == offsetof(Lds, before) + kRunMax * sizeof(K),
                   "the neighbours lie right before the keys");
+    static_assert(offsetof(Lds, behind) == offsetof(Lds, key) + MAX * sizeof(K),
+                  "and right behind them");
     uint64_t head[R];
     bool inv = false;
 #pragma unroll
@@ -156,10 +161,57 @@ __device__ __forceinline__ void wave_sort(WaveLds<K, HAS_V> &L, K (&key)[R],
     // long runs out of order: every digit that differs
     for (int p = 0; p < num_passes<K, kRadixBits>(); ++p)
         if ((diff >> (p * kRadixBits)) & (kRadix - 1))
-            wave_sort_digit<K, HAS_V, R>(L, key, pos, m, lane, p * kRadixBits);
+            wave_sort_digit<K, HAS_V, R, MAX>(L, key, pos, m, lane, p * kRadixBits);
 #pragma unroll
     for (int j = 0; j < R; ++j)
         to[j] = j * kWave + lane;
+}
+
+// Where a wave's elements come from and go to (the same place: in place).
+template <typename K, typename V>
+struct WaveData {
+    const K *kin;
+    const V *vin;
+    K *kout;
+    V *vout;
+};
+
+// Sorts m elements, 1 <= m <= 64 R, in R slots of 64; kmap is applied to the keys
+// on load and undone on store.
+template <typename K, typename V, bool HAS_V, int R, uint32_t MAX>
+__device__ __forceinline__ void radix_wave(WaveLds<K, HAS_V, MAX> &L, const WaveData<K, V> &d,
+                                           uint32_t m, uint32_t lane, uint32_t kmap)
+{
+    K key[R];
+    uint32_t pos[HAS_V ? R : 1], to[R];
+#pragma unroll
+    for (int j = 0; j < R; ++j) {
+        const uint32_t e = j * kWave + lane;
+        key[j] = e < m ? d.kin[e] : (K)0;
+        if constexpr (HAS_V)
+            pos[j] = e;
+    }
+    if (kmap) {
+#pragma unroll
+        for (int j = 0; j < R; ++j)
+            key[j] = map_in(key[j], kmap);
+    }
+    wave_sort<K, HAS_V, R, MAX>(L, key, pos, m, lane, to);
+    // every value is read before any is written (in place: vin == vout)
+    V val[HAS_V ? R : 1];
+    if constexpr (HAS_V) {
+#pragma unroll
+        for (int j = 0; j < R; ++j)
+            val[j] = j * kWave + lane < m ? d.vin[pos[j]] : (V)0;
+    }
+#pragma unroll
+    for (int j = 0; j < R; ++j) {
+        if (j * kWave + lane < m) {
+            d.kout[to[j]] = map_out(key[j], kmap);
+            if constexpr (HAS_V)
+                d.vout[to[j]] = val[j];
+        }
+    }
 }
 
 }  // namespace rs

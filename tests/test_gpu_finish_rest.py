@@ -154,3 +154,21 @@ def test_segments_with_runs_longer_than_a_tile(rs, oracle_lib, pairs, in_place):
     print(f"case pairs={pairs} in_place={in_place}", flush=True)
     w = batch_checked(rs, oracle_lib, parts, pairs, in_place, "float", True)
     assert w[LONGER_LEN] == 2 and w[GIANT] == 2
+
+
+# runs at the edges of what a wave sorts, in four slots and in eight
+@pytest.mark.parametrize("in_place", [False, True])
+@pytest.mark.parametrize("bits,pairs", KINDS)
+def test_runs_for_a_wave(rs, oracle_lib, bits, pairs, in_place):
+    n, sizes = 20000, (65, 128, 255, 256, 257, 511, 512, 513)
+    g = np.random.RandomState(51)
+    keys = datagen.keys("uniform", n, bits, seed=52)
+    at = g.permutation(n)
+    low = keys.dtype.type((1 << (bits - 18)) - 1)
+    for size in sizes:
+        a, at = at[:size], at[size:]
+        keys[a] = (keys[a[0]] & ~low) | (keys[a] & low)
+        keys[a[:4]] = keys[a[0]]  # equal ones among them, too few for the sample
+    print(f"case bits={bits} pairs={pairs} in_place={in_place}", flush=True)
+    w = sort_checked(rs, oracle_lib, keys, pairs, in_place, "signed", True)
+    assert w[FINISH] & 1 and w[UNSORTED] >= len(sizes) and 1 <= w[LONGER_LEN] <= 2
