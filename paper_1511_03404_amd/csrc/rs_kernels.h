@@ -319,6 +319,20 @@ struct PlanArgs {
 constexpr float kFinishMean = 32.f;
 constexpr float kFinishMeanSame = 1.f / 32.f;
 constexpr uint32_t kSampleSame = 4;
+// 32-bit keys have two passes to gain at most, and a sweep over runs of several
+// groups takes longer than one over as many single keys: groups of kSampleCopies
+// keys count too where fewer repeats show them, as in a long segment's sample
+// (batch of 2^24 pairs, 300 copies of a key over all segments: 487 us, 416 so).
+constexpr uint32_t kSampleCopies = 6;
+template <typename K>
+__device__ __forceinline__ uint32_t sample_same(uint32_t sample, uint32_t n)
+{
+    if (sizeof(K) == 8)
+        return kSampleSame;
+    // repeats among `sample` draws from n / kSampleCopies keys
+    const float r = (float)sample * (float)sample * (0.5f * kSampleCopies) / (float)n;
+    return r < 1.f ? 1u : r < (float)kSampleSame ? (uint32_t)r : kSampleSame;
+}
 constexpr uint32_t kFinishRepeatMean = 48;
 // k_finish costs about a pass, so it has to save two (this also leaves the
 // last slot free for k_last).
@@ -551,7 +565,7 @@ __global__ __launch_bounds__(kRadix * 4) void k_plan(PlanArgs a)
                 sample_repeats<K, kSampleMax, kSampleThreads>(sample, a.sample_count, 0, s_tag_same, &s_same);
                 sample_repeats<K, kSampleMax, kSampleThreads>(sample, a.sample_count, low * R, s_tag, &s_repeats);
                 __syncthreads();
-                const bool groups = s_same >= kSampleSame;
+                const bool groups = s_same >= sample_same<K>(a.sample_count, a.n);
                 const uint32_t allow = groups ? 0u : a.allow;
                 if (groups && 2 * s_same < a.sample_count)
                     low = min(low, stop_at<D>(a.n, s_trivial, s_max, kFinishMeanSame));
@@ -1383,7 +1397,9 @@ __global__ __launch_bounds__(256) void k_seg_scan(SegHistArgs a)
     constexpr int D = num_passes<K, R>();
     constexpr int NB = 1 << R;
     static_assert(D <= kSegSkewShift, "pass flags fit 16 bits each");
-    constexpr uint32_t PER = 2, TAB = 2 * PER * 256;  // sampled keys per thread, hash slots
+    // sampled keys per thread, hash slots; 32-bit keys: enough to see groups that
+    // a segment of 2^20 holds (sample_same)
+    constexpr uint32_t PER = sizeof(K) == 4 ? 4 : 2, TAB = 2 * PER * 256;
     __shared__ uint32_t s_tmp[8];
     __shared__ float s_sq[256 / kWave];
     __shared__ int s_trivial[D];
@@ -1428,7 +1444,7 @@ __global__ __launch_bounds__(256) void k_seg_scan(SegHistArgs a)
         int low = 0;
         if constexpr (R == kRadixBits) {
             // where the segment's passes may stop, as k_plan, from a sample
-            // of 512 of its keys
+            // of its keys
             low = stop_at<D>(size, s_trivial, s_max, kFinishMean);
             if (low) {
                 K sample[PER];
@@ -1457,7 +1473,7 @@ __global__ __launch_bounds__(256) void k_seg_scan(SegHistArgs a)
                     __syncthreads();
                     const uint32_t repeats = s_repeats, same = s_same;
                     __syncthreads();
-                    if (!same_known && same >= kSampleSame) {
+                    if (!same_known && same >= sample_same<K>(PER * 256, size)) {
                         allow = 0;
                         if (2 * same < PER * 256) {
                             const int strict = stop_at<D>(size, s_trivial, s_max, kFinishMeanSame);

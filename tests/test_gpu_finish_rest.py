@@ -172,3 +172,14 @@ def test_runs_for_a_wave(rs, oracle_lib, bits, pairs, in_place):
     print(f"case bits={bits} pairs={pairs} in_place={in_place}", flush=True)
     w = sort_checked(rs, oracle_lib, keys, pairs, in_place, "signed", True)
     assert w[FINISH] & 1 and w[UNSORTED] >= len(sizes) and 1 <= w[LONGER_LEN] <= 2
+
+
+# groups of about 19 equal 32-bit keys in one long segment: runs of several groups
+# would take the sweep longer than the two passes it saves
+@pytest.mark.parametrize("pairs", [False, True])
+def test_segment_of_groups_takes_every_digit(rs, oracle_lib, pairs):
+    g = np.random.RandomState(61)
+    keys = datagen.keys("uniform", 55000, 32, seed=62)[g.randint(0, 55000, 1 << 20)]
+    print(f"case pairs={pairs}", flush=True)
+    w = batch_checked(rs, oracle_lib, [keys, datagen.keys("uniform", 100, 32)], pairs)
+    assert w[PASS_MASK] == 15 and w[LONG_LEN] == 0
