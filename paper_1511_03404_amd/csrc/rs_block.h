@@ -223,59 +223,152 @@ __device__ __forceinline__ void block_sort_digits(BlockLds<K, HAS_V, THREADS, IT
                                                       __builtin_ctz(digits) * kRadixBits);
 }
 
-// Sorts the workgroup's elements; to[j] is where item j then belongs.
-//
-// The keys' highest differing bit is found first, and only the 16 bits from
-// there down are sorted by counting sorts, two passes for any key width: up
-// to 16384 elements then share those bits with few others, and each such
-// run is put in order by counting (run_move), which needs no staging of the
-// values.  Runs that are too long and out of order send the whole tile
-// through every digit that differs, 64-bit keys through the 32 highest
-// differing bits first: such runs come of repeated keys, and different keys
-// seldom share as many (16000 64-bit keys drawn from a power law and spread by
-// a multiplicative hash: 138 us by every digit, 89 so; with 24 bits of 32-bit
-// keys a pair of keys shares them nearly always).  With such 32-bit keys a
-// sort of 8193 to 16384 takes longer than one of every digit at once: 82 us
-// against 41, where uniform keys take 31 against 34 and 64 values 31 against 59.
-template <typename K, typename V, bool HAS_V, int THREADS, int ITEMS>
-__device__ __forceinline__ void block_sort(BlockLds<K, HAS_V, THREADS, ITEMS> &L,
-                                           const BlockItems<THREADS, ITEMS> &it, K (&key)[ITEMS],
-                                           V (&val)[HAS_V ? ITEMS : 1], uint32_t (&to)[ITEMS])
+// Orders the run [start, start + len) of the staged keys, sorted by their high bits
+// and out of order below: by one wave, one distinct key after another, each found
+// and counted in a scan over the run.  Keys alone are written to kout; with
+// values, where each element belongs to s_place.  False, with nothing written to
+// kout, if the run has too many distinct keys for that.
+constexpr uint32_t kPeelKeys = kWave;    // distinct keys, one a lane
+constexpr uint32_t kPeelChunks = 512;    // chunks of 64 read in all
+template <typename K, bool HAS_V>
+__device__ __forceinline__ bool peel_run(const K *s_k, uint16_t *s_place, K *kout, uint32_t kmap,
+                                         uint32_t start, uint32_t len)
+{
+    const uint32_t lane = threadIdx.x % kWave;
+    const uint32_t chunks = (len + kWave - 1) / kWave;
+    const auto least = [](K x) {
+        for (int s = 1; s < kWave; s *= 2) {
+            const K y = sizeof(K) == 8 ? (K)__shfl_xor((unsigned long long)x, s)
+                                       : (K)__shfl_xor((unsigned int)x, s);
+            x = y < x ? y : x;
+        }
+        return x;
+    };
+    K next = KeyTraits<K>::kPad;
+    for (uint32_t e = lane; e < len; e += kWave)
+        next = min(next, s_k[start + e]);
+    K own = 0;             // this lane's distinct key, and how many go before it
+    uint32_t own_from = 0;
+    uint32_t keys = 0, out = 0, read = chunks;
+    while (out < len) {
+        read += chunks;
+        if (keys == kPeelKeys || read > kPeelChunks)
+            return false;
+        const K key = least(next);
+        if (lane == keys) {
+            own = key;
+            own_from = out;
+        }
+        ++keys;
+        next = KeyTraits<K>::kPad;
+        for (uint32_t c = 0; c < len; c += kWave) {
+            const bool in = c + lane < len;
+            const K x = s_k[start + min(c + lane, len - 1)];
+            const uint64_t same = __ballot(in && x == key);
+            if constexpr (HAS_V) {
+                if (in && x == key)
+                    s_place[start + c + lane] = (uint16_t)(start + out + lanes_below(same));
+            }
+            out += (uint32_t)__popcll(same);
+            next = x > key && x < next ? x : next;
+        }
+    }
+    if constexpr (!HAS_V) {
+        for (uint32_t i = 0; i < keys; ++i) {
+            const K key = read_lane(own, i);
+            const uint32_t end = i + 1 < keys ? read_lane(own_from, i + 1) : len;
+            for (uint32_t e = read_lane(own_from, i) + lane; e < end; e += kWave)
+                kout[start + e] = map_out(key, kmap);
+        }
+    }
+    return true;
+}
+
+// Orders the runs of more than kRunMax elements that are out of order, among m
+// staged keys sorted by their bits above low_ones, by every thread of the
+// workgroup.  s_word is room for a word a chunk of 64 and a mark; the rest as
+// peel_run.
+template <typename K, bool HAS_V>
+__device__ __forceinline__ bool block_long_runs(const K *s_k, uint64_t *s_word, uint16_t *s_place,
+                                                K *kout, uint32_t kmap, uint32_t m, K low_ones)
+{
+    const uint32_t t = threadIdx.x;
+    const uint32_t W = blockDim.x / kWave;
+    const uint32_t w = __builtin_amdgcn_readfirstlane(t / kWave);
+    const uint32_t lane = t % kWave;
+    const uint32_t chunks = (m + kWave - 1) / kWave;
+    // every chunk's head word (elements past the last count as heads), and a mark
+    // for the chunks where a run to order may start (one at most: it goes on
+    // into the next)
+    uint64_t *s_head = s_word;
+    uint32_t *s_mark = (uint32_t *)(s_word + chunks);
+    for (uint32_t i = t; i < (chunks + 31) / 32; i += blockDim.x)
+        s_mark[i] = 0;
+    for (uint32_t c = w; c < chunks; c += W) {
+        const uint32_t at = c * kWave + lane;
+        const uint64_t head =
+            __ballot(at == 0 || at >= m || (s_k[at] ^ s_k[at - 1]) > low_ones);
+        if (lane == 0)
+            s_head[c] = head;
+    }
+    __syncthreads();
+    for (uint32_t c = w; c < chunks; c += W) {
+        const uint32_t at = c * kWave + lane;
+        const uint64_t head = uniform_word(s_head[c]);
+        const uint64_t inv = __ballot(at > 0 && at < m && s_k[at] < s_k[at - 1]);
+        const uint64_t in = head ? (head & (0 - head)) - 1 : ~0ull;
+        const uint64_t last = head ? ~0ull << (kWave - 1 - __builtin_clzll(head)) : 0ull;
+        const auto mark = [&](uint32_t chunk) {
+            if (lane == 0)
+                atomicOr(&s_mark[chunk / 32], 1u << (chunk % 32));
+        };
+        if (inv & last)
+            mark(c);
+        if (inv & in) {
+            // back to a chunk with a head (the first one has)
+            uint32_t back = 1;
+            uint64_t found;
+            while ((found = __ballot(c < back + lane || s_head[c - back - lane] != 0)) == 0)
+                back += kWave;
+            mark(c - back - (uint32_t)__builtin_ctzll(found));
+        }
+    }
+    __syncthreads();
+    bool all = true;
+    for (uint32_t c = w; c < chunks; c += W) {
+        if (!(__builtin_amdgcn_readfirstlane(s_mark[c / 32]) >> (c % 32) & 1))
+            continue;
+        const uint32_t start = c * kWave + kWave - 1 - __builtin_clzll(uniform_word(s_head[c]));
+        // ahead to a chunk with a head
+        uint32_t ahead = c + 1;
+        uint64_t found;
+        while ((found = __ballot(ahead + lane >= chunks || s_head[ahead + lane] != 0)) == 0)
+            ahead += kWave;
+        ahead += (uint32_t)__builtin_ctzll(found);
+        const uint32_t end =
+            ahead < chunks
+                ? ahead * kWave + (uint32_t)__builtin_ctzll(uniform_word(s_head[ahead]))
+                : m;
+        if (min(end, m) - start > kRunMax)
+            all = all && peel_run<K, HAS_V>(s_k, s_place, kout, kmap, start, min(end, m) - start);
+    }
+    return !__syncthreads_or(!all);
+}
+
+// The runs of keys that share their bits from `shift` up, for staged keys that are
+// sorted by those: to[j] is where item j then belongs.  False if longer runs are
+// out of order: their elements stay where they are.
+template <typename K, bool HAS_V, int THREADS, int ITEMS>
+__device__ __forceinline__ bool block_sort_runs(BlockLds<K, HAS_V, THREADS, ITEMS> &L,
+                                                const BlockItems<THREADS, ITEMS> &it,
+                                                const K (&key)[ITEMS], uint32_t (&to)[ITEMS],
+                                                int shift)
 {
     constexpr int W = THREADS / kWave;
     K *s_k = (K *)L.stage;
     const uint32_t t = threadIdx.x;
     const uint32_t w = __builtin_amdgcn_readfirstlane(t / kWave);
     const uint32_t lane = t % kWave;
-#pragma unroll
-    for (int j = 0; j < ITEMS; ++j)
-        to[j] = it.at(j);
-    // the bits in which any key differs from the first one
-    if (t == 0) {
-        L.diff = 0;
-        s_k[0] = key[0];
-    }
-    __syncthreads();
-    const K first = s_k[0];
-    {
-        K d = 0;
-        it.each([&](int j) { d |= it.has(j) ? key[j] ^ first : (K)0; });
-        const uint32_t lo = wave_or((uint32_t)d);
-        const uint32_t hi = sizeof(K) == 8 ? wave_or((uint32_t)((uint64_t)d >> 32)) : 0u;
-        if (lane == kWave - 1 && (lo | hi))
-            atomicOr((unsigned long long *)&L.diff, ((uint64_t)hi << 32) | lo);
-    }
-    __syncthreads();
-    const uint64_t diff = uniform_word(L.diff);
-    if (diff == 0)
-        return;  // one key only: in place
-    const int top = (kWave - 1) - __builtin_clzll(diff);
-    const int shift = max(0, top - (2 * kRadixBits - 1));
-    block_sort_digit<K, V, HAS_V, THREADS, ITEMS>(L, it, key, val, shift);
-    if (top >= kRadixBits)
-        block_sort_digit<K, V, HAS_V, THREADS, ITEMS>(L, it, key, val, shift + kRadixBits);
-    if (shift == 0 || (diff & (((uint64_t)1 << shift) - 1)) == 0)
-        return;  // nothing below the sorted bits
     // the runs: head words and neighbours out of order, as in k_finish
     const K low_ones = ((K)1 << shift) - 1;
     uint64_t head[ITEMS];
@@ -302,7 +395,7 @@ __device__ __forceinline__ void block_sort(BlockLds<K, HAS_V, THREADS, ITEMS> &L
         L.out[w] = out;
     }
     if (!__syncthreads_or(out != 0))
-        return;  // every run is in order already
+        return true;  // every run is in order already
     const uint64_t before = w == 0 ? ~0ull : uniform_word(L.head[2 * w - 1]);
     const uint64_t behind = w == W - 1 ? ~0ull : uniform_word(L.head[2 * w + 2]);
     // chunks next to one with elements out of order: in the others nothing moves
@@ -334,12 +427,174 @@ __device__ __forceinline__ void block_sort(BlockLds<K, HAS_V, THREADS, ITEMS> &L
             }
         }
     });
-    if (!__syncthreads_or(lost))
-        return;
+    return !__syncthreads_or(lost);
+}
+
+// Sorts the workgroup's elements; to[j] is where item j then belongs.
+//
+// The keys' highest differing bit is found first, and only the 16 bits from
+// there down are sorted by counting sorts, two passes for any key width: up
+// to 16384 elements then share those bits with few others, and each such
+// run is put in order by counting (run_move), which needs no staging of the
+// values.  Where that does not do, block_sort_rest has to follow:
+//   * kBlockLost   longer runs are out of order, which comes of repeated keys
+//                  (two that share the 16 bits, with 64 elements or more); the
+//                  other elements are in place;
+//   * kBlockEvery  the keys mostly share those bits (a few large ones set the
+//                  highest bit) and nothing has been done.  They are told by
+//                  pairs of elements, 64 in each wave: a wave counts the pairs
+//                  that differ, but below the 16 bits from its own highest
+//                  differing bit, and most waves have to count two or more.
+enum BlockResult { kBlockDone, kBlockLost, kBlockEvery };
+
+template <typename K, typename V, bool HAS_V, int THREADS, int ITEMS>
+__device__ __forceinline__ BlockResult block_sort(BlockLds<K, HAS_V, THREADS, ITEMS> &L,
+                                                  const BlockItems<THREADS, ITEMS> &it,
+                                                  K (&key)[ITEMS], V (&val)[HAS_V ? ITEMS : 1],
+                                                  uint32_t (&to)[ITEMS])
+{
+    constexpr int W = THREADS / kWave;
+    K *s_k = (K *)L.stage;
+    const uint32_t t = threadIdx.x;
+    const uint32_t w = __builtin_amdgcn_readfirstlane(t / kWave);
+    const uint32_t lane = t % kWave;
 #pragma unroll
     for (int j = 0; j < ITEMS; ++j)
         to[j] = it.at(j);
-    if (sizeof(K) == 8 && top >= 4 * kRadixBits) {
+    // the bits in which any key differs from the first one
+    if (t == 0) {
+        L.diff = 0;
+        s_k[0] = key[0];
+    }
+    __syncthreads();
+    const K first = s_k[0];
+    {
+        K d = 0;
+        it.each([&](int j) { d |= it.has(j) ? key[j] ^ first : (K)0; });
+        const uint32_t lo = wave_or((uint32_t)d);
+        const uint32_t hi = sizeof(K) == 8 ? wave_or((uint32_t)((uint64_t)d >> 32)) : 0u;
+        if (lane == kWave - 1 && (lo | hi))
+            atomicOr((unsigned long long *)&L.diff, ((uint64_t)hi << 32) | lo);
+        // the wave's highest differing bit + 1, and its pairs (elements 64 P apart)
+        // that differ below the 16 bits from there down
+        constexpr int P = BlockItems<THREADS, ITEMS>::kGroup - 1;
+        const uint64_t wave_diff = read_lane(((uint64_t)hi << 32) | lo, kWave - 1);
+        const uint32_t bits = wave_diff ? kWave - __builtin_clzll(wave_diff) : 0u;
+        const K x = it.has(P) ? key[0] ^ key[P] : (K)0;
+        const uint64_t pairs =
+            __ballot(x != 0 && bits > 2 * kRadixBits && (x >> (bits - 2 * kRadixBits)) == 0);
+        if (lane == 0)
+            L.out[w] = bits << 8 | (uint32_t)__popcll(pairs);
+    }
+    __syncthreads();
+    const uint64_t diff = uniform_word(L.diff);
+    if (diff == 0)
+        return kBlockDone;  // one key only: in place
+    const int top = (kWave - 1) - __builtin_clzll(diff);
+    const int shift = max(0, top - (2 * kRadixBits - 1));
+    // waves whose pairs mostly share the high bits: all of them if the wave's
+    // highest differing bit lies below
+    const uint32_t seen = lane < (uint32_t)W ? L.out[lane] : 0u;
+    const uint64_t alike = __ballot((seen & 255u) > 1 || (seen && (int)(seen >> 8) <= shift));
+    const uint32_t waves = (it.m + it.used * kWave - 1) / (it.used * kWave);
+    if (2 * (uint32_t)__popcll(alike) > waves)
+        return kBlockEvery;
+    block_sort_digit<K, V, HAS_V, THREADS, ITEMS>(L, it, key, val, shift);
+    if (top >= kRadixBits)
+        block_sort_digit<K, V, HAS_V, THREADS, ITEMS>(L, it, key, val, shift + kRadixBits);
+    if (shift == 0 || (diff & (((uint64_t)1 << shift) - 1)) == 0)
+        return kBlockDone;  // nothing below the sorted bits
+    return block_sort_runs<K, HAS_V, THREADS, ITEMS>(L, it, key, to, shift) ? kBlockDone
+                                                                            : kBlockLost;
+}
+
+// Where a workgroup's elements come from and go to (the same place: in place), and
+// the key orders applied on load and undone on store.
+template <typename K, typename V>
+struct BlockData {
+    const K *kin;
+    const V *vin;
+    K *kout;
+    V *vout;
+    uint32_t map_load, map_store;
+};
+
+template <typename K, typename V, bool HAS_V, int THREADS, int ITEMS>
+__device__ __forceinline__ void block_load(const BlockItems<THREADS, ITEMS> &it, const K *kin,
+                                           const V *vin, uint32_t kmap, K (&key)[ITEMS],
+                                           V (&val)[HAS_V ? ITEMS : 1])
+{
+    it.each([&](int j) {
+        key[j] = it.has(j) ? kin[it.at(j)] : (K)0;
+        if constexpr (HAS_V)
+            val[j] = it.has(j) ? vin[it.at(j)] : (V)0;
+    });
+    // mapped once every load is issued (a map between loads would wait
+    // for each in turn)
+    if (kmap)
+        it.each([&](int j) { key[j] = map_in(key[j], kmap); });
+}
+
+// What block_sort has left, once its elements are written: the long runs out of
+// order, one distinct key after another (two keys in a run, say).  If one has
+// too many for that, or nothing has been done, the whole tile is read again
+// and sorted by every digit that differs, 64-bit keys by the 32 highest
+// differing bits first.
+//
+// After the elements are written, since nothing is held in registers then: in
+// block_sort itself, where the elements are, this made the sorts of 16384
+// spill them (64-bit keys 34 -> 49 us).
+//
+// With every digit sorted from the start, with all of them after the two passes
+// whatever the runs, and so: 16000 32-bit keys of 32 copies each 49, 86 and 39 us;
+// 16000 keys below 2^15 and one of 2^30 52, 82 and 38.
+template <typename K, typename V, bool HAS_V, int THREADS, int ITEMS>
+__device__ __forceinline__ void block_sort_rest(BlockLds<K, HAS_V, THREADS, ITEMS> &L, uint32_t m,
+                                                const BlockData<K, V> &d, bool every)
+{
+    constexpr int W = THREADS / kWave;
+    const BlockItems<THREADS, ITEMS> it(m);
+    const uint64_t diff = uniform_word(L.diff);
+    const int top = (kWave - 1) - __builtin_clzll(diff);
+    const K *s_k = (const K *)L.stage;
+    // the elements have to be there for every thread of the workgroup
+    __syncthreads();
+    K key[ITEMS];
+    V val[HAS_V ? ITEMS : 1];
+    if (!every) {
+        // the digit counters are free, and the memory of the values, behind the
+        // keys and their guard
+        static_assert(W * ITEMS * 8 + (W * ITEMS + 31) / 32 * 4 <= sizeof L.wcnt, "words fit");
+        uint16_t *s_place =
+            (uint16_t *)(L.stage + ((size_t)THREADS * ITEMS + kRunMax) * sizeof(K));
+        if constexpr (HAS_V)
+            it.each([&](int j) { s_place[it.at(j)] = (uint16_t)it.at(j); });
+        const K low_ones = ((K)1 << (top - (2 * kRadixBits - 1))) - 1;
+        if (block_long_runs<K, HAS_V>(s_k, (uint64_t *)L.wcnt, s_place, d.kout, d.map_store, m,
+                                      low_ones)) {
+            if constexpr (HAS_V) {
+                it.each([&](int j) {
+                    if (it.has(j) && s_place[it.at(j)] != it.at(j))
+                        val[j] = d.vout[it.at(j)];
+                });
+                __syncthreads();  // everything is read before it is overwritten
+                it.each([&](int j) {
+                    const uint32_t to = s_place[it.at(j)];
+                    if (it.has(j) && to != it.at(j)) {
+                        d.kout[to] = map_out(s_k[it.at(j)], d.map_store);
+                        d.vout[to] = val[j];
+                    }
+                });
+            }
+            return;
+        }
+        __syncthreads();
+    }
+    block_load<K, V, HAS_V, THREADS, ITEMS>(it, every ? d.kin : d.kout, every ? d.vin : d.vout,
+                                            every ? d.map_load : d.map_store, key, val);
+    __syncthreads();  // everything is read before it is overwritten
+    bool sorted = false;
+    if (sizeof(K) == 8 && !every && top >= 4 * kRadixBits) {
         for (int at = top + 1 - 4 * kRadixBits; at <= top; at += kRadixBits)
             block_sort_digit<K, V, HAS_V, THREADS, ITEMS>(L, it, key, val, at);
         bool inv = false;
@@ -347,13 +602,44 @@ __device__ __forceinline__ void block_sort(BlockLds<K, HAS_V, THREADS, ITEMS> &L
             const bool has = it.has(j) && it.at(j) > 0;
             inv = inv || (has && key[j] < s_k[has ? it.at(j) - 1 : 0u]);
         });
-        if (!__syncthreads_or(inv))
-            return;
+        sorted = !__syncthreads_or(inv);
     }
-    uint32_t digits = 0;
-    for (int p = 0; p < num_passes<K, kRadixBits>(); ++p)
-        digits |= ((diff >> (p * kRadixBits)) & (kRadix - 1)) ? 1u << p : 0u;
-    block_sort_digits<K, V, HAS_V, THREADS, ITEMS>(L, it, key, val, digits);
+    if (!sorted) {
+        uint32_t digits = 0;
+        for (int p = 0; p < num_passes<K, kRadixBits>(); ++p)
+            digits |= ((diff >> (p * kRadixBits)) & (kRadix - 1)) ? 1u << p : 0u;
+        block_sort_digits<K, V, HAS_V, THREADS, ITEMS>(L, it, key, val, digits);
+    }
+    it.each([&](int j) {
+        if (it.has(j)) {
+            d.kout[it.at(j)] = map_out(key[j], d.map_store);
+            if constexpr (HAS_V)
+                d.vout[it.at(j)] = val[j];
+        }
+    });
+}
+
+// Sorts m elements of the workgroup, from d's input to its output.
+template <typename K, typename V, bool HAS_V, int THREADS, int ITEMS>
+__device__ __forceinline__ void block_sort_data(BlockLds<K, HAS_V, THREADS, ITEMS> &L, uint32_t m,
+                                                const BlockData<K, V> &d)
+{
+    const BlockItems<THREADS, ITEMS> it(m);
+    K key[ITEMS];
+    V val[HAS_V ? ITEMS : 1];
+    block_load<K, V, HAS_V, THREADS, ITEMS>(it, d.kin, d.vin, d.map_load, key, val);
+    uint32_t to[ITEMS];
+    const BlockResult r = block_sort<K, V, HAS_V, THREADS, ITEMS>(L, it, key, val, to);
+    if (r != kBlockEvery)
+        it.each([&](int j) {
+            if (it.has(j)) {
+                d.kout[to[j]] = map_out(key[j], d.map_store);
+                if constexpr (HAS_V)
+                    d.vout[to[j]] = val[j];
+            }
+        });
+    if (__builtin_expect(r != kBlockDone, 0))
+        block_sort_rest<K, V, HAS_V, THREADS, ITEMS>(L, m, d, r == kBlockEvery);
 }
 
 template <typename K, typename V, bool HAS_V, int THREADS, int ITEMS>
@@ -392,27 +678,10 @@ __global__ __launch_bounds__(THREADS) void k_block_sort(BlockArgs a)
             m = (uint32_t)a.n;
         }
 
-        const BlockItems<THREADS, ITEMS> it(m);
-        K key[ITEMS];
-        V val[HAS_V ? ITEMS : 1];
-        it.each([&](int j) {
-            key[j] = it.has(j) ? kin[start + it.at(j)] : (K)0;
-            if constexpr (HAS_V)
-                val[j] = it.has(j) ? vin[start + it.at(j)] : (V)0;
-        });
-        // mapped once every load is issued (a map between loads would wait
-        // for each in turn)
-        if (a.kmap)
-            it.each([&](int j) { key[j] = map_in(key[j], a.kmap); });
-        uint32_t to[ITEMS];
-        block_sort<K, V, HAS_V, THREADS, ITEMS>(L, it, key, val, to);
-        it.each([&](int j) {
-            if (it.has(j)) {
-                kout[start + to[j]] = map_out(key[j], a.kmap);
-                if constexpr (HAS_V)
-                    vout[start + to[j]] = val[j];
-            }
-        });
+        const BlockData<K, V> d{kin + start,  HAS_V ? vin + start : nullptr,
+                                kout + start, HAS_V ? vout + start : nullptr,
+                                a.kmap,       a.kmap};
+        block_sort_data<K, V, HAS_V, THREADS, ITEMS>(L, m, d);
         __syncthreads();  // the next range overwrites the LDS
     }
 }

@@ -141,39 +141,22 @@ struct MergeTileArgs {
 // on its lane-mask word, two reads and a write there.  Merging in LDS from 8
 // sorted elements per thread instead, ten rounds, 2^24 32-bit pairs took 223 us
 // in tiles of 8192, and one more merge level (62 us with its splits); tiles of
-// 16384 in two counting sorts and a sweep take 167.  A tile whose runs of equal
-// high bits are long and out of order needs every digit and takes longer than
-// the merges did: 2^24 keys drawn from a power law and spread by a
-// multiplicative hash, the whole sort 624 -> 731 us (32-bit), 825 -> 929
-// (64-bit), where uniform keys went 631 -> 536 and 834 -> 720.
+// 16384 in two counting sorts and a sweep take 167.  Keys drawn from a power law
+// and spread by a multiplicative hash (long runs out of order in the tiles): 2^24
+// of them, the whole sort by LDS merges -> so 625 -> 606 us (32-bit), 825 -> 791
+// (64-bit); uniform keys 631 -> 536 and 834 -> 720.
 template <typename K, typename V, bool HAS_V, int THREADS, int ITEMS>
 __global__ __launch_bounds__(THREADS) void k_merge_tile(MergeTileArgs a)
 {
     __shared__ BlockLds<K, HAS_V, THREADS, ITEMS> L;
     const uint32_t base = blockIdx.x * a.tile;
-    const BlockItems<THREADS, ITEMS> it(min(a.tile, a.n - base));
-    const K *kin = (const K *)a.kin + base;
-    const V *vin = HAS_V ? (const V *)a.vin + base : nullptr;
-    K key[ITEMS];
-    V val[HAS_V ? ITEMS : 1];
-    it.each([&](int j) {
-        key[j] = it.has(j) ? kin[it.at(j)] : (K)0;
-        if constexpr (HAS_V)
-            val[j] = it.has(j) ? vin[it.at(j)] : (V)0;
-    });
-    if (a.map_load)
-        it.each([&](int j) { key[j] = map_in(key[j], a.map_load); });
-    uint32_t to[ITEMS];
-    block_sort<K, V, HAS_V, THREADS, ITEMS>(L, it, key, val, to);
-    K *kout = (K *)a.kout + base;
-    V *vout = HAS_V ? (V *)a.vout + base : nullptr;
-    it.each([&](int j) {
-        if (it.has(j)) {
-            kout[to[j]] = map_out(key[j], a.map_store);
-            if constexpr (HAS_V)
-                vout[to[j]] = val[j];
-        }
-    });
+    const BlockData<K, V> d{(const K *)a.kin + base,
+                            HAS_V ? (const V *)a.vin + base : nullptr,
+                            (K *)a.kout + base,
+                            HAS_V ? (V *)a.vout + base : nullptr,
+                            a.map_load,
+                            a.map_store};
+    block_sort_data<K, V, HAS_V, THREADS, ITEMS>(L, min(a.tile, a.n - base), d);
 }
 
 // One merge level: runs [q 2w, q 2w + w) and [q 2w + w, q 2w + 2w) (clipped
