@@ -118,78 +118,44 @@ struct FinishLds {
     // elements out of order.
     uint64_t head[2 * W + 2], inv[2 * W + 2];
     uint2 pend[W][kFinishPend];  // places that each wave has to report
-    uint32_t count[W], longs[W];
-    uint32_t done;  // waves that have written theirs
-};
-
-// What a wave has found in its tiles (uniform): places where a longer run is
-// out of order, and longer runs.
-struct FinishFound {
-    uint32_t places = 0;
-    uint32_t longs = 0;
+    uint32_t longs;              // longer runs met, in order or not
 };
 
 // The wave reports that element i of segment seg is smaller than the one before
-// it, in a run that is too long to be ordered here.  The first reports wait in
-// LDS for the workgroup's end: atomics on one word end one after another, 14 ns
-// apart (2^25 64-bit keys, 100 of each: with an atomic for each of 335,000 long
-// runs the sweep took 5 ms).
+// it, in a run that is too long to be ordered here.  Reports wait in LDS, since
+// atomics on one word end one after another, 14 ns apart (2^25 64-bit keys, 100 of
+// each: with an atomic for each of 335,000 long runs the sweep took 5 ms).
 template <typename K, int THREADS, int ITEMS>
-__device__ __forceinline__ void finish_report(FinishLds<K, THREADS, ITEMS> &L, uint32_t *ctrl,
-                                              const RestArea &rest, FinishFound &found, uint32_t i,
-                                              uint32_t seg)
+__device__ __forceinline__ void finish_report(FinishLds<K, THREADS, ITEMS> &L, uint32_t &places,
+                                              uint32_t i, uint32_t seg)
 {
-    if (threadIdx.x % kWave == 0) {
-        if (found.places < kFinishPend) {
-            L.pend[threadIdx.x / kWave][found.places] = make_uint2(i, seg);
-        } else {
-            const uint32_t l = atomicAdd(&ctrl[kCtrlUnsorted], 1u);
-            if (l < rest.cap)
-                rest.list[l] = make_uint4(i, seg, 0, 0);
-        }
-    }
-    ++found.places;
+    if (threadIdx.x % kWave == 0)
+        L.pend[threadIdx.x / kWave][places] = make_uint2(i, seg);
+    ++places;
 }
 
-// After the last tile.  The workgroup's last wave lists what all have found: no
-// barrier, which would make every wave wait for the slowest.  (L.done was zero
-// before a barrier.)
+// After a tile: lists the wave's reports if there may be no room for those of
+// another tile, or if it was the last one.  After the last one the workgroup's
+// longer runs are counted too.
 template <typename K, int THREADS, int ITEMS>
-__device__ __forceinline__ void finish_end(FinishLds<K, THREADS, ITEMS> &L, uint32_t *ctrl,
-                                           const RestArea &rest, const FinishFound &found)
+__device__ __forceinline__ void finish_list(FinishLds<K, THREADS, ITEMS> &L, uint32_t *ctrl,
+                                            const RestArea &rest, uint32_t &places, bool last)
 {
-    constexpr uint32_t W = THREADS / kWave;
+    static_assert(2 * 2 * ITEMS <= (int)kFinishPend, "a tile has two places a chunk");
     const uint32_t lane = threadIdx.x % kWave;
-    uint32_t done = 0;
-    if (lane == 0) {
-        const uint32_t w = threadIdx.x / kWave;
-        L.count[w] = min(found.places, kFinishPend);
-        L.longs[w] = found.longs;
-        done = __hip_atomic_fetch_add(&L.done, 1u, __ATOMIC_ACQ_REL, __HIP_MEMORY_SCOPE_WORKGROUP);
+    if (__builtin_expect(places > (last ? 0 : kFinishPend - 2 * ITEMS), 0)) {
+        uint32_t l = 0;
+        if (lane == 0)
+            l = atomicAdd(&ctrl[kCtrlUnsorted], places);
+        l = __builtin_amdgcn_readfirstlane(l) + lane;
+        if (lane < places && l < rest.cap) {
+            const uint2 place = L.pend[threadIdx.x / kWave][lane];
+            rest.list[l] = make_uint4(place.x, place.y, 0, 0);
+        }
+        places = 0;
     }
-    if (__builtin_amdgcn_readfirstlane(done) != W - 1)
-        return;
-    // a lane for each wave, then for each of its places
-    const uint32_t count = lane < W ? L.count[lane] : 0u;
-    const uint32_t met = lane < W ? L.longs[lane] : 0u;
-    if (__builtin_expect(__ballot(count | met) == 0, 1))
-        return;
-    const uint32_t upto = wave_inclusive_scan(count);
-    const uint32_t longs = wave_inclusive_scan(met);
-    uint32_t base = 0;
-    if (lane == kWave - 1) {
-        if (upto)
-            base = atomicAdd(&ctrl[kCtrlUnsorted], upto);
-        if (longs)
-            atomicAdd(&ctrl[kCtrlLongLen], longs);
-    }
-    base = __builtin_amdgcn_readlane(base, kWave - 1);
-    for (uint32_t w = 0; w < W; ++w) {
-        const uint32_t c = __builtin_amdgcn_readlane(count, w);
-        const uint32_t l = base + __builtin_amdgcn_readlane(upto, w) - c + lane;
-        if (lane < c && l < rest.cap)
-            rest.list[l] = make_uint4(L.pend[w][lane].x, L.pend[w][lane].y, 0, 0);
-    }
+    if (last && threadIdx.x == 0 && L.longs)
+        atomicAdd(&ctrl[kCtrlLongLen], L.longs);
 }
 
 // The tile of an array of n elements that starts at tb: from sk, sv to dk,
@@ -198,8 +164,7 @@ __device__ __forceinline__ void finish_end(FinishLds<K, THREADS, ITEMS> &L, uint
 template <typename K, typename V, bool HAS_V, int THREADS, int ITEMS, typename Report>
 __device__ __forceinline__ void finish_tile(FinishLds<K, THREADS, ITEMS> &L, const K *sk,
                                             const V *sv, K *dk, V *dv, uint32_t n, uint32_t tb,
-                                            int shift, uint32_t map, uint32_t &longs,
-                                            Report &&report)
+                                            int shift, uint32_t map, Report &&report)
 {
     constexpr uint32_t T = THREADS * ITEMS;
     constexpr uint32_t H = kWave;
@@ -291,6 +256,7 @@ __device__ __forceinline__ void finish_tile(FinishLds<K, THREADS, ITEMS> &L, con
         inv[0] = uniform_word(s_inv[p]);
         inv[ITEMS + 1] = uniform_word(s_inv[q]);
     }
+    uint32_t longs = 0;
 #pragma unroll
     for (int j = 0; j < ITEMS; ++j) {
         const uint32_t e = e0 + j * kWave;
@@ -326,6 +292,8 @@ __device__ __forceinline__ void finish_tile(FinishLds<K, THREADS, ITEMS> &L, con
         if (here && ends + (next ? __builtin_ctzll(next) : kWave) >= kRunMax)
             ++longs;
     }
+    if (__builtin_expect(longs, 0) && lane == 0)
+        atomicAdd(&L.longs, longs);
     __syncthreads();  // the next tile overwrites the LDS
 }
 
@@ -343,16 +311,15 @@ __device__ __forceinline__ void finish_all(FinishLds<K, THREADS, ITEMS> &L, Fini
     K *dk = pick<K>(a.b, dst, false);
     V *dv = HAS_V ? pick<V>(a.b, dst, true) : nullptr;
     const uint32_t tiles = (a.n + T - 1) / T;
-    if (blockIdx.x >= tiles)
-        return;
+    uint32_t places = 0;  // reports that wait (uniform)
     if (threadIdx.x == 0)
-        L.done = 0;
-    FinishFound found;
-    for (uint32_t tile = blockIdx.x; tile < tiles; tile += gridDim.x)
+        L.longs = 0;  // a tile has barriers before and after its use
+    for (uint32_t tile = blockIdx.x; tile < tiles; tile += gridDim.x) {
         finish_tile<K, V, HAS_V, THREADS, ITEMS>(
-            L, sk, sv, dk, dv, a.n, tile * T, shift, map, found.longs,
-            [&](uint32_t i) { finish_report(L, a.ctrl, a.rest, found, i, 0); });
-    finish_end(L, a.ctrl, a.rest, found);
+            L, sk, sv, dk, dv, a.n, tile * T, shift, map,
+            [&](uint32_t i) { finish_report(L, places, i, 0); });
+        finish_list(L, a.ctrl, a.rest, places, tile + gridDim.x >= tiles);
+    }
 }
 
 template <typename K, typename V, bool HAS_V, int THREADS, int ITEMS>
@@ -384,11 +351,12 @@ __global__ __launch_bounds__(C::kThreads) void k_pass_finish(PassFinishArgs a)
         PassLds<K, C, HAS_V> pass;
         FinishLds<K, C::kThreads, kFinishItemsFused> finish;
     } L;
-    const uint32_t word = __builtin_amdgcn_readfirstlane(a.f.ctrl[kCtrlFinish]);
+    const uint32_t word = __builtin_amdgcn_readfirstlane(a.p.ctrl[kCtrlFinish]);
+    const uint32_t plan = __builtin_amdgcn_readfirstlane(a.p.ctrl[kCtrlPlan + a.p.pass]);
     if (word & kFinishRun)
         finish_all<K, V, HAS_V, C::kThreads, kFinishItemsFused>(L.finish, a.f, word);
     else if (blockIdx.x < a.pass_grid)
-        pass_slot<K, V, HAS_V, C>(a.p, L.pass);
+        pass_slot<K, V, HAS_V, C>(a.p, plan, L.pass);
 }
 
 struct LastArgs {
@@ -807,11 +775,13 @@ __global__ __launch_bounds__(C::kThreads) void k_last(LastArgs a)
 
     uint32_t *ctrl = a.p.ctrl;
     const uint32_t finish = __builtin_amdgcn_readfirstlane(ctrl[kCtrlFinish]);
+    const uint32_t plan = __builtin_amdgcn_readfirstlane(ctrl[kCtrlPlan + a.p.pass]);
+    const uint32_t unsorted = __builtin_amdgcn_readfirstlane(ctrl[kCtrlUnsorted]);
     if (!(finish & kFinishRun)) {
-        pass_slot<K, V, HAS_V, C>(a.p, L.pass);
+        pass_slot<K, V, HAS_V, C>(a.p, plan, L.pass);
         return;
     }
-    if (ctrl[kCtrlUnsorted] == 0)
+    if (unsorted == 0)
         return;
     const uint32_t n = a.p.n;
     const uint32_t buf = (finish >> kFinishDstShift) & 3u;  // where k_finish wrote
@@ -878,13 +848,13 @@ __global__ __launch_bounds__(THREADS) RS_FINISH_SGPRS void k_seg_finish(SegFinis
     __shared__ FinishLds<K, THREADS, ITEMS> L;
     if (!(a.ctrl[kSegPassMask] & kSegAnyFinish))
         return;
-    if (threadIdx.x == 0)
-        L.done = 0;
-    __syncthreads();
     for (uint32_t i = blockIdx.x * THREADS + threadIdx.x; i < a.rest.num_words;
          i += gridDim.x * THREADS)
         a.rest.words[i] = 0;
-    FinishFound found;
+    uint32_t places = 0;
+    if (threadIdx.x == 0)
+        L.longs = 0;
+    __syncthreads();  // there may be no tile
     const uint32_t tiles = std::min(a.ctrl[kSegTiles], a.max_tiles);
     // groups of sweep tiles: a segment's record takes three dependent loads
     const uint32_t per = a.tile / (T * a.group);
@@ -904,13 +874,15 @@ __global__ __launch_bounds__(THREADS) RS_FINISH_SGPRS void k_seg_finish(SegFinis
         const uint32_t size = __builtin_amdgcn_readfirstlane(rec.size);
         uint32_t tb = __builtin_amdgcn_readfirstlane(
             (tile - rec.tile_start) * a.tile + (item - tile * per) * a.group * T);
-        for (uint32_t g = 0; g < a.group && tb < size; ++g, tb += T)
+        for (uint32_t g = 0; g < a.group && tb < size; ++g, tb += T) {
             finish_tile<K, V, HAS_V, THREADS, ITEMS>(
                 L, sk, sv, dk, dv, size, tb, (int)(m.low * kRadixBits),
-                dst == kBufOut ? a.kmap : 0u, found.longs,
-                [&](uint32_t i) { finish_report(L, a.ctrl, a.rest, found, i, seg); });
+                dst == kBufOut ? a.kmap : 0u,
+                [&](uint32_t i) { finish_report(L, places, i, seg); });
+            finish_list(L, a.ctrl, a.rest, places, false);
+        }
     }
-    finish_end(L, a.ctrl, a.rest, found);
+    finish_list(L, a.ctrl, a.rest, places, true);
 }
 
 struct SegLastArgs {

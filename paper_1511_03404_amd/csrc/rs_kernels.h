@@ -104,8 +104,9 @@ struct HistArgs {
     uint32_t fine;        // small sorts: up to 16 keys per thread, key by key,
                           // instead of batches (n <= 16 * grid * kHistThreads)
     void *sample;         // when not null: a sample of the mapped keys for k_plan
-    uint32_t sample_every;  // a batch in this many gives to the sample,
-    uint32_t sample_step;   // one key of a thread in this many
+    uint32_t sample_every;  // a batch in 2^this many gives to the sample,
+    uint32_t sample_step;   // one key of a thread in 2^this many; with fine, one
+                            // of every thread number, by the workgroups in turn
 };
 
 // Counters of k_hist: per digit position and per bin, kHistCols columns of
@@ -210,8 +211,8 @@ __global__ __launch_bounds__(kHistThreads) void k_hist(HistArgs a)
                     hist_add<R, COLS>(tab, p, digit_of<R>(k, p * R), col);
             }
         }
-        if (a.sample && gtid % a.sample_step == 0)
-            ((K *)a.sample)[gtid / a.sample_step] = map_in(key[0], a.kmap);
+        if (a.sample && t * gridDim.x / kHistThreads == blockIdx.x)
+            ((K *)a.sample)[t] = map_in(key[0], a.kmap);
         __syncthreads();
         if (a.part)
             hist_store<D, R, COLS>(tab, a.part + (uint64_t)blockIdx.x * ((uint32_t)D << R), t);
@@ -245,9 +246,9 @@ __global__ __launch_bounds__(kHistThreads) void k_hist(HistArgs a)
             for (int i = 0; i < NK; ++i)
                 key[i] = map_in(key[i], a.kmap);
         }
-        if (a.sample && b % a.sample_every == 0 && t % a.sample_step == 0)
-            ((K *)a.sample)[b / a.sample_every * (kHistThreads / a.sample_step) +
-                            t / a.sample_step] = key[0];
+        const uint32_t bs = (uint32_t)b >> a.sample_every, ts = t >> a.sample_step;
+        if (a.sample && bs << a.sample_every == (uint32_t)b && ts << a.sample_step == t)
+            ((K *)a.sample)[bs * (kHistThreads >> a.sample_step) + ts] = key[0];
 #pragma unroll
         for (int p = 0; p < D; ++p) {
 #pragma unroll
@@ -1167,15 +1168,16 @@ __device__ __forceinline__ void pass_tile(PassLds<K, C, HAS_V> &L, const K *tk, 
 
 namespace rs {
 
-// The pass slot a.pass, by a workgroup of k_pass (or of k_last).
+// The pass slot a.pass, whose plan word is `plan`, by a workgroup of k_pass (or of
+// a kernel that holds a pass; each reads the plan word beside its own words, so
+// that it waits for memory once).
 template <typename K, typename V, bool HAS_V, typename C, typename Lds>
-__device__ __forceinline__ void pass_slot(const PassArgs a, Lds &L)
+__device__ __forceinline__ void pass_slot(const PassArgs a, uint32_t plan, Lds &L)
 {
     constexpr int THREADS = C::kThreads;
     constexpr int T = C::kTile;
 
     const uint32_t t = threadIdx.x;
-    const uint32_t plan = __builtin_amdgcn_readfirstlane(a.ctrl[kCtrlPlan + a.pass]);
     if (!(plan & kPlanRun)) {
         if (plan & (kPlanCopyIn | kPlanCopyInV)) {
             // no pass moves data: copy in -> out (each array not sorted in place)
@@ -1252,7 +1254,7 @@ template <typename K, typename V, bool HAS_V, typename C>
 __global__ __launch_bounds__(C::kThreads) void k_pass(PassArgs a)
 {
     __shared__ std::conditional_t<C::kWide, WideLds<K, C, HAS_V>, PassLds<K, C, HAS_V>> L;
-    pass_slot<K, V, HAS_V, C>(a, L);
+    pass_slot<K, V, HAS_V, C>(a, __builtin_amdgcn_readfirstlane(a.ctrl[kCtrlPlan + a.pass]), L);
 }
 
 // ---------------------------------------------------------------------------

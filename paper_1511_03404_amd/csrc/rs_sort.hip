@@ -646,18 +646,16 @@ static rs_status run_sort(rs_context *ctx, const K *kin, const K *vin, K *kout, 
         const uint32_t batches = ha.nvec * (16 / sizeof(K)) / 16384;
         sample = wb + L.off_tmp_k;
         ha.sample = sample;
-        ha.sample_every = 1;
         if (ha.fine) {
-            ha.sample_step = L.hist_blocks;  // of all threads
             sample_count = kHistThreads;
         } else {
-            while (batches / ha.sample_every > want)
-                ha.sample_every *= 2;
-            const uint32_t from = (batches + ha.sample_every - 1) / ha.sample_every;
-            ha.sample_step = 1;
-            while (from * (kHistThreads / ha.sample_step) > want && ha.sample_step < kHistThreads)
-                ha.sample_step *= 2;
-            sample_count = std::min(from * (kHistThreads / ha.sample_step),
+            while (batches >> ha.sample_every > want)
+                ++ha.sample_every;
+            const uint32_t from = (batches + (1u << ha.sample_every) - 1) >> ha.sample_every;
+            while (from * (kHistThreads >> ha.sample_step) > want &&
+                   kHistThreads >> ha.sample_step > 1)
+                ++ha.sample_step;
+            sample_count = std::min(from * (kHistThreads >> ha.sample_step),
                                     kSampleMax * kSampleThreads);
         }
         // repeats of `sample_count` draws from runs of kFinishRepeatMean
