@@ -193,11 +193,18 @@ __device__ __forceinline__ PairRuns pair_runs(uint32_t g, uint32_t w, uint32_t n
 // merge_chains.  A step is one trip to memory, so for few splits the steps are
 // what it takes: of 2^24 32-bit pairs 11.4 us a level by halving, 7.8 by fifths
 // (2^20 keys in all 130 -> 117).  With more splits the scattered lines that the
-// probes fetch cost more than the steps saved: 2^26 keys 2608 us by halving,
-// 2697 by fifths, and so do 8 or 64 probes a step at any size.  One wave per
-// workgroup spreads the fetches over the chip.
+// probes fetch cost more than the steps saved, and so do 8 or 64 probes a step
+// at any size.  The whole sort in us, by halving / by fifths:
+//               2^24         3 2^23       2^25         2^26
+//   32-bit keys  543 / 534    795 / 807  1025 / 1053  2603 / 2691
+//   32-bit pairs 740 / 730   1315 / 1268 1643 / 1624  3289 / 3396
+//   64-bit keys  729 / 718   1368 / 1327 1749 / 1745  3554 / 3701
+//   64-bit pairs 1476 / 1423 2271 / 2245 2933 / 2946
+// One wave per workgroup spreads the fetches over the chip.
 constexpr uint32_t kSplitLanes = 4;
-constexpr uint32_t kSplitTiles = 8192;  // at most, for kSplitLanes
+// splits of a level (one for every 2048 outputs), at most, for kSplitLanes
+template <typename K, bool HAS_V>
+constexpr uint32_t kSplitTiles = sizeof(K) == 4 && !HAS_V ? 8192 : 12288;
 
 template <typename K, int TILE, uint32_t LANES>
 __global__ __launch_bounds__(kWave) void k_merge_split(MergeLevelArgs a)

@@ -14,7 +14,7 @@ struct MergeLaunch {
     }
     static void split(const MergeLevelArgs &a, hipStream_t s)
     {
-        if (a.tiles <= kSplitTiles)
+        if (a.tiles <= kSplitTiles<K, HAS_V>)
             hipLaunchKernelGGL((k_merge_split<K, S::kPassTile, kSplitLanes>),
                                dim3((a.tiles * kSplitLanes + kWave - 1) / kWave), dim3(kWave), 0, s,
                                a);
