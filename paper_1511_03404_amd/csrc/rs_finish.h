@@ -86,7 +86,12 @@ struct FinishArgs {
 
 constexpr int kFinishThreads = 256;
 constexpr int kFinishItems = 4;
-// sorts of up to kFinishFused elements sweep in a pass's launch
+// Sorts of up to kFinishFused elements sweep in a pass's launch (k_pass_finish).
+// The same line for every kind: whole sorts of uniform keys in us, in that launch
+// / in one of its own, 2^20 + 1, 1250000 and 1700000 elements: 32-bit keys 57.3 /
+// 57.8, 57.9 / 56.1, 69.6 / 64.9; pairs 62.1 / 63.0, 63.7 / 62.5, 74.0 / 71.6;
+// 64-bit keys 72.3 / 72.7, 76.6 / 74.1, 88.1 / 84.6; pairs 75.7 / 78.7, 81.1 / 78.8,
+// 93.5 / 88.1.
 constexpr int kFinishItemsFused = 2;
 constexpr uint32_t kFinishFused = 1u << 20;
 
