@@ -525,7 +525,7 @@ def measure_segmented(args, torch, rs, datagen, dev, with_cpu=True, quick=False)
     large = sizes[sizes > 16384]
     # the elements that each pass moved, from the large segments' records and
     # plans in the workspace (each segment has its own: csrc/rs_segmented.h)
-    moved = segment_moves(ws, S, cfg["radix_bits"])
+    moved = segment_moves(ws, S, cfg["radix_bits"], large)
     pass_ms = [ms for j, ms in enumerate(kern.get("k_seg_pass_u32", []))
                if moved[j % len(moved)]]
     roofline = None
@@ -599,9 +599,11 @@ def measure_segmented(args, torch, rs, datagen, dev, with_cpu=True, quick=False)
     return out
 
 
-def segment_moves(ws, nseg, r):
+def segment_moves(ws, nseg, r, large_sizes):
     """Elements of the large segments that each digit pass of the batched sort
-    of 32-bit keys in workspace `ws` moved."""
+    of 32-bit keys in workspace `ws` moved.  The records are found by the layout of
+    csrc/rs_sort.hip (make_seg_layout): that they hold the batch's large segments
+    is checked."""
     def up(x):
         return -(-x // 256) * 256
     d = -(-32 // r)
@@ -610,6 +612,10 @@ def segment_moves(ws, nseg, r):
     n = int(ws[:256].cpu().numpy().view(np.uint32)[SEG_LARGE])
     size = ws[large:large + 16 * n].cpu().numpy().view(np.uint32).reshape(n, 4)[:, 2]
     f = ws[flags:flags + 4 * n].cpu().numpy().view(np.uint32)
+    assert np.array_equal(np.sort(size), np.sort(large_sizes)), \
+        "the workspace's segment records are not where this looks for them"
+    assert not (f & 0xF000).any() and ((f >> 8 & 15) < d).all(), \
+        "the segments' plans are not where this looks for them"
     low = (f >> 8) & 15 if r == 8 else 0
     return [int(size[((f >> p & 1) == 0) & (p >= low)].sum(dtype=np.int64)) for p in range(d)]
 
