@@ -7,7 +7,7 @@ import torch
 
 import datagen
 from test_gpu_finish import (ANY_FINISH, FINISH, GIANT, KINDS, LONG_LEN, LONGER_LEN, PASS_MASK,
-                             UNSORTED, batch_checked, clusters, dev, sort_checked)
+                             SLOTS, UNSORTED, batch_checked, clusters, dev, sort_checked)
 
 pytestmark = pytest.mark.gpu
 
@@ -183,3 +183,17 @@ def test_segment_of_groups_takes_every_digit(rs, oracle_lib, pairs):
     print(f"case pairs={pairs}", flush=True)
     w = batch_checked(rs, oracle_lib, [keys, datagen.keys("uniform", 100, 32)], pairs)
     assert w[PASS_MASK] == 15 and w[LONG_LEN] == 0
+
+
+# the routes of sorts without long runs, at their edges: the sweep of 32-bit keys in
+# a launch of its own (above 2^20), every digit above what two of them leave short
+# enough, and the smallest sorts of more than one workgroup
+@pytest.mark.parametrize("bits,pairs,n,sweeps", [
+    (32, False, (1 << 20) + 77, True), (32, True, (1 << 20) + 77, True),
+    (32, False, (1 << 21) + 4095, False), (32, True, (1 << 21) + 4095, False),
+    (64, True, 8193, True), (64, False, 16385, True), (32, True, 16385, True)])
+def test_route_at_the_edges(rs, oracle_lib, bits, pairs, n, sweeps):
+    print(f"case bits={bits} pairs={pairs} n={n}", flush=True)
+    w = sort_checked(rs, oracle_lib, datagen.keys("uniform", n, bits, seed=3), pairs)
+    assert bool(w[FINISH] & 1) == sweeps and not w[UNSORTED]
+    assert (w[SLOTS] < bits // 8) == sweeps
