@@ -828,8 +828,8 @@ __global__ __launch_bounds__(C::kThreads) void k_last(LastArgs a)
 // ---------------------------------------------------------------------------
 // The same for the large segments of a segmented sort, each with its own
 // finish shift (k_seg_scan).  2000 segments of 2^4 to 2^20 32-bit pairs: four
-// passes of 738 us each before, two and a sweep of 1020 us now; 24 of 2^10 to
-// 2^22 64-bit pairs: eight passes of 62 us, now three and a sweep of 50 us.
+// passes of 738 us each before, two and a sweep of 828 us now; 24 of 2^10 to
+// 2^22 64-bit pairs: eight passes of 62 us, now three and a sweep of 48 us.
 // With runs of up to 16 the sweep is bound by its compares, not by HBM (590 us).
 
 struct SegFinishArgs {
